@@ -94,9 +94,10 @@ enum {
 
 /* md_params.flags bits 8-9: workgroups of the compacted kernel per home cell, each taking
  * every s-th group of the cell's home atoms (the work units of the loop over home atoms of
- * Algorithm 1, spread over more compute units). 0 chooses automatically (4 on grids of at
- * most 64 cells, 2 up to 128, else 1); MD_PAIR_SPLIT(s) forces s = 1, 2 or 4. Results are the
- * same bits for every s. Not with MD_PAIR_PREDICATED (MD_ERR_INVALID_ARG). */
+ * Algorithm 1, spread over more compute units). 0 chooses automatically (1 on grids of more
+ * than 256 cells, more on smaller ones); MD_PAIR_SPLIT(s) forces s = 1, 2 or 4. On grids of
+ * at most 256 cells the neighbour list may also be cut into slices of a workgroup each,
+ * chosen from the grid and the atom count alone. Results are the same bits for every s. Not with MD_PAIR_PREDICATED (MD_ERR_INVALID_ARG). */
 #define MD_PAIR_SPLIT_MASK (3u << 8)
 #define MD_PAIR_SPLIT(s) ((uint32_t)((s) == 1 ? 1 : (s) == 2 ? 2 : (s) == 4 ? 3 : 0) << 8)
 
@@ -177,8 +178,8 @@ md_status md_forces_f32_stages(const md_params* p, int64_t n_atoms, const float*
  *     per device, created when the library's code is first used on that device and held
  *     until the process ends. Its device address is looked up once per device, on the
  *     first call with that device current.
- *   - Systems whose md_workspace_bytes(p, n_atoms, 0) exceeds that size are rejected with
- *     MD_ERR_CAPACITY before anything is enqueued (at 8 atom types about 230,000 atoms
+ *   - Systems whose md_workspace_bytes(p, n_atoms, 0), without the up to 128 KiB of energy
+ *     partials of small grids, exceeds that size are rejected with MD_ERR_CAPACITY before anything is enqueued (at 8 atom types about 230,000 atoms
  *     of the 0.1 atoms/A^3 systems). Other argument errors as for md_forces_f32.
  *   - Every call on one device uses that device's one array: calls that overlap on one
  *     device (other streams, other host threads) race and give undefined results;

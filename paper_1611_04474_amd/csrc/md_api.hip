@@ -13,7 +13,10 @@ namespace md {
 // Workspace of md_forces_f32_noalloc: one per device, held from the library's first use
 // on that device until the process ends. Host code reaches it only through the device
 // address that hipGetSymbolAddress returns for the current device (noalloc_scratch).
-constexpr size_t kScratchBytes = (size_t)MD_NOALLOC_MAX_WORKSPACE_BYTES;
+// The array is larger than the size limit on systems by the most that the energy partials of
+// small grids (Plan::small_grid_parts) add, which the limit does not count.
+constexpr size_t kScratchLimit = (size_t)MD_NOALLOC_MAX_WORKSPACE_BYTES;
+constexpr size_t kScratchBytes = kScratchLimit + sizeof(long long) * kFsMaxSplit * kFsMaxSlices * kFsMaxCells;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -87,9 +90,61 @@ static bool uses_compact(const md_params* p, int real_bytes) {
          !(real_bytes == 8 && (p->flags & MD_ACCUM_F32_ATOMIC));
 }
 
+// Split of a home cell's work (FsWork). With fewer cells than compute units the chip is idle
+// unless a cell is shared out: parts of the home atoms repeat the staging of the neighbour
+// list and its flush, slices of the list repeat the work around each group of home atoms (its
+// loads, window searches, partial FIFO passes and sums), and either pays only until there is a
+// workgroup per compute unit. The choice is the least time of a model of the kernel in
+// microseconds,
+//   rounds x (start + loops x (staging of L + groups per wave x (group + filter and force of L)))
+// with L the atoms of a slice, fitted to a sweep of 1-8 slices x 1-8 parts (pair stage and
+// binning of 3,000 to 92,224 atoms; within 15% over the sweep, and its choice within 7% of the
+// sweep's best). Whole calls, one split before (parts only, at most 4) and now: 3,000 atoms in
+// 8 cells 103 -> 66 us, 9,001 in 40 73 -> 61, 6,000 in 27 68 -> 54, 20,000 in 64 92 -> 82,
+// float64 3,000 427 -> 138. At 343 and 486 cells (one workgroup each) a second slice
+// costs 13% and 30%, so grids of more than 256 cells stay whole. The full shell stores each
+// atom's sum without atomics, so its slices stay in one workgroup.
+FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bool half) {
+  FsWork best{1, 1};
+  const uint32_t v = (flags & MD_PAIR_SPLIT_MASK) >> 8;
+  if (n > 0 && n_cells > 0 && n_cells <= kFsMaxCells) {
+    const bool f64 = real_bytes == 8;
+    const double start = f64 ? 5.2 : 11.1, stage = 0.0033, group = f64 ? 42.5 : 9.0,
+                 pair = f64 ? 0.0252 : 0.0026, lds = f64 ? 1472 : 3008;
+    const double groups = (double)n / (double)n_cells / 4.0;   // of 4 home atoms, per cell
+    const double list = (half ? 14.0 : 27.0) * (double)n / (double)n_cells;   // staged atoms
+    double t_best = 0;
+    for (int s = 1; s <= (half ? kFsMaxSlices : 1); ++s)
+      for (int g = 1; g <= kFsMaxSplit; ++g) {
+        const double wgs = (double)(n_cells * s * g) / 256.0;
+        const double rounds = wgs < 3.0 ? ceil(wgs) : wgs + 0.5;
+        const double cut = fmax((double)s, ceil(list / lds)), loops = ceil(cut / s);
+        const double waves = groups / g / 16.0, per_wave = waves < 1.0 ? 1.0 : waves + 0.2;
+        const double t =
+            rounds * (start + loops * (stage * list / cut + per_wave * (group + pair * list / cut)));
+        if (t_best == 0 || t < t_best) {
+          t_best = t;
+          best = FsWork{g, s};
+        }
+      }
+  }
+  if (v) best.split = v == 1 ? 1 : v == 2 ? 2 : 4;
+  return best;
+}
+
 // Grid rule: n_d = floor(L_d / r_cut), one cell fewer when L_d/n_d exceeds r_cut by
 // less than 1e-3 A (so rounding of a coordinate at a cell face never hides a pair),
 // and at least 2 cells per axis (L >= 2 r_cut keeps the minimum image unique).
+static bool half_shell(const md_params* p) {
+  return !(p->flags & (MD_ACCUM_F32_ATOMIC | MD_PAIR_FULL_SHELL));
+}
+
+// Workgroups of the compacted kernel per home cell.
+static int64_t fs_units(const md_params* p, const Plan& pl, int64_t n) {
+  const FsWork w = md_fs_work(p->flags, pl.real_bytes, pl.n_cells, n, half_shell(p));
+  return (int64_t)w.split * w.slices;
+}
+
 md_status make_plan(const md_params* p, int64_t n, int real_bytes, Plan* pl) {
   md_status s = check_params(p);
   if (s != MD_OK) return s;
@@ -129,7 +184,15 @@ md_status make_plan(const md_params* p, int64_t n, int real_bytes, Plan* pl) {
   o = align_up(o + (compact ? sizeof(long long) * 3 * (real_bytes / 4) * nn
                             : (size_t)real_bytes * kSlots * 3 * nn));
   pl->off_facc = o;      o = align_up(o + sizeof(float) * 3 * nn);
-  pl->off_epart = o;     o = align_up(o + sizeof(double) * pl->n_tasks);
+  // energy partials: one float64 per task, or one (float64: two) int64 per workgroup of the
+  // compacted kernel, as many as any flags could choose
+  pl->off_epart = o;
+  const size_t task_parts = align_up(sizeof(double) * pl->n_tasks);
+  const size_t unit_parts = cells <= kFsMaxCells ? align_up(sizeof(long long) * (real_bytes / 4) *
+                                                            kFsMaxSplit * kFsMaxSlices * cells)
+                                                 : 0;
+  pl->small_grid_parts = unit_parts > task_parts ? unit_parts - task_parts : 0;
+  o += task_parts + pl->small_grid_parts;
   pl->off_lj = o;        o = align_up(o + (size_t)real_bytes * 2 * kMaxTypes * kMaxTypes);
   pl->off_paircount = o; o = align_up(o + sizeof(int32_t) * 2 * nn);
   // binning with per-block LDS histograms when the grid fits in LDS
@@ -207,9 +270,11 @@ SysArgs<Real> make_args(const md_params* p, const Plan& pl, int64_t n, const Rea
   a.ewald_alpha = (p->flags & MD_COULOMB_EWALD) ? (Real)p->ewald_alpha : Real(0);
   a.flags = p->flags;
   a.compact = uses_compact(p, (int)sizeof(Real)) ? 1 : 0;
-  a.half_shell =
-      (a.compact && !(p->flags & (MD_ACCUM_F32_ATOMIC | MD_PAIR_FULL_SHELL))) ? 1 : 0;
-  a.fs_split = a.compact ? md_fs_split(p->flags, pl.n_cells) : 1;
+  a.half_shell = a.compact && half_shell(p) ? 1 : 0;
+  const FsWork fw = a.compact ? md_fs_work(p->flags, (int)sizeof(Real), pl.n_cells, n, a.half_shell != 0)
+                              : FsWork{1, 1};
+  a.fs_split = fw.split;
+  a.fs_slices = a.fs_su = fw.slices;
   return a;
 }
 
@@ -303,7 +368,7 @@ md_status md_workspace_layout(const md_params* p, int64_t n_atoms, int double_pr
   out->energy_partials = pl.off_epart;
   out->n_energy_partials =
       md::uses_compact(p, double_precision ? 8 : 4)
-          ? pl.n_cells * md::md_fs_split(p->flags, pl.n_cells)
+          ? pl.n_cells * md::fs_units(p, pl, n_atoms)
           : pl.n_tasks;
   out->z_split = pl.off_zsplit;
   out->total_bytes = pl.total;
@@ -339,7 +404,7 @@ md_status md_forces_f32_noalloc(const md_params* p, int64_t n_atoms, const float
   // every argument check, the size limit included, before any HIP call
   md_status s = md::make_plan(p, n_atoms, 4, &pl);
   if (s != MD_OK) return s;
-  if (pl.total > md::kScratchBytes) return MD_ERR_CAPACITY;
+  if (pl.total - pl.small_grid_parts > md::kScratchLimit) return MD_ERR_CAPACITY;
   if (d_status && ((uintptr_t)d_status & 3)) return MD_ERR_INVALID_ARG;
   // pointer checks of md_forces_f32 (the workspace is checked against a stand-in with the
   // scratch array's size and alignment)

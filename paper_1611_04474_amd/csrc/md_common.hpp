@@ -31,18 +31,20 @@ __host__ __device__ inline int md_pair_drain(uint32_t flags) {
   return v == 0 ? 2 : v == 1 ? 1 : v == 2 ? 3 : 4;
 }
 
-// Workgroups of the compacted pair kernel per home cell, each taking every split-th group
-// of the cell's home atoms: MD_PAIR_SPLIT(s) in md_params.flags, or (field 0) automatic:
-// grids of fewer than 128 (4) or 64 (2) cells take 2 or 4, so that the 256 compute units get
-// work; larger grids take 1 (a split repeats the staging and the neighbour-side flush, which
-// measured 25% slower at 486 cells).
-__host__ __device__ inline int md_fs_split(uint32_t flags, int64_t n_cells) {
-  const uint32_t v = (flags & MD_PAIR_SPLIT_MASK) >> 8;
-  if (v) return v == 1 ? 1 : v == 2 ? 2 : 4;
-  if (n_cells <= 0) return 1;
-  const int64_t s = 256 / n_cells;   // workgroups per compute unit's worth of cells
-  return s >= 4 ? 4 : s >= 2 ? 2 : 1;
-}
+// Work units of the compacted pair kernel per home cell. The neighbour list of a cell is
+// cut into `slices` equal slices (more where one would not fit the LDS), the cell's groups of
+// home atoms into `split` interleaved parts, and one workgroup takes a slice and a part.
+// A home atom's partial force is rounded to fixed point once per slice, so the number of
+// slices depends on the grid and the atom count alone, never on the split that a caller
+// forces or on the batch a system runs in: those change which workgroup does the work and
+// not one bit of the result.
+struct FsWork {
+  int split;    // parts of the home atoms
+  int slices;   // slices of the neighbour list
+};
+constexpr int kFsMaxSplit = 8, kFsMaxSlices = 8;
+constexpr int kFsMaxCells = 256;   // larger grids: one workgroup per cell unless forced
+FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bool half);
 
 struct WsHeader {
   uint32_t status;
@@ -94,6 +96,8 @@ struct Plan {
       off_part, off_facc, off_epart, off_lj, off_paircount, off_bhist, off_bstat, off_order,
       off_cost,
       off_zsplit, off_ukey, off_upos, off_kpart, total;
+  size_t small_grid_parts;      // bytes by which the energy partials of a grid of at most
+                                // kFsMaxCells cells exceed one word per task
   int bin_blocks;               // blocks of the LDS-histogram binning pass (0: global atomics)
   int64_t bin_chunk;            // atoms per such block
 };
@@ -160,7 +164,11 @@ struct SysArgs {
                                //    or, float32 only, facc with MD_ACCUM_F32_ATOMIC)
   int half_shell;              // 1: the compacted kernel visits each pair once and adds
                                //    into acc64 with integer atomics (acc64 starts at zero)
-  int fs_split;                // compacted-kernel workgroups per home cell (md_fs_split)
+  int fs_split;                // parts of a home cell's atoms, one workgroup each (FsWork)
+  int fs_slices;               // slices of its neighbour list, at least (FsWork)
+  int fs_su;                   // slices spread over workgroups: fs_split x fs_su workgroups
+                               // per home cell (fs_slices, or 1 in a batch that fills the
+                               // chip: then one workgroup takes the slices in turn)
 };
 
 // Up to kBatchMax systems evaluated by one launch of each kernel of the path. The
@@ -181,6 +189,8 @@ struct Batch {
     return s;
   }
 };
+
+static_assert(sizeof(Batch<float>) <= 4096 - 64, "kernel arguments");
 
 // Per-type sigma and epsilon, mixed into the LJ table by the binning stage.
 struct TypeTable {

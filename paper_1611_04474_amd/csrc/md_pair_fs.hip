@@ -160,6 +160,7 @@ struct Hdr {
   Seg seg[kMaxSeg];
   int n_seg;
   int total;        // neighbour-list length
+  int n_slice, len; // slices that it is staged in, and their length
   int iters;        // binary-search steps that cover the longest segment
   int next;         // next group of home atoms to hand out
   int done;         // waves that have added their energy to esum
@@ -372,7 +373,7 @@ __device__ inline void lds_store_u16_lanes4(uint32_t a0, uint32_t a1, uint32_t a
 // kHalf: the half shell (64-bit fixed-point sums only). kDrain: force batches per drain.
 template <typename Real, bool kHalf, int kCoul, bool kClamp, bool kDiag, int kDrain>
 __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real>& a, int cap,
-                                                              int64_t cellA, int part) {
+                                                              int64_t cellA, int unit) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
   constexpr bool kF32 = sizeof(Real) == 4;
   constexpr int kImg = kHalf ? 14 : 27;   // neighbour images
@@ -500,6 +501,10 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
     if (lane == 0) {
       H.n_seg = __builtin_popcountll(heads);
       H.total = tot;
+      // slices: equal, at most cap (a multiple of 64) long
+      const int ns = max(max(1, a.fs_slices), (tot + cap - 1) / cap);
+      H.n_slice = ns;
+      H.len = ((tot + ns - 1) / ns + 63) & ~63;
       H.done = 0;
       H.esum[0] = H.esum[1] = 0;
       int it = 0;
@@ -515,9 +520,13 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
   const int n_grp_q = (nA + kQ - 1) / kQ;
   // this workgroup's share of the home cell: groups part, part + n_split, part + 2 n_split, ..
   const int n_split = a.fs_split;
+  const int part = unit % n_split;
+  // the neighbour list in n_slice slices of H.len staged atoms (the last one shorter); this
+  // workgroup takes slices unit / n_split, + fs_su, ...
+  const int n_slice = H.n_slice;
   // largest home-side partial of one slice (see kAccRange)
   const float home_max = (kHalf ? kAccRange - 14.f * (float)a.fs_split * kNbrPartialMax : kAccRange) /
-                         (float)max(1, (total + cap - 1) / cap);
+                         (float)n_slice;
   const Real R = vsqrt(rc2) + Real(kWin);
   // energy: float32 in units of 2^-24 kcal/mol; float64 two-word (e_fix, e_lo): exact,
   // order-independent sums
@@ -529,13 +538,21 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
   // LDS byte address where FIFO k of this wave starts: fk0 + 2 k kFifo
   const uint32_t fk0 = (uint32_t)(LL.fifo + 2 * w * kWaveFifo);
 
-  for (int P0 = 0; P0 < total; P0 += cap) {
-    const int P1 = min(total, P0 + cap);
+  // the slice length is read again where it is needed: scalar registers are scarce
+  auto slice_len = [&]() __attribute__((always_inline)) {
+    return __builtin_amdgcn_readfirstlane(H.len);
+  };
+  for (int P0 = (unit / n_split) * slice_len(); P0 < total; P0 += a.fs_su * slice_len()) {
+    const int P1 = min(total, P0 + slice_len());
     // stage the neighbour-list slice [P0, P1): wave w copies images w and w + 16 (both z
     // halves, to their two segments), issuing all loads of up to 4 x 64 atoms before the
     // LDS stores; the half shell also clears the slots' accumulators
     for (int m = w; m < kImg; m += kNW) {
       const Img im = H.img[m];
+      // nothing of this image in the slice
+      if ((im.off[0] >= P1 || im.off[0] + im.n0 <= P0) &&
+          (im.off[1] >= P1 || im.off[1] + (im.count - im.n0) <= P0))
+        continue;
       // o_g = o - h: the origin in this image's frame
       const Real og0 = O0 - ((im.grp & 1) ? L0 : Real(0));
       const Real og1 = O1 - ((im.grp & 2) ? L1 : Real(0));
@@ -1031,7 +1048,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
         const Img im = H.img[m];
         for (int e = lane; e < im.count; e += 64) {
           const int dst = e < im.n0 ? im.off[0] + e : im.off[1] + (e - im.n0);
-          if (dst < P0 || dst >= P1) continue;
+          if (dst < P0 || dst >= P1) continue;   // staged by another slice
           const int64_t src = im.start + e;
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
@@ -1065,7 +1082,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
       }
       // the next slice clears the accumulators; after the last one nothing waits here, so
       // the workgroup can end while its atomics are still on their way
-      if (P0 + cap < total) __syncthreads();
+      if (P0 + a.fs_su * slice_len() < total) __syncthreads();
     }
   }
 
@@ -1098,7 +1115,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
     }
     last = __builtin_amdgcn_readfirstlane(__shfl(rank, 0)) == kNW - 1;
     if (last && lane == 0) {
-      const int64_t slot = part * a.n_cells + cellA;
+      const int64_t slot = unit * a.n_cells + cellA;
       long long* ep = reinterpret_cast<long long*>(a.epart);
       if constexpr (kF32) {
         ep[slot] = __hip_atomic_load(&H.esum[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1116,7 +1133,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
     // candidates of Algorithm 1: every (home atom, other neighbour-list atom), counted
     // from both atoms in the full shell (halved after the kernel) and once in the half
     // shell; the neighbour slots this kernel actually filtered come separately
-    if (w == 0 && part == 0) {
+    if (w == 0 && unit == 0) {
       const unsigned long long nA_ = (unsigned long long)nA;
       const unsigned long long cand =
           kHalf ? nA_ * (nA_ - 1) / 2 + nA_ * (unsigned long long)(total - nA)
@@ -1140,11 +1157,11 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
 // to the header's two clock sums: their ratio is the clock the kernel ran at, weighted by
 // workgroup time. Called by lane 0 of the workgroup's last wave to finish.
 template <typename Real>
-__device__ inline void record_cost(const SysArgs<Real>& a, int64_t cell, int part, uint64_t t0,
+__device__ inline void record_cost(const SysArgs<Real>& a, int64_t cell, int unit, uint64_t t0,
                                    uint64_t c0, bool first) {
   const uint64_t dc = __builtin_amdgcn_s_memtime() - c0;
   const uint64_t dt = __builtin_amdgcn_s_memrealtime() - t0;
-  if (part == 0) a.cost[cell] = dt < 0xffffffffull ? (uint32_t)dt : 0xffffffffu;
+  if (unit == 0) a.cost[cell] = dt < 0xffffffffull ? (uint32_t)dt : 0xffffffffu;
   atomicAdd(&a.hdr->clock[0], (unsigned long long)dc);
   atomicAdd(&a.hdr->clock[1], (unsigned long long)dt);
   if (first) {
@@ -1159,11 +1176,11 @@ void k_pair_fs(SysArgs<Real> a, int cap) {
   // home cells in the order the binning chose (longest first)
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   const uint64_t c0 = __builtin_amdgcn_s_memtime();
-  // workgroup b: cell order[b % n_cells], part b / n_cells (every cell's first part first)
+  // workgroup b: cell order[b % n_cells], unit b / n_cells (every cell's first unit first)
   const int64_t cell = a.order[blockIdx.x % a.n_cells];
-  const int part = (int)(blockIdx.x / a.n_cells);
-  const bool last = pair_fs<Real, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, cell, part);
-  if (last && (threadIdx.x & 63) == 0) record_cost(a, cell, part, t0, c0, blockIdx.x == 0);
+  const int unit = (int)(blockIdx.x / a.n_cells);
+  const bool last = pair_fs<Real, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, cell, unit);
+  if (last && (threadIdx.x & 63) == 0) record_cost(a, cell, unit, t0, c0, blockIdx.x == 0);
 }
 
 // One launch for a batch: block b is cell order[b - cum[s]] of system s.
@@ -1172,12 +1189,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNW / 
 void k_pair_fs_batch(Batch<float> b, int cap) {
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   const uint64_t c0 = __builtin_amdgcn_s_memtime();
-  int64_t unit;
-  const int s = b.pick(blockIdx.x, unit);
-  const int64_t cell = b.sys[s].order[unit % b.sys[s].n_cells];
-  const int part = (int)(unit / b.sys[s].n_cells);
-  const bool last = pair_fs<float, kHalf, kCoul, kClamp, kDiag, kDrain>(b.sys[s], cap, cell, part);
-  if (last && (threadIdx.x & 63) == 0) record_cost(b.sys[s], cell, part, t0, c0, unit == 0);
+  int64_t blk;
+  const int s = b.pick(blockIdx.x, blk);
+  const int64_t cell = b.sys[s].order[blk % b.sys[s].n_cells];
+  const int unit = (int)(blk / b.sys[s].n_cells);
+  const bool last = pair_fs<float, kHalf, kCoul, kClamp, kDiag, kDrain>(b.sys[s], cap, cell, unit);
+  if (last && (threadIdx.x & 63) == 0) record_cost(b.sys[s], cell, unit, t0, c0, blk == 0);
 }
 
 template <bool H, int S, bool C, bool D, int R>
@@ -1245,7 +1262,7 @@ hipError_t dispatch(const SysArgs<Real>& a, const Args& args, int n_types, int64
 template <typename Real>
 hipError_t launch_pair_fs(const SysArgs<Real>& a, hipStream_t stream) {
   if (a.n == 0) return hipSuccess;
-  return dispatch(a, a, a.n_types, a.n_cells * a.fs_split, stream,
+  return dispatch(a, a, a.n_types, a.n_cells * a.fs_split * a.fs_su, stream,
                   [](auto tag, dim3 g, dim3 b, size_t sh, hipStream_t st, const SysArgs<Real>& x,
                      int cap) {
                     using Tg = decltype(tag);
@@ -1263,7 +1280,7 @@ hipError_t launch_pair_fs_batch(const Batch<float>& b0, hipStream_t stream) {
   int nt = 1;
   b.cum[0] = 0;
   for (int s = 0; s < b.n; ++s) {
-    b.cum[s + 1] = b.cum[s] + b.sys[s].n_cells * b.sys[s].fs_split;
+    b.cum[s + 1] = b.cum[s] + b.sys[s].n_cells * b.sys[s].fs_split * b.sys[s].fs_su;
     nt = b.sys[s].n_types > nt ? b.sys[s].n_types : nt;
   }
   return dispatch(b.sys[0], b, nt, b.cum[b.n], stream,

@@ -1,0 +1,50 @@
+"""How the force path's work is shared out over workgroups, at the sizes where it changes.
+
+Bars as in test_gpu_parity.py: float64 1e-12 and exact partner counts, float32 1e-5 on the
+conditioning-normalised and RMS errors, energy 1e-6."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1611_04474_amd import api
+from paper_1611_04474_amd import workloads as W
+
+from _gpu import run
+from _metrics import force_errors
+
+pytestmark = pytest.mark.gpu
+
+
+def _system(n, box, seed):
+    s = W.gen_system(n, box, seed)
+    return s, s.params()
+
+
+@pytest.mark.parametrize("double", [False, True])
+@pytest.mark.parametrize("n,box", [
+    (1, (24.5, 24.5, 24.5)),      # 8 cells, most slices of every list empty
+    (65, (24.5, 40.0, 30.0)),     # lists about one 64-atom slice long
+    (3000, (30.0, 30.0, 30.0)),   # 8 cells of more groups than one workgroup's waves
+    (4001, (97.0, 97.0, 49.0)),   # 8 x 8 x 4 = 256 cells: the largest grid that is cut
+    (4001, (97.0, 97.0, 62.0)),   # 8 x 8 x 5 = 320 cells: one workgroup per cell
+])
+def test_units_match_oracle(gpu, n, box, double):
+    """Slices of the neighbour list and parts of the home atoms, from one atom to 320 cells:
+    the oracle's forces, energy and partner counts, and the same bits however the home atoms
+    are split."""
+    print("case:", n, box, "double", double, flush=True)
+    s, p = _system(n, box, 3)
+    pos = s.pos.astype(np.float64) if double else s.pos
+    q = s.charges.astype(np.float64) if double else s.charges
+    f, e, ws, cnt = run(p, pos, s.types, q, gpu, double=double, flags=api.DIAG_COUNTERS)
+    r = oracle.forces(p, s.pos, s.types, s.charges, "bruteforce")
+    err = force_errors(f, r.force, r.abs_sum)
+    tol = 1e-12 if double else 1e-5
+    assert err["max_norm"] <= tol and err["rms"] <= tol, err
+    assert e == pytest.approx(r.energy, rel=1e-12 if double else 1e-6, abs=1e-9)
+    if double:
+        assert np.array_equal(cnt, r.count)
+    assert api.read_status(ws) == 0
+    for split in (1, 4):
+        f2, e2 = run(p, pos, s.types, q, gpu, double=double, flags=api.PAIR_SPLIT(split))[:2]
+        assert np.array_equal(f, f2) and e == e2
