@@ -48,3 +48,18 @@ def test_units_match_oracle(gpu, n, box, double):
     for split in (1, 4):
         f2, e2 = run(p, pos, s.types, q, gpu, double=double, flags=api.PAIR_SPLIT(split))[:2]
         assert np.array_equal(f, f2) and e == e2
+
+
+@pytest.mark.parametrize("n", [2040, 6000, 16384, 16385])
+def test_crowded_sort_order(gpu, n):
+    """Cells whose atoms lie in planes of x, so that the in-cell sort's buckets overflow their
+    lists, gathered from 1, 3, 8 and 9 histogram blocks (the last past the block-by-block
+    gather): every cell ordered by (z half, x, index), ties in x included."""
+    print("case: crowded sort,", n, "atoms", flush=True)
+    from test_gpu_parity import _check_binning
+    s, p = _system(n, (60.0, 37.0, 97.0), 8)
+    pos = s.pos.copy()
+    pos[: n // 2, 0] = np.float32(2.5) * np.round(pos[: n // 2, 0] / np.float32(2.5))
+    pos[:, 0] = np.clip(pos[:, 0], 0, 59.5)
+    f, e, ws, _ = run(p, pos, s.types, s.charges, gpu)
+    _check_binning(p, pos, ws, n)
