@@ -5,6 +5,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <utility>
 
 #include "md_common.hpp"
 
@@ -13,10 +14,11 @@ namespace md {
 // Workspace of md_forces_f32_noalloc: one per device, held from the library's first use
 // on that device until the process ends. Host code reaches it only through the device
 // address that hipGetSymbolAddress returns for the current device (noalloc_scratch).
-// The array is larger than the size limit on systems by the most that the energy partials of
-// small grids (Plan::small_grid_parts) add, which the limit does not count.
+// The array is larger than the size limit on systems by what the limit does not count
+// (Plan::uncounted).
 constexpr size_t kScratchLimit = (size_t)MD_NOALLOC_MAX_WORKSPACE_BYTES;
-constexpr size_t kScratchBytes = kScratchLimit + sizeof(long long) * kFsMaxSplit * kFsMaxSlices * kFsMaxCells;
+constexpr size_t kScratchBytes = kScratchLimit + 1024 + sizeof(long long) * kFsMaxSplit * kFsMaxSlices * kFsMaxCells;
+static_assert(sizeof(SysArgs<float>) <= 512, "batch arguments");
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -44,6 +46,8 @@ static md_status noalloc_scratch(void** out) {
 
 // Copies the status word of a workspace to caller memory, in stream order.
 __global__ void k_copy_status(const WsHeader* hdr, uint32_t* out) { *out = hdr->status; }
+
+constexpr size_t kArgsOffset = sizeof(WsHeader);   // Plan::off_args
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -168,6 +172,9 @@ md_status make_plan(const md_params* p, int64_t n, int real_bytes, Plan* pl) {
   pl->real_bytes = real_bytes;
   const size_t nn = (size_t)(n > 0 ? n : 1);
   size_t o = align_up(sizeof(WsHeader));
+  static_assert(kArgsOffset % 256 == 0, "alignment");
+  pl->off_args = o;      o = align_up(o + sizeof(SysArgs<float>));   // of a batched call
+  pl->uncounted = align_up(sizeof(SysArgs<float>));
   pl->off_count = o;     o = align_up(o + sizeof(int32_t) * cells);
   pl->off_start = o;     o = align_up(o + sizeof(int32_t) * (cells + 1));
   pl->off_cell = o;      o = align_up(o + sizeof(int32_t) * nn);
@@ -191,8 +198,8 @@ md_status make_plan(const md_params* p, int64_t n, int real_bytes, Plan* pl) {
   const size_t unit_parts = cells <= kFsMaxCells ? align_up(sizeof(long long) * (real_bytes / 4) *
                                                             kFsMaxSplit * kFsMaxSlices * cells)
                                                  : 0;
-  pl->small_grid_parts = unit_parts > task_parts ? unit_parts - task_parts : 0;
-  o += task_parts + pl->small_grid_parts;
+  o += task_parts > unit_parts ? task_parts : unit_parts;
+  if (unit_parts > task_parts) pl->uncounted += unit_parts - task_parts;
   pl->off_lj = o;        o = align_up(o + (size_t)real_bytes * 2 * kMaxTypes * kMaxTypes);
   pl->off_paircount = o; o = align_up(o + sizeof(int32_t) * 2 * nn);
   // binning with per-block LDS histograms when the grid fits in LDS
@@ -317,11 +324,66 @@ static bool same_kind(const md_params* x, const md_params* y) {
   return true;
 }
 
-static md_status launch_batch(const Batch<float>& b, const md_params* p, hipStream_t st) {
-  if (b.n == 0) return MD_OK;
-  if (launch_binning_batch(b, make_type_table(p), st) != hipSuccess) return MD_ERR_HIP;
-  if (launch_pair_fs_batch(b, st) != hipSuccess) return MD_ERR_HIP;
-  if (launch_finalize_batch(b, st) != hipSuccess) return MD_ERR_HIP;
+// Work units of the systems of one batched launch. A system alone may split its cells to fill
+// the chip; in a batch the others fill it, and a split only repeats staging. Each system
+// keeps as many workgroups per cell as leave none of them longer than a 512th of the batch's
+// work (two per compute unit), at most its own choice; its slices (which fix the results'
+// bits) stay, taken in turn by fewer workgroups. A cell's cost is about its atoms squared plus
+// the staging and group overhead. Systems with the costliest workgroups come first, so that
+// short ones fill the tail.
+static void batch_units(int n, SysArgs<float>* sys) {
+  double cost[kBatchMax], total = 0;
+  for (int s = 0; s < n; ++s) {
+    const double m = (double)sys[s].n / (double)sys[s].n_cells;
+    cost[s] = m * m + 60.0 * m;
+    total += cost[s] * (double)sys[s].n_cells;
+  }
+  for (int s = 0; s < n; ++s) {
+    SysArgs<float>& a = sys[s];
+    if (!(a.flags & MD_PAIR_SPLIT_MASK)) {   // a split that the caller forces stays
+      const int units = (int)fmin(64.0, ceil(cost[s] * 512.0 / total));
+      a.fs_su = units < a.fs_su ? units : a.fs_su;
+      const int split = (units + a.fs_su - 1) / a.fs_su;
+      a.fs_split = split < a.fs_split ? split : a.fs_split;
+    }
+    cost[s] /= (double)(a.fs_su * a.fs_split);
+  }
+  for (int i = 1; i < n; ++i)   // insertion sort, longest workgroups first
+    for (int k = i; k > 0 && cost[k] > cost[k - 1]; --k) {
+      std::swap(cost[k], cost[k - 1]);
+      std::swap(sys[k], sys[k - 1]);
+    }
+}
+
+// Copies the systems' arguments to their places in device memory.
+__global__ __launch_bounds__(128) void k_put_args(PutArgs p) {
+  constexpr int kWords = (int)(sizeof(SysArgs<float>) / 4);
+  static_assert(kWords <= 128 && sizeof(SysArgs<float>) % 4 == 0, "a word per thread");
+  const int t = threadIdx.x, s = blockIdx.x;
+  if (t < kWords)
+    reinterpret_cast<uint32_t*>(p.dst[s])[t] = reinterpret_cast<const uint32_t*>(&p.sys[s])[t];
+}
+
+static md_status launch_batch(int n, SysArgs<float>* sys, const md_params* p, hipStream_t st) {
+  if (n == 0) return MD_OK;
+  batch_units(n, sys);
+  Batch b;
+  b.n = n;
+  for (int s = 0; s < kBatchMax; ++s)
+    b.sys[s] = reinterpret_cast<const SysArgs<float>*>((char*)sys[s < n ? s : 0].hdr + kArgsOffset);
+  for (int s0 = 0; s0 < n; s0 += kPutMax) {
+    PutArgs pa;
+    pa.n = n - s0 < kPutMax ? n - s0 : kPutMax;
+    for (int k = 0; k < kPutMax; ++k) {
+      const int s = k < pa.n ? s0 + k : s0;
+      pa.dst[k] = const_cast<SysArgs<float>*>(b.sys[s]);
+      pa.sys[k] = sys[s];
+    }
+    hipLaunchKernelGGL(k_put_args, dim3((unsigned)pa.n), dim3(128), 0, st, pa);
+  }
+  if (launch_binning_batch(b, sys, make_type_table(p), st) != hipSuccess) return MD_ERR_HIP;
+  if (launch_pair_fs_batch(b, sys, st) != hipSuccess) return MD_ERR_HIP;
+  if (launch_finalize_batch(b, sys, st) != hipSuccess) return MD_ERR_HIP;
   return MD_OK;
 }
 
@@ -404,7 +466,7 @@ md_status md_forces_f32_noalloc(const md_params* p, int64_t n_atoms, const float
   // every argument check, the size limit included, before any HIP call
   md_status s = md::make_plan(p, n_atoms, 4, &pl);
   if (s != MD_OK) return s;
-  if (pl.total - pl.small_grid_parts > md::kScratchLimit) return MD_ERR_CAPACITY;
+  if (pl.total - pl.uncounted > md::kScratchLimit) return MD_ERR_CAPACITY;
   if (d_status && ((uintptr_t)d_status & 3)) return MD_ERR_INVALID_ARG;
   // pointer checks of md_forces_f32 (the workspace is checked against a stand-in with the
   // scratch array's size and alignment)
@@ -465,8 +527,8 @@ md_status md_forces_batched(const md_system* sys, int32_t n_sys, void* stream) {
   // batches of up to kBatchMax systems of one kind, in input order; any other system is
   // evaluated on its own.
   hipStream_t st = (hipStream_t)stream;
-  md::Batch<float> b;
-  b.n = 0;
+  md::SysArgs<float> sys_args[md::kBatchMax];
+  int n_batch = 0;
   const md_params* kind = nullptr;
   for (int32_t k = 0; k < n_sys; ++k) {
     md::Plan pl;
@@ -480,17 +542,17 @@ md_status md_forces_batched(const md_system* sys, int32_t n_sys, void* stream) {
       if (s != MD_OK) return s;
       continue;
     }
-    if (b.n == md::kBatchMax || (b.n > 0 && !md::same_kind(kind, &sys[k].p))) {
-      md_status s = md::launch_batch(b, kind, st);
+    if (n_batch == md::kBatchMax || (n_batch > 0 && !md::same_kind(kind, &sys[k].p))) {
+      md_status s = md::launch_batch(n_batch, sys_args, kind, st);
       if (s != MD_OK) return s;
-      b.n = 0;
+      n_batch = 0;
     }
-    if (b.n == 0) kind = &sys[k].p;
-    b.sys[b.n++] = md::make_args<float>(&sys[k].p, pl, sys[k].n_atoms, sys[k].d_pos,
+    if (n_batch == 0) kind = &sys[k].p;
+    sys_args[n_batch++] = md::make_args<float>(&sys[k].p, pl, sys[k].n_atoms, sys[k].d_pos,
                                         sys[k].d_type, sys[k].d_charge, sys[k].d_force,
                                         sys[k].d_energy, sys[k].d_ws);
   }
-  return md::launch_batch(b, kind, st);
+  return md::launch_batch(n_batch, sys_args, kind, st);
 }
 
 md_status md_read_device_status(const void* d_ws, void* stream, uint32_t* bits) {

@@ -153,8 +153,8 @@ __device__ inline void store_nt(P4<Real>* dst, const P4<Real>& v) {
 // Atom i (of cell c) goes to slot `slot` of the cell-major arrays that precede the in-cell
 // sort: its sort key and type as one 16-byte record, and its wrapped (x, y, z, q).
 // kNt: streaming stores (grids of at most kScanFused cells, where each block writes its own
-// range and they measured faster); larger grids' k_scatter needs L2 to merge the partial
-// lines of its scattered stores. A compile-time choice: a run-time branch between the two
+// range, and few enough atoms: streaming); larger grids' k_scatter needs L2 to merge the
+// partial lines of its scattered stores. A compile-time choice: a run-time branch between the two
 // store forms lets the compiler merge them and drop the hint.
 template <bool kNt, typename Real>
 __device__ inline void put_atom(const SysArgs<Real>& a, int64_t i, int c, int32_t slot, Real x,
@@ -207,7 +207,7 @@ constexpr int kHistPer = kBinChunkUnit / kBinThreads;
 // by the in-cell sort then. Larger grids: the histogram goes to bhist[blk][0 .. n_cells - 1]
 // and the cell and slot of each atom to cell[] and rank[], and the block clears its atoms'
 // per-atom sums.
-template <typename Real>
+template <bool kNt, typename Real>
 __device__ inline void bin_hist(const SysArgs<Real>& a, int64_t blk) {
   extern __shared__ int32_t s_h[];   // [n_cells] counts, then the status bits
   __shared__ int32_t s_tot[kBinThreads / 64];
@@ -289,26 +289,27 @@ __device__ inline void bin_hist(const SysArgs<Real>& a, int64_t blk) {
 #pragma unroll
     for (int u = 0; u < kHistPer; ++u) {
       const int64_t i = i0 + u * kBinThreads + tid;
-      if (i < i1) put_atom<true>(a, i, c[u], (int32_t)(i0 + s_h[c[u]] + rk[u]), x[u], y[u], z[u], q[u], ty[u]);
+      if (i < i1) put_atom<kNt>(a, i, c[u], (int32_t)(i0 + s_h[c[u]] + rk[u]), x[u], y[u], z[u], q[u], ty[u]);
     }
     return;
   }
   for (int64_t i = i0 + tid; i < i1; i += kBinThreads) {
     const int ci = a.cell[i];
-    put_atom<true>(a, i, ci, (int32_t)(i0 + s_h[ci] + a.rank[i]), a.pos_in[3 * i + 0],
+    put_atom<kNt>(a, i, ci, (int32_t)(i0 + s_h[ci] + a.rank[i]), a.pos_in[3 * i + 0],
              a.pos_in[3 * i + 1], a.pos_in[3 * i + 2], a.q_in[i], a.type_in[i]);
   }
 }
 
-template <typename Real>
+template <bool kNt, typename Real>
 __global__ __launch_bounds__(kBinThreads) void k_bin_hist(SysArgs<Real> a) {
-  bin_hist(a, blockIdx.x);
+  bin_hist<kNt>(a, blockIdx.x);
 }
 
-__global__ __launch_bounds__(kBinThreads) void k_bin_hist_batch(Batch<float> b) {
+template <bool kNt>
+__global__ __launch_bounds__(kBinThreads) void k_bin_hist_batch(Batch b) {
   int64_t blk;
-  const int s = b.pick(blockIdx.x, blk);
-  bin_hist(b.sys[s], blk);
+  const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
+  bin_hist<kNt>(a, blk);
 }
 
 template <typename Real>
@@ -389,10 +390,10 @@ __global__ __launch_bounds__(1024) void k_bin_colscan(SysArgs<Real> a) {
   bin_colscan(a, blockIdx.x);
 }
 
-__global__ __launch_bounds__(1024) void k_bin_colscan_batch(Batch<float> b) {
+__global__ __launch_bounds__(1024) void k_bin_colscan_batch(Batch b) {
   int64_t blk;
-  const int s = b.pick(blockIdx.x, blk);
-  bin_colscan(b.sys[s], blk);
+  const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
+  bin_colscan(a, blk);
 }
 
 // Whether cost[] holds the pair kernel's times of the last evaluation on this grid (a
@@ -559,10 +560,10 @@ __global__ __launch_bounds__(1024) void k_bin_scan(SysArgs<Real> a, TypeTable tt
   bin_scan(a, tt, own_header);
 }
 
-__global__ __launch_bounds__(1024) void k_bin_scan_batch(Batch<float> b, TypeTable tt) {
+__global__ __launch_bounds__(1024) void k_bin_scan_batch(Batch b, TypeTable tt) {
   int64_t blk;
-  const int s = b.pick(blockIdx.x, blk);
-  bin_scan(b.sys[s], tt, 1);
+  const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
+  bin_scan(a, tt, 1);
 }
 
 // Each atom goes to its cell's range (in arbitrary order) with its sort key, its wrapped
@@ -594,10 +595,10 @@ __global__ __launch_bounds__(256) void k_scatter(SysArgs<Real> a) {
   scatter(a, xcd_contiguous(blockIdx.x, gridDim.x));
 }
 
-__global__ __launch_bounds__(256) void k_scatter_batch(Batch<float> b) {
+__global__ __launch_bounds__(256) void k_scatter_batch(Batch b) {
   int64_t blk;
-  const int s = b.pick(blockIdx.x, blk);
-  scatter(b.sys[s], blk);
+  const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
+  scatter(a, blk);
 }
 
 // One workgroup per cell. Each member's position in the cell is the number of members
@@ -677,7 +678,7 @@ __device__ inline SortLds& sort_lds() {
   return l;
 }
 
-// kNt: the outputs with streaming stores (grids of at most kScanFused cells).
+// kNt: the outputs with streaming stores (grids of at most kScanFused cells: streaming).
 template <bool kNt, typename Real>
 __device__ inline void cell_sort(const SysArgs<Real>& a, int64_t c) {
   constexpr int kChunk = kSortChunk;
@@ -1008,14 +1009,14 @@ __device__ inline void bin_tail(const SysArgs<Real>& a, const TypeTable& tt) {
 
 // Block blk of k_cell_sort: with the fused scan, block 0 ends the binning and block c + 1
 // sorts cell c; otherwise block c sorts cell c.
-template <typename Real>
+template <bool kNt, typename Real>
 __device__ inline void cell_sort_or_tail(const SysArgs<Real>& a, const TypeTable& tt, int64_t blk) {
   if (!scan_fused(a)) {
     cell_sort<false>(a, blk);
   } else if (blk == 0) {
     bin_tail(a, tt);
   } else {
-    cell_sort<true>(a, blk - 1);
+    cell_sort<kNt>(a, blk - 1);
   }
 }
 
@@ -1024,15 +1025,16 @@ __host__ __device__ inline int64_t sort_blocks(const SysArgs<Real>& a) {
   return a.n_cells + (scan_fused(a) ? 1 : 0);
 }
 
-template <typename Real>
+template <bool kNt, typename Real>
 __global__ __launch_bounds__(kSortThreads) void k_cell_sort(SysArgs<Real> a, TypeTable tt) {
-  cell_sort_or_tail(a, tt, blockIdx.x);
+  cell_sort_or_tail<kNt>(a, tt, blockIdx.x);
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_cell_sort_batch(Batch<float> b, TypeTable tt) {
+template <bool kNt>
+__global__ __launch_bounds__(kSortThreads) void k_cell_sort_batch(Batch b, TypeTable tt) {
   int64_t blk;
-  const int s = b.pick(blockIdx.x, blk);
-  cell_sort_or_tail(b.sys[s], tt, blk);
+  const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
+  cell_sort_or_tail<kNt>(a, tt, blk);
 }
 
 }  // namespace
@@ -1046,13 +1048,25 @@ TypeTable make_type_table(const md_params* p) {
   return tt;
 }
 
+// Whether a launch over n atoms in all (grids of at most kScanFused cells) writes its outputs
+// with streaming stores. They take them past L2 in pieces of a line, which is faster while the
+// memory keeps up: float32, whole calls, ordinary against streaming: 73k atoms 174.8 and
+// 173.5 us, 92k 165.8 and 164.6, 126k 241.5 and 241.5, 173k 323.9 and 325.8; a batch of 16
+// requests (685k atoms) 1074 and 1126 us (its histogram kernel 14.5 and 46.7). Float64
+// records are twice as long: 92k atoms 959 and 979 us.
+template <typename Real>
+static bool streaming(int64_t n) {
+  return n * (int64_t)(sizeof(Real) / 4) <= 131072;
+}
+
 template <typename Real>
 hipError_t launch_binning(const SysArgs<Real>& a, const TypeTable& tt, hipStream_t stream) {
   int own_header = 1;
+  const bool nt = streaming<Real>(a.n);
   if (a.n > 0 && a.bin_blocks > 0) {
     const size_t shmem = sizeof(int32_t) * (size_t)(a.n_cells + 1);
-    hipLaunchKernelGGL(k_bin_hist<Real>, dim3((unsigned)a.bin_blocks), dim3(kBinThreads), shmem, stream,
-                       a);
+    hipLaunchKernelGGL((nt ? k_bin_hist<true, Real> : k_bin_hist<false, Real>),
+                       dim3((unsigned)a.bin_blocks), dim3(kBinThreads), shmem, stream, a);
   } else if (a.n > 0) {
     int64_t work = a.n_cells > a.n ? a.n_cells : a.n;
     int64_t blocks = (work + 255) / 256;
@@ -1079,41 +1093,38 @@ hipError_t launch_binning(const SysArgs<Real>& a, const TypeTable& tt, hipStream
     hipLaunchKernelGGL(k_scatter<Real>, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, stream,
                        a);
   }
-  hipLaunchKernelGGL(k_cell_sort<Real>, dim3((unsigned)sort_blocks(a)), dim3(kSortThreads), 0,
-                     stream, a, tt);
+  hipLaunchKernelGGL((nt ? k_cell_sort<true, Real> : k_cell_sort<false, Real>),
+                     dim3((unsigned)sort_blocks(a)), dim3(kSortThreads), 0, stream, a, tt);
   return hipGetLastError();
 }
 
-// Sets cum[] of a batch from per-system block counts.
-template <typename F>
-static int64_t batch_blocks(Batch<float>& b, F per_sys) {
-  b.cum[0] = 0;
-  for (int s = 0; s < b.n; ++s) b.cum[s + 1] = b.cum[s] + per_sys(b.sys[s]);
-  return b.cum[b.n];
-}
-
-hipError_t launch_binning_batch(const Batch<float>& b0, const TypeTable& tt, hipStream_t stream) {
-  Batch<float> b = b0;
+hipError_t launch_binning_batch(Batch& b, const SysArgs<float>* sys, const TypeTable& tt,
+                                hipStream_t stream) {
   size_t shmem = 0;
+  int64_t n = 0;
+  for (int s = 0; s < b.n; ++s) n += sys[s].n;
+  const bool nt = streaming<float>(n);
   for (int s = 0; s < b.n; ++s) {
-    const size_t need = sizeof(int32_t) * (size_t)(b.sys[s].n_cells + 1);
+    const size_t need = sizeof(int32_t) * (size_t)(sys[s].n_cells + 1);
     shmem = need > shmem ? need : shmem;
   }
-  int64_t nb = batch_blocks(b, [](const SysArgs<float>& a) { return (int64_t)a.bin_blocks; });
-  hipLaunchKernelGGL(k_bin_hist_batch, dim3((unsigned)nb), dim3(kBinThreads), shmem, stream, b);
+  int64_t nb = batch_blocks(b, sys, [](const SysArgs<float>& a) { return (int64_t)a.bin_blocks; });
+  hipLaunchKernelGGL((nt ? k_bin_hist_batch<true> : k_bin_hist_batch<false>), dim3((unsigned)nb),
+                     dim3(kBinThreads), shmem, stream, b);
   // grids of more than kScanFused cells (the others need no scan kernels)
-  nb = batch_blocks(b, [](const SysArgs<float>& a) { return colscan_blocks(a); });
+  nb = batch_blocks(b, sys, [](const SysArgs<float>& a) { return colscan_blocks(a); });
   if (nb > 0) hipLaunchKernelGGL(k_bin_colscan_batch, dim3((unsigned)nb), dim3(1024), 0, stream, b);
-  nb = batch_blocks(b, [](const SysArgs<float>& a) { return scan_fused(a) ? (int64_t)0 : (int64_t)1; });
+  nb = batch_blocks(b, sys, [](const SysArgs<float>& a) { return (int64_t)(scan_fused(a) ? 0 : 1); });
   if (nb > 0) {
     hipLaunchKernelGGL(k_bin_scan_batch, dim3((unsigned)nb), dim3(1024), 0, stream, b, tt);
-    nb = batch_blocks(b, [](const SysArgs<float>& a) {
+    nb = batch_blocks(b, sys, [](const SysArgs<float>& a) {
       return scan_fused(a) ? (int64_t)0 : (a.n + 255) / 256;
     });
     hipLaunchKernelGGL(k_scatter_batch, dim3((unsigned)nb), dim3(256), 0, stream, b);
   }
-  nb = batch_blocks(b, [](const SysArgs<float>& a) { return sort_blocks(a); });
-  hipLaunchKernelGGL(k_cell_sort_batch, dim3((unsigned)nb), dim3(kSortThreads), 0, stream, b, tt);
+  nb = batch_blocks(b, sys, [](const SysArgs<float>& a) { return sort_blocks(a); });
+  hipLaunchKernelGGL((nt ? k_cell_sort_batch<true> : k_cell_sort_batch<false>), dim3((unsigned)nb),
+                     dim3(kSortThreads), 0, stream, b, tt);
   return hipGetLastError();
 }
 

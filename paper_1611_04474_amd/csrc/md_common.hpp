@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "mdforce.h"
 
 namespace md {
@@ -92,12 +94,13 @@ struct Plan {
   int64_t n;
   int real_bytes;               // 4 or 8
   // byte offsets
-  size_t off_count, off_start, off_cell, off_rank, off_pos, off_hpre, off_type, off_perm,
+  size_t off_args, off_count, off_start, off_cell, off_rank, off_pos, off_hpre, off_type, off_perm,
       off_part, off_facc, off_epart, off_lj, off_paircount, off_bhist, off_bstat, off_order,
       off_cost,
       off_zsplit, off_ukey, off_upos, off_kpart, total;
-  size_t small_grid_parts;      // bytes by which the energy partials of a grid of at most
-                                // kFsMaxCells cells exceed one word per task
+  size_t uncounted;             // bytes that the no-allocation call's limit does not count:
+                                // the batch arguments, and the energy partials of a grid of
+                                // at most kFsMaxCells cells beyond one word per task
   int bin_blocks;               // blocks of the LDS-histogram binning pass (0: global atomics)
   int64_t bin_chunk;            // atoms per such block
 };
@@ -171,26 +174,59 @@ struct SysArgs {
                                // chip: then one workgroup takes the slices in turn)
 };
 
-// Up to kBatchMax systems evaluated by one launch of each kernel of the path. The
-// systems' arguments travel in the kernel argument block; block b of a batched launch
-// belongs to system s with cum[s] <= b < cum[s+1], as its local block b - cum[s].
-constexpr int kBatchMax = 10;   // keeps every batched kernel's arguments under 4 KB
+// Up to kBatchMax systems evaluated by one launch of each kernel of the path. Their
+// arguments (about 350 bytes each) stand in device memory, in each system's workspace, put
+// there by k_put_args; the kernels get the systems' block ranges and the arguments'
+// addresses. Block b of a batched launch belongs to the system s with cum[s] <= b < cum[s+1],
+// as its local block b - cum[s]. Handed over by value instead, ten systems fill the 4 KB of
+// kernel arguments, and a larger batch takes another launch of each kernel: 16 requests of 2k-200k
+// atoms 1148 us that way, 1130 this way.
+constexpr int kBatchMax = 128;
+constexpr int kPutMax = 10;     // systems per k_put_args launch (kernel arguments under 4 KB)
 
-template <typename Real>
 struct Batch {
   int n;
   int64_t cum[kBatchMax + 1];
-  SysArgs<Real> sys[kBatchMax];
-
-  __device__ inline int pick(int64_t b, int64_t& local) const {
-    int s = 0;
-    while (s + 1 < n && cum[s + 1] <= b) ++s;
-    local = b - cum[s];
-    return s;
-  }
+  const SysArgs<float>* sys[kBatchMax];
 };
 
-static_assert(sizeof(Batch<float>) <= 4096 - 64, "kernel arguments");
+struct PutArgs {
+  int n;
+  SysArgs<float>* dst[kPutMax];
+  SysArgs<float> sys[kPutMax];
+};
+static_assert(sizeof(Batch) + sizeof(double) * 2 * kMaxTypes <= 4096 - 64, "kernel arguments");
+static_assert(sizeof(PutArgs) <= 4096 - 64, "kernel arguments");
+
+// The system of block b and its local block: lane l compares the ends of systems l and
+// l + 64 with b, so that the table is read in one round trip.
+__device__ inline const SysArgs<float>* batch_pick(const Batch& t, int64_t b, int64_t& local) {
+  static_assert(kBatchMax == 128, "two table entries per lane");
+  const int lane = threadIdx.x & 63;
+  const int64_t e0 = t.cum[lane + 1], e1 = t.cum[lane + 65];   // past n: at least cum[n]
+  const int s = __builtin_popcountll(__builtin_amdgcn_ballot_w64(e0 <= b)) +
+                __builtin_popcountll(__builtin_amdgcn_ballot_w64(e1 <= b));
+  local = b - t.cum[s];
+  return t.sys[s];
+}
+
+// A system's arguments, read through the scalar cache; its pointers are to global memory.
+__device__ inline SysArgs<float> batch_args(const SysArgs<float>* p) {
+  typedef const __attribute__((address_space(4))) SysArgs<float>* cptr;
+  SysArgs<float> a;
+  __builtin_memcpy(&a, (cptr)(uintptr_t)p, sizeof(a));
+  auto global = [](auto& q) {
+    typedef std::remove_reference_t<decltype(*q)> T;
+    q = (T*)(__attribute__((address_space(1))) T*)q;
+  };
+  global(a.pos_in); global(a.type_in); global(a.q_in); global(a.force_out); global(a.energy_out);
+  global(a.hdr); global(a.count); global(a.start); global(a.cell); global(a.rank);
+  global(a.ukey); global(a.upos); global(a.pos); global(a.hpre); global(a.type); global(a.perm);
+  global(a.part); global(a.facc); global(a.epart); global(a.lj); global(a.paircount);
+  global(a.acc64); global(a.bhist); global(a.bstat); global(a.order); global(a.cost);
+  global(a.zsplit);
+  return a;
+}
 
 // Per-type sigma and epsilon, mixed into the LJ table by the binning stage.
 struct TypeTable {
@@ -214,12 +250,22 @@ hipError_t launch_finalize(const SysArgs<Real>& a, hipStream_t stream);
 template <typename Real>
 hipError_t launch_pair_fs(const SysArgs<Real>& a, hipStream_t stream);
 
-// Batched float32 launchers. Every system of the batch has n > 0, uses the LDS-histogram
-// binning (bin_blocks > 0), the compacted kernel, and the same flags and
-// type table.
-hipError_t launch_binning_batch(const Batch<float>& b, const TypeTable& tt, hipStream_t stream);
-hipError_t launch_pair_fs_batch(const Batch<float>& b, hipStream_t stream);
-hipError_t launch_finalize_batch(const Batch<float>& b, hipStream_t stream);
+// Batched float32 launchers over n systems' arguments (host copies; b.sys holds the addresses
+// of the device copies). Every system of the batch has n > 0, uses the LDS-histogram binning
+// (bin_blocks > 0), the compacted kernel, and the same flags and type table.
+hipError_t launch_binning_batch(Batch& b, const SysArgs<float>* sys, const TypeTable& tt,
+                                hipStream_t stream);
+hipError_t launch_pair_fs_batch(Batch& b, const SysArgs<float>* sys, hipStream_t stream);
+hipError_t launch_finalize_batch(Batch& b, const SysArgs<float>* sys, hipStream_t stream);
+
+// Sets cum[] of a batch from per-system block counts (entries past the last system repeat
+// the total); returns the total.
+template <typename F>
+inline int64_t batch_blocks(Batch& b, const SysArgs<float>* sys, F per_sys) {
+  b.cum[0] = 0;
+  for (int s = 0; s < kBatchMax; ++s) b.cum[s + 1] = b.cum[s] + (s < b.n ? per_sys(sys[s]) : 0);
+  return b.cum[b.n];
+}
 
 // Velocity-Verlet kernels of md_run_vv_f32 (md_integrate.hip). kick_drift: v += h F/m,
 // x += dt v wrapped into [0, L). kick: v += h F/m, and the kinetic energy, from per-block

@@ -170,10 +170,10 @@ __global__ __launch_bounds__(256) void k_finalize_energy(SysArgs<Real> a) {
   finalize_or_energy(a, blockIdx.x);
 }
 
-__global__ __launch_bounds__(256) void k_finalize_energy_batch(Batch<float> b) {
+__global__ __launch_bounds__(256) void k_finalize_energy_batch(Batch b) {
   int64_t blk;
-  const int s = b.pick(blockIdx.x, blk);
-  finalize_or_energy(b.sys[s], blk);
+  const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
+  finalize_or_energy(a, blk);
 }
 
 }  // namespace
@@ -185,11 +185,9 @@ hipError_t launch_finalize(const SysArgs<Real>& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_finalize_batch(const Batch<float>& b0, hipStream_t stream) {
-  Batch<float> b = b0;
-  b.cum[0] = 0;
-  for (int s = 0; s < b.n; ++s) b.cum[s + 1] = b.cum[s] + (b.sys[s].n + 255) / 256 + 1;
-  hipLaunchKernelGGL(k_finalize_energy_batch, dim3((unsigned)b.cum[b.n]), dim3(256), 0, stream, b);
+hipError_t launch_finalize_batch(Batch& b, const SysArgs<float>* sys, hipStream_t stream) {
+  const int64_t nb = batch_blocks(b, sys, [](const SysArgs<float>& a) { return (a.n + 255) / 256 + 1; });
+  hipLaunchKernelGGL(k_finalize_energy_batch, dim3((unsigned)nb), dim3(256), 0, stream, b);
   return hipGetLastError();
 }
 

@@ -1186,15 +1186,15 @@ void k_pair_fs(SysArgs<Real> a, int cap) {
 // One launch for a batch: block b is cell order[b - cum[s]] of system s.
 template <bool kHalf, int kCoul, bool kClamp, bool kDiag, int kDrain>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNW / 4, kNW / 4)))
-void k_pair_fs_batch(Batch<float> b, int cap) {
+void k_pair_fs_batch(Batch b, int cap) {
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   const uint64_t c0 = __builtin_amdgcn_s_memtime();
   int64_t blk;
-  const int s = b.pick(blockIdx.x, blk);
-  const int64_t cell = b.sys[s].order[blk % b.sys[s].n_cells];
-  const int unit = (int)(blk / b.sys[s].n_cells);
-  const bool last = pair_fs<float, kHalf, kCoul, kClamp, kDiag, kDrain>(b.sys[s], cap, cell, unit);
-  if (last && (threadIdx.x & 63) == 0) record_cost(b.sys[s], cell, unit, t0, c0, blk == 0);
+  const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
+  const int64_t cell = a.order[blk % a.n_cells];
+  const int unit = (int)(blk / a.n_cells);
+  const bool last = pair_fs<float, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, cell, unit);
+  if (last && (threadIdx.x & 63) == 0) record_cost(a, cell, unit, t0, c0, blk == 0);
 }
 
 template <bool H, int S, bool C, bool D, int R>
@@ -1275,16 +1275,14 @@ hipError_t launch_pair_fs(const SysArgs<Real>& a, hipStream_t stream) {
 template hipError_t launch_pair_fs<float>(const SysArgs<float>&, hipStream_t);
 template hipError_t launch_pair_fs<double>(const SysArgs<double>&, hipStream_t);
 
-hipError_t launch_pair_fs_batch(const Batch<float>& b0, hipStream_t stream) {
-  Batch<float> b = b0;
+hipError_t launch_pair_fs_batch(Batch& b, const SysArgs<float>* sys, hipStream_t stream) {
   int nt = 1;
-  b.cum[0] = 0;
-  for (int s = 0; s < b.n; ++s) {
-    b.cum[s + 1] = b.cum[s] + b.sys[s].n_cells * b.sys[s].fs_split * b.sys[s].fs_su;
-    nt = b.sys[s].n_types > nt ? b.sys[s].n_types : nt;
-  }
-  return dispatch(b.sys[0], b, nt, b.cum[b.n], stream,
-                  [](auto tag, dim3 g, dim3 bl, size_t sh, hipStream_t st, const Batch<float>& x,
+  for (int s = 0; s < b.n; ++s) nt = sys[s].n_types > nt ? sys[s].n_types : nt;
+  const int64_t nb = batch_blocks(b, sys, [](const SysArgs<float>& a) {
+    return a.n_cells * a.fs_split * a.fs_su;
+  });
+  return dispatch(sys[0], b, nt, nb, stream,
+                  [](auto tag, dim3 g, dim3 bl, size_t sh, hipStream_t st, const Batch& x,
                      int cap) {
                     using Tg = decltype(tag);
                     hipLaunchKernelGGL(

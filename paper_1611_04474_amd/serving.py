@@ -10,7 +10,7 @@ memory until its result is back on the host, and:
     is admitted, so copies overlap the batches already running (on an idle GPU they go on
     the compute stream in front of the batch instead);
   * launches every admitted, not yet launched request as one batched call
-    (md_forces_batched: one launch per kernel of the path for up to 10 systems of one
+    (md_forces_batched: one launch per kernel of the path for up to 128 systems of one
     kind) whenever fewer than `max_inflight` batches are on the GPU, so requests that
     arrive while others run join the next batch instead of waiting for the queue to
     drain;

@@ -63,3 +63,33 @@ def test_crowded_sort_order(gpu, n):
     pos[:, 0] = np.clip(pos[:, 0], 0, 59.5)
     f, e, ws, _ = run(p, pos, s.types, s.charges, gpu)
     _check_binning(p, pos, ws, n)
+
+
+@pytest.mark.parametrize("sizes", [
+    [2000, 2500],                          # few cells in all: the systems keep their splits
+    [2001, 90000, 3000, 40000, 1700],      # mixed: small systems' cells whole, costliest first
+    [1600 + 37 * k for k in range(130)],   # more systems than one launch takes
+])
+def test_batch_units_same_bits(gpu, sizes):
+    """A batch shares its systems out over fewer workgroups than they would take alone; every
+    system's forces and energy are the bits of its own call."""
+    import torch
+    print("case: batch of", len(sizes), "sizes", sizes[:5], flush=True)
+    systems, alone = [], []
+    table = W.draw_type_table(np.random.default_rng(2))
+    for k, n in enumerate(sizes):
+        L = W.cube_for(n)
+        s = W.gen_system(n, (max(L, 24.5),) * 3, 100 + k, type_table=table)
+        p = api.Params.from_dict(s.params())
+        d = dict(params=p, pos=torch.as_tensor(s.pos).to(gpu), types=torch.as_tensor(s.types).to(gpu),
+                 charges=torch.as_tensor(s.charges).to(gpu),
+                 force=torch.empty(n, 3, device=gpu),
+                 energy=torch.empty(1, dtype=torch.float64, device=gpu),
+                 workspace=api.alloc_workspace(p, n, gpu))
+        alone.append([t.clone() for t in api.forces(p, d["pos"], d["types"], d["charges"])])
+        systems.append(d)
+    for _ in range(2):
+        api.forces_batched(systems)
+        torch.cuda.synchronize()
+        for d, (f, e) in zip(systems, alone):
+            assert torch.equal(d["force"], f) and torch.equal(d["energy"], e)
