@@ -11,6 +11,9 @@
 // two give equal terms), plus the self term -k alpha/sqrt(pi) sum q^2 and the neutralising
 // background -k pi Q^2 / (2 V alpha^2).
 //
+// This file holds the entry points and the direct sum, which smaller systems take; larger ones
+// take the same sum through a grid (md_ewald_mesh.hip).
+//
 // Phases are exact modulo one turn: each atom's fractional coordinate is held as a 32-bit
 // fixed-point fraction u, so m u (mod 2^32) is the phase of wave number m with no rounding,
 // and only the final sine and cosine round. Wave vectors are grouped in rows (mx, my), each
@@ -28,7 +31,7 @@
 // Every sum runs in a fixed order, so the results are the same bits on every run.
 #include <math.h>
 
-#include "md_common.hpp"
+#include "md_ewald.hpp"
 
 namespace md {
 namespace {
@@ -87,21 +90,9 @@ __global__ __launch_bounds__(256) void k_ew_setup(EwArgs a) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   double q2 = 0.0, q1 = 0.0;
   if (i < a.n) {
-    uint32_t st = 0, u[3];
-    for (int d = 0; d < 3; ++d) {
-      const double x = (double)a.pos[3 * i + d];
-      if (x != x) {
-        st |= MD_STATUS_NAN;
-        u[d] = 0;
-        continue;
-      }
-      const double s = x / a.L[d];
-      const double f = s - floor(s);                               // [0, 1)
-      u[d] = (uint32_t)(unsigned long long)llrint(f * 4294967296.0);   // 2^32 wraps to 0
-    }
-    const float qi = a.q[i];
-    if (qi != qi) st |= MD_STATUS_NAN;
-    a.ups[i] = make_uint4(u[0], u[1], u[2], __float_as_uint(qi));
+    uint32_t st = 0;
+    a.ups[i] = ew_fractions(a.pos, a.q, a.L, i, st);
+    const float qi = __uint_as_float(a.ups[i].w);
     q2 = (double)qi * (double)qi;
     q1 = (double)qi;
     if (st) atomicOr(&a.hdr->status, st);
@@ -374,33 +365,7 @@ __global__ __launch_bounds__(256) void k_ew_force(EwArgs a) {
 
 // Energy: row partials, then self and background terms, in a fixed order.
 __global__ __launch_bounds__(256) void k_ew_energy(EwArgs a) {
-  __shared__ double s[256], s2[256], s1[256];
-  double e = 0.0, q2 = 0.0, q1 = 0.0;
-  const int64_t ne = a.rows * a.zblocks;
-  for (int64_t t = threadIdx.x; t < ne; t += 256) e += a.erow[t];
-  for (int64_t t = threadIdx.x; t < a.qblocks; t += 256) {
-    q2 += a.qpart[t].x;
-    q1 += a.qpart[t].y;
-  }
-  s[threadIdx.x] = e;
-  s2[threadIdx.x] = q2;
-  s1[threadIdx.x] = q1;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      s[threadIdx.x] += s[threadIdx.x + off];
-      s2[threadIdx.x] += s2[threadIdx.x + off];
-      s1[threadIdx.x] += s1[threadIdx.x + off];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double pi = 3.141592653589793;
-    const double V = a.L[0] * a.L[1] * a.L[2];
-    const double self = -a.coulomb_k * a.alpha / sqrt(pi) * s2[0];
-    const double bg = -a.coulomb_k * pi * s1[0] * s1[0] / (2.0 * V * a.alpha * a.alpha);
-    *a.energy = s[0] + self + bg;
-  }
+  ew_energy_sum(a.erow, a.rows * a.zblocks, a.qpart, a.qblocks, a.L, a.alpha, a.coulomb_k, a.energy);
 }
 
 __global__ void k_ew_clear_status(WsHeader* hdr) { hdr->status = 0; }
@@ -451,13 +416,16 @@ md_status ew_plan(const md_params* p, int64_t n, const int32_t kmax[3], EwPlan* 
 }
 
 }  // namespace
+
 }  // namespace md
 
 extern "C" {
 
 size_t md_ewald_workspace_bytes(const md_params* p, int64_t n_atoms, const int32_t kmax[3]) {
   md::EwPlan pl;
-  return md::ew_plan(p, n_atoms, kmax, &pl) == MD_OK ? pl.total : 0;
+  if (md::ew_plan(p, n_atoms, kmax, &pl) != MD_OK) return 0;
+  md::EwMeshPlan mesh;
+  return md::ew_mesh_plan(p, n_atoms, kmax, pl.total, &mesh) ? mesh.total : pl.total;
 }
 
 md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d_pos,
@@ -471,7 +439,15 @@ md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d
   if (n_atoms > 0 && (!d_pos || !d_charge || !d_force ||
                       (((uintptr_t)d_pos | (uintptr_t)d_charge | (uintptr_t)d_force) & 3)))
     return MD_ERR_INVALID_ARG;
-  if (!d_ws || ((uintptr_t)d_ws & 255) || ws_bytes < pl.total) return MD_ERR_WORKSPACE;
+  md::EwMeshPlan mesh;
+  const bool grid = md::ew_mesh_plan(p, n_atoms, kmax, pl.total, &mesh);
+  if (!d_ws || ((uintptr_t)d_ws & 255) || ws_bytes < (grid ? mesh.total : pl.total))
+    return MD_ERR_WORKSPACE;
+  if (grid)
+    return md::launch_ew_mesh(mesh, p, n_atoms, d_pos, d_charge, d_force, d_energy, accumulate ? 1 : 0,
+                              d_ws, (hipStream_t)stream) == hipSuccess
+               ? MD_OK
+               : MD_ERR_HIP;
   md::EwArgs a;
   char* b = (char*)d_ws;
   a.n = n_atoms;

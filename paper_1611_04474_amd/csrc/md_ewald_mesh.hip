@@ -1,0 +1,826 @@
+// Ewald reciprocal-space sum of larger systems: the same sum over wave vectors as
+// md_ewald.hip, through a non-uniform Fourier transform, O(N + grid) instead of O(N K).
+//
+// The charges are spread to a regular grid with a window wide enough that the gridding error
+// (3e-8 of the forces at an oversampling of 1.75, from a float64 comparison with the direct
+// sum) lies below float32 rounding, so this is not a particle-mesh approximation with an
+// accuracy to choose: results agree with the direct sum to its own rounding (see the
+// accuracy at launch_ew_mesh). With real separable basis functions t_n(l), n = 2 m + a:
+// cos (a = 0) or sin (a = 1) of 2 pi m l / M, the pieces are
+//   b[l]    = sum_j q_j phi(l_x - X_j) phi(l_y - Y_j) phi(l_z - Z_j),   X = M_x u_x, ...
+//   R[n]    = sum_l b[l] t_nx(l_x) t_ny(l_y) t_nz(l_z)
+//   Q[n]    = (4 pi k / V) mu(m) exp(-|kv|^2/(4 alpha^2)) / |kv|^2 / phihat(m)^2  R[n]
+//   E       = 1/2 sum_n Q[n] R[n]
+//   c[l]    = sum_n Q[n] t_nx t_ny t_nz
+//   F_j     = q_j sum_l c[l] (M_x/L_x phi'(l_x - X_j) phi phi, ...)
+// with mu the number of distinct sign choices of the mode m >= 0 (the characters of the sign
+// flips are orthogonal, so the sum over +-m of |S|^2 is mu times the sum of the squares of
+// R over the eight cos/sin choices, and the potential has the coefficients mu R), and phihat
+// the window's transform. The window is phi(t) = exp(beta (sqrt(1 - (2t/w)^2) - 1)) on
+// |t| < w/2, w = 10 grid points (Barnett, Magland and af Klinteberg, SIAM J. Sci. Comput. 41
+// (2019) C479), with beta from the axis's oversampling.
+//
+// Grids have a few million points at most and only the modes |m| <= kmax are wanted, so the
+// transforms are products with a table of sines and cosines per axis on the matrix cores
+// (float32 MFMA), any grid size, a few GFLOP; a fast Fourier transform would save operations
+// that are not the bound. Kernels:
+//   k_em_init     tables, window transforms, counters
+//   k_em_setup    per atom: fractions, NaN check, partial sums of q^2 and q; bin count
+//   k_em_scan     bin starts;   k_em_scatter  atom indices to bins
+//   k_em_sort     each bin in index order (so sums run in a fixed order)
+//   k_em_spread   b, one workgroup per tile of 8 x 8 x 16 grid points
+//   k_em_right / k_em_left   the six axis transforms (Q and E after the last forward one)
+//   k_em_force    forces, one workgroup per tile
+//   k_em_energy   fixed-order sum of the energy partials, self and background
+// Every sum runs in a fixed order: the results are the same bits on every run.
+#include <math.h>
+
+#include "md_ewald.hpp"
+
+namespace md {
+namespace {
+
+constexpr int kW = 10;                  // window width in grid points
+constexpr int kTX = 8, kTZ = 16;        // tile: 8 x 8 x 16 grid points
+constexpr int kLo = kW / 2 - 1;         // an atom at grid cell l covers l - 4 .. l + 5
+constexpr int kHi = kW / 2;
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// The window phi(t) = exp(beta (sqrt(1 - x^2) - 1)), x = 2 t / w, and its derivative, for
+// t = r - f with r a whole number of grid points and f a 32-bit fraction (both exact); c =
+// beta log2(e). The exponent is formed in float64 (its root from a float32 one and a Newton
+// step; float64 FMAs issue at float32's rate here), so that phi carries little more than the
+// rounding of the hardware's 2^x: in float32 throughout the exponent's rounding alone put
+// 3e-7 into the forces.
+__device__ inline float window(int r, uint32_t f, double c, float& d) {
+  const double t = fma((double)f, -2.3283064365386963e-10, (double)r);   // 2^-32
+  const double x = t * (2.0 / kW);
+  const double y = fma(-x, x, 1.0);
+  const float yf = fmaxf((float)y, 1e-7f);
+  const float rs = __builtin_amdgcn_rsqf(yf);
+  const double s0 = (double)(yf * rs);
+  const double s = fma(fma(-s0, s0, y), (double)(0.5f * rs), s0);
+  const double g = c * (s - 1.0);
+  const float hi = (float)g, lo = (float)(g - (double)hi);
+  const float e = __builtin_amdgcn_exp2f(hi);
+  const float v = y > 1e-7 ? fmaf(e, lo * 0.6931472f, e) : 0.f;
+  d = v * ((float)(-x * (c * (0.6931471805599453 * 2.0 / kW))) * rs);
+  return v;
+}
+
+// Grid cell of a 32-bit fraction u on an axis of M points; f: the offset within it as a 32-bit
+// fraction.
+__device__ inline int grid_cell(uint32_t u, int M, uint32_t& f) {
+  const uint64_t p = (uint64_t)u * (uint32_t)M;
+  f = (uint32_t)p;
+  return (int)(p >> 32);
+}
+
+__device__ inline int bin_of(const EwMeshArgs& a, uint4 u) {
+  uint32_t f;
+  const int x = grid_cell(u.x, a.M[0], f) / kTX, y = grid_cell(u.y, a.M[1], f) / kTX,
+            z = grid_cell(u.z, a.M[2], f) / kTZ;
+  return (x * a.nt[1] + y) * a.nt[2] + z;
+}
+
+// Blocks 0 .. nb_tab - 1: the tables, an entry per thread; then one wave per (axis, mode):
+// the window's transform by the trapezoid rule (its integrand is smooth to e^-beta at the
+// ends, so 320 points leave no error in float64) and the mode's factors; the bin counters are
+// cleared by every block.
+__global__ __launch_bounds__(256) void k_em_init(EwMeshArgs a, unsigned nb_tab) {
+  const int64_t gt = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (int64_t i = gt; i < a.nbins; i += (int64_t)gridDim.x * 256) a.count[i] = 0;
+  if (gt == 0) a.hdr->status = 0;
+  if (blockIdx.x < nb_tab) {
+    int64_t e = gt;
+    for (int d = 0; d < 3; ++d) {
+      const int64_t sz = (int64_t)a.N[d] * a.M[d];
+      if (e < sz) {
+        const int n = (int)(e / a.M[d]), l = (int)(e % a.M[d]);
+        const int m = n >> 1;
+        double s = 0.0, c = 0.0;
+        if (m <= a.K[d]) sincospi(2.0 * (double)(((int64_t)m * l) % a.M[d]) / (double)a.M[d], &s, &c);
+        const float v = (float)((n & 1) ? s : c);
+        a.tab[d][e] = v;                                   // [n][l]
+        a.tabT[d][(int64_t)l * a.N[d] + n] = v;            // [l][n]
+        return;
+      }
+      e -= sz;
+    }
+    return;
+  }
+  const int wv = (int)(blockIdx.x - nb_tab) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  int m = wv, d = 0;
+  while (d < 3 && m >= a.N[d] / 2) {
+    m -= a.N[d] / 2;
+    ++d;
+  }
+  if (d >= 3) return;
+  double sum = 0.0;
+  const double xi = (double)m / (double)a.M[d];
+  for (int p = lane; p < 160; p += 64) {
+    const double t = ((double)p + 0.5) / 32.0;             // 0 .. 5, the even half
+    const double x = t * (2.0 / kW);
+    sum += exp2(a.cb[d] * (sqrt(1.0 - x * x) - 1.0)) * cospi(2.0 * xi * t);
+  }
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if (lane != 0) return;
+  const double ph = sum / 16.0;                            // 2 h sum, h = 1/32
+  const double k = 2.0 * M_PI * (double)m / a.L[d];
+  const double g = m <= a.K[d] ? (m > 0 ? 2.0 : 1.0) * exp(-k * k / (4.0 * a.alpha * a.alpha)) / (ph * ph)
+                               : 0.0;
+  a.gfac[d][2 * m] = a.gfac[d][2 * m + 1] = g;
+  a.ksq[d][2 * m] = a.ksq[d][2 * m + 1] = k * k;
+}
+
+__global__ __launch_bounds__(256) void k_em_setup(EwMeshArgs a) {
+  __shared__ double sq2[256], sq[256];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  double q2 = 0.0, q1 = 0.0;
+  if (i < a.n) {
+    uint32_t st = 0;
+    const uint4 u = ew_fractions(a.pos, a.q, a.L, i, st);
+    a.ups[i] = u;
+    const float qi = __uint_as_float(u.w);
+    q2 = (double)qi * (double)qi;
+    q1 = (double)qi;
+    if (st) atomicOr(&a.hdr->status, st);
+    const int b = bin_of(a, u);
+    a.slot[i] = make_int2(b, atomicAdd(&a.count[b], 1));
+  }
+  sq2[threadIdx.x] = q2;
+  sq[threadIdx.x] = q1;
+  __syncthreads();
+  for (int off = 128; off > 0; off >>= 1) {
+    if ((int)threadIdx.x < off) {
+      sq2[threadIdx.x] += sq2[threadIdx.x + off];
+      sq[threadIdx.x] += sq[threadIdx.x + off];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) a.qpart[blockIdx.x] = make_double2(sq2[0], sq[0]);
+}
+
+// Exclusive scan of the bin counts, one workgroup, 4 bins per thread and round.
+__global__ __launch_bounds__(1024) void k_em_scan(EwMeshArgs a) {
+  __shared__ int s_w[16];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  int carry = 0;
+  for (int64_t b0 = 0; b0 < a.nbins; b0 += 4096) {
+    int v[4], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t b = b0 + 4 * t + k;
+      v[k] = b < a.nbins ? a.count[b] : 0;
+      sum += v[k];
+    }
+    int inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    if (lane == 63) s_w[w] = inc;
+    __syncthreads();
+    int before = carry, all = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      before += k < w ? s_w[k] : 0;
+      all += s_w[k];
+    }
+    __syncthreads();
+    int ex = before + inc - sum;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t b = b0 + 4 * t + k;
+      if (b < a.nbins) a.start[b] = ex;
+      ex += v[k];
+    }
+    carry += all;
+  }
+  if (t == 0) a.start[a.nbins] = carry;
+}
+
+__global__ __launch_bounds__(256) void k_em_scatter(EwMeshArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.n) return;
+  const int2 s = a.slot[i];
+  a.ids[a.start[s.x] + s.y] = (int)i;
+}
+
+// One wave per bin: its atoms in index order, so that the spreading adds in a fixed order.
+// Up to kRankMax members rank by counting smaller indices; a fuller bin marks them in a bit
+// map of kMapBits consecutive indices at a time and lists the marked ones. Then the atoms'
+// window values and derivatives, 10 per axis, half a wave per atom: the spreading, which meets
+// an atom in about 7 tiles, and the forces read them back.
+// LDS operations of a wave complete in order; the fence keeps the compiler to it as well.
+__device__ inline void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+__device__ inline void put_windows(const EwMeshArgs& a, int s, int m, const uint4* rec) {
+  const int lane = threadIdx.x & 63, c = lane & 31, d = min(c / kW, 2), k = c % kW;
+  const double cb = a.cb[d];
+  const int M = a.M[d];
+  for (int e = lane >> 5; e < m; e += 2) {
+    const uint4 u = rec[e];
+    uint32_t f;
+    grid_cell(d == 0 ? u.x : d == 1 ? u.y : u.z, M, f);
+    float dw;
+    const float w = window(k - kLo, f, cb, dw);
+    if (c < 3 * kW) {
+      a.win[(int64_t)(s + e) * 32 + c] = w;
+      a.dwin[(int64_t)(s + e) * 32 + c] = dw;
+    }
+  }
+}
+
+constexpr int kRankMax = 256, kMapBits = 32768;
+__global__ __launch_bounds__(256) void k_em_sort(EwMeshArgs a) {
+  __shared__ uint32_t s_map[4][kMapBits / 32];
+  __shared__ uint4 s_rec[4][kRankMax];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t b = (int64_t)blockIdx.x * 4 + w;
+  if (b >= a.nbins) return;
+  const int s = a.start[b], m = a.start[b + 1] - s;
+  uint32_t* map = s_map[w];
+  if (m <= kRankMax) {
+    int id[kRankMax / 64], r[kRankMax / 64];
+#pragma unroll
+    for (int k = 0; k < kRankMax / 64; ++k) {
+      const int e = lane + 64 * k;
+      id[k] = e < m ? a.ids[s + e] : 0x7fffffff;
+      r[k] = 0;
+      map[e] = (uint32_t)id[k];
+    }
+    wave_lds_fence();
+    for (int j = 0; j < m; ++j) {
+      const int x = (int)map[j];
+#pragma unroll
+      for (int k = 0; k < kRankMax / 64; ++k) r[k] += x < id[k] ? 1 : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kRankMax / 64; ++k) {
+      if (lane + 64 * k < m) {
+        const uint4 u = a.ups[id[k]];
+        a.rec[s + r[k]] = u;
+        s_rec[w][r[k]] = u;
+        a.sid[s + r[k]] = id[k];
+      }
+    }
+    wave_lds_fence();
+    put_windows(a, s, m, s_rec[w]);
+    return;
+  }
+  int out = s;
+  for (int64_t i0 = 0; i0 < a.n; i0 += kMapBits) {
+    wave_lds_fence();
+    for (int e = lane; e < kMapBits / 32; e += 64) map[e] = 0;
+    wave_lds_fence();
+    for (int e = lane; e < m; e += 64) {
+      const int64_t r = (int64_t)a.ids[s + e] - i0;
+      if (r >= 0 && r < kMapBits) atomicOr(&map[r >> 5], 1u << (r & 31));
+    }
+    wave_lds_fence();
+    for (int e0 = 0; e0 < kMapBits / 32; e0 += 64) {
+      uint32_t v = map[e0 + lane];
+      const int c = __builtin_popcount(v);
+      int inc = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(inc, o);
+        if (lane >= o) inc += y;
+      }
+      int p = out + inc - c;
+      while (v) {
+        const int i = (int)(i0 + 32 * (e0 + lane) + __builtin_ctz(v));
+        a.rec[p] = a.ups[i];
+        a.sid[p] = i;
+        ++p;
+        v &= v - 1;
+      }
+      out += __shfl(inc, 63);
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // the records are read back
+  put_windows(a, s, m, a.rec + s);
+}
+
+// The charges' grid, one workgroup of 4 waves per tile of 8 x 8 x 16 points: as a matrix
+// product over the atoms near the tile, b[(x, y)][z] = sum_j (q phi_x phi_y)[(x, y)][j]
+// phi_z[j][z], on the matrix cores, wave w taking x = 2 w and 2 w + 1. The atoms come from
+// the tile's own bin and the 26 around it (each axis has at least three); those whose window
+// meets the tile (one in four) are listed in bin order, up to kKeep at a time, and their
+// windows laid out over the tile's points kSub atoms at a time. In a 16x16x4 f32 product lane
+// l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and holds D[4 (l / 16) + i][l % 16].
+constexpr int kKeep = 1024, kSub = 64, kCand = 4;   // kCand candidates per thread and round
+__global__ __launch_bounds__(256) void k_em_spread(EwMeshArgs a) {
+  __shared__ int s_start[27], s_cum[28];
+  __shared__ int s_at[kKeep], s_rel[kKeep];   // sorted position; x, y, z + 8 relative to the tile
+  __shared__ float s_w[kSub][32 + 2];         // per atom: 8 x, 8 y and 16 z points of the tile
+  __shared__ int s_n[4][kCand];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int tz = blockIdx.x % a.nt[2], ty = (blockIdx.x / a.nt[2]) % a.nt[1],
+            tx = blockIdx.x / (a.nt[2] * a.nt[1]);
+  if (t < 64) {
+    int c = 0;
+    if (t < 27) {
+      int bx = tx + t / 9 - 1, by = ty + (t / 3) % 3 - 1, bz = tz + t % 3 - 1;
+      bx += bx < 0 ? a.nt[0] : bx >= a.nt[0] ? -a.nt[0] : 0;
+      by += by < 0 ? a.nt[1] : by >= a.nt[1] ? -a.nt[1] : 0;
+      bz += bz < 0 ? a.nt[2] : bz >= a.nt[2] ? -a.nt[2] : 0;
+      const int b = (bx * a.nt[1] + by) * a.nt[2] + bz;
+      s_start[t] = a.start[b];
+      c = a.start[b + 1] - s_start[t];
+    }
+    int inc = c;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+      const int y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    if (t < 28) s_cum[t] = inc - c;   // s_cum[27]: the total
+  }
+  __syncthreads();
+  const int total = s_cum[27];
+  v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+  const int row = lane & 15, kk = lane >> 4;
+  int n = 0;   // atoms listed
+  for (int e0 = 0; e0 < total; e0 += 256 * kCand) {
+    // wave w lists candidates e0 + 256 k + 64 w + lane: its bin by bisection, its position
+    // relative to the tile
+    int pos[kCand], rel[kCand];
+    unsigned long long keep[kCand];
+#pragma unroll
+    for (int k = 0; k < kCand; ++k) {
+      const int e = e0 + 256 * k + t;
+      int b = 0;
+#pragma unroll
+      for (int h = 16; h > 0; h >>= 1)
+        if (b + h < 27 && s_cum[b + h] <= e) b += h;
+      const bool in = e < total;
+      pos[k] = in ? s_start[b] + e - s_cum[b] : 0;
+      const uint4 u = a.rec[pos[k]];
+      uint32_t f;
+      const int rx = grid_cell(u.x, a.M[0], f) % kTX + kTX * (b / 9 - 1);
+      const int ry = grid_cell(u.y, a.M[1], f) % kTX + kTX * ((b / 3) % 3 - 1);
+      const int rz = grid_cell(u.z, a.M[2], f) % kTZ + kTZ * (b % 3 - 1);
+      rel[k] = (rx + 8) | (ry + 8) << 8 | (rz + 8) << 16;
+      keep[k] = __builtin_amdgcn_ballot_w64(in && rx >= -kHi && rx < kTX + kLo && ry >= -kHi &&
+                                            ry < kTX + kLo && rz >= -kHi && rz < kTZ + kLo);
+      if (lane == 0) s_n[w][k] = __builtin_popcountll(keep[k]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kCand; ++k) {
+      int at = n;
+      for (int v = 0; v < 4; ++v) {
+        at += v < w ? s_n[v][k] : 0;
+        n += s_n[v][k];
+      }
+      if (keep[k] >> lane & 1) {
+        at += __builtin_amdgcn_mbcnt_hi((unsigned)(keep[k] >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((unsigned)keep[k], 0u));
+        s_at[at] = pos[k];
+        s_rel[at] = rel[k];
+      }
+    }
+    __syncthreads();
+    // the next round may list up to 256 kCand more
+    if (n + 256 * kCand <= kKeep && e0 + 256 * kCand < total) continue;
+    // window values at the tile's points, 32 per atom (past the last atom zeros), those of the
+    // next kSub atoms on their way while the matrix cores take the last ones
+    constexpr int kVals = 32 * kSub / 256;
+    float val[kVals];
+    auto fetch = [&](int j0) {
+      const int c = t & 31;
+      const int off = c < 8 ? 0 : c < 16 ? kW : 2 * kW, sh = c < 8 ? 0 : c < 16 ? 8 : 16;
+      const int x = (c < 8 ? c : c < 16 ? c - 8 : c - 16) + kLo + 8;
+#pragma unroll
+      for (int k = 0; k < kVals; ++k) {
+        const int j = j0 + 8 * k + (t >> 5);
+        val[k] = 0.f;
+        if (j < n) {
+          const int p = s_at[j], i = x - ((s_rel[j] >> sh) & 255);   // the window's point
+          if (i >= 0 && i < kW) {
+            val[k] = a.win[(int64_t)p * 32 + off + i];
+            if (c < 8) val[k] *= __uint_as_float(a.rec[p].w);
+          }
+        }
+      }
+    };
+    if (n > 0) fetch(0);
+    for (int j0 = 0; j0 < n; j0 += kSub) {
+      const int n8 = (min(kSub, n - j0) + 7) & ~7;
+#pragma unroll
+      for (int k = 0; k < kVals; ++k) s_w[8 * k + (t >> 5)][t & 31] = val[k];
+      __syncthreads();
+      if (j0 + kSub < n) fetch(j0 + kSub);
+      for (int s = 0; s < n8; s += 8) {
+        const float *wa = s_w[s + kk], *wb = s_w[s + 4 + kk];
+        const float va = wa[2 * w + (row >> 3)] * wa[8 + (row & 7)];
+        const float vb = wb[2 * w + (row >> 3)] * wb[8 + (row & 7)];
+        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(va, wa[16 + row], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(vb, wb[16 + row], acc1, 0, 0, 0);
+      }
+      __syncthreads();
+    }
+    n = 0;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int p = 16 * w + 4 * kk + i;
+    const int64_t x = kTX * tx + (p >> 3), y = kTX * ty + (p & 7);
+    a.buf0[(x * a.M[1] + y) * a.M[2] + kTZ * tz + row] = acc0[i] + acc1[i];
+  }
+}
+
+// Axis transforms. Each group of 16 k is summed by the matrix cores in float32 from zero and
+// the groups in float64 (float32 sums over whole lines put 2e-7 into the forces); the operands
+// of the next group are on their way meanwhile.
+// Last axis: out[r][j] = sum_k in[r][k] T[k][j] for r < rows (rows, K and J multiples of 16). A
+// wave takes 16 rows x up to 64 columns; a lane reads four consecutive k of its row at once
+// (step s of a group uses k0 + 4 (l / 16) + s, for T as well).
+__global__ __launch_bounds__(256) void k_em_right(const float* __restrict__ in,
+                                                  const float* __restrict__ T,
+                                                  float* __restrict__ out, int64_t rows, int K, int J) {
+  const int lane = threadIdx.x & 63, row = lane & 15, kk = lane >> 4;
+  const int jt = (J + 63) / 64;
+  const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t r0 = wv / jt * 16;
+  if (r0 >= rows) return;
+  const int j0 = (int)(wv % jt) * 64;
+  const int nj = min(4, (J - j0) / 16);
+  double acc[4][4] = {};   // [column tile][row]
+  const float* ip = in + (r0 + row) * K + 4 * kk;
+  const float* tp = T + (int64_t)4 * kk * J + j0 + row;
+  float4 av;
+  float bv[4][4];
+  auto load = [&](int k0, float4& va, float (&vb)[4][4]) {
+    va = *reinterpret_cast<const float4*>(ip + k0);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) vb[s][c] = c < nj ? tp[(int64_t)(k0 + s) * J + 16 * c] : 0.f;
+  };
+  load(0, av, bv);
+  for (int k0 = 0; k0 < K; k0 += 16) {
+    float4 an;
+    float bn[4][4];
+    load(k0 + 16 < K ? k0 + 16 : 0, an, bn);
+    const float a4[4] = {av.x, av.y, av.z, av.w};
+    v4f g[4] = {};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        g[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[s], bv[s][c], g[c], 0, 0, 0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[c][i] += (double)g[c][i];
+    av = an;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) bv[s][c] = bn[s][c];
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    if (c >= nj) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[(r0 + 4 * kk + i) * J + j0 + 16 * c + row] = (float)acc[c][i];
+  }
+}
+
+// Another axis: out[b][i][j] = sum_k T[k][i] in[b][k][j] for b < nb, i < I, j < J (multiples of
+// 16). A wave takes 16 rows i x 32 columns j. kScale (the last forward transform: i = nx, j =
+// (ny, nz)): R is scaled to Q in float64 and the wave's part of the energy, 1/2 sum Q R, goes
+// to epart.
+template <bool kScale>
+__global__ __launch_bounds__(256) void k_em_left(EwMeshArgs a, const float* __restrict__ in,
+                                                 const float* __restrict__ T,
+                                                 float* __restrict__ out, int64_t nb, int I, int K,
+                                                 int64_t J) {
+  const int lane = threadIdx.x & 63, row = lane & 15, kk = lane >> 4;
+  const int64_t jt = (J + 31) / 32;
+  const int it = I / 16;
+  const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (wv >= nb * it * jt) return;
+  const int64_t j0 = wv % jt * 32, b = wv / (jt * it);
+  const int i0 = (int)(wv / jt % it) * 16;
+  const bool two = j0 + 32 <= J;
+  double acc[2][4] = {};   // [column tile][row]
+  const float* ip = in + (b * K + kk) * J + j0 + row;
+  const float* tp = T + (int64_t)kk * I + i0 + row;
+  float av[4], bv[4][2];
+  auto load = [&](int k0, float (&va)[4], float (&vb)[4][2]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      va[s] = tp[(int64_t)(k0 + 4 * s) * I];
+      vb[s][0] = ip[(k0 + 4 * s) * J];
+      vb[s][1] = two ? ip[(k0 + 4 * s) * J + 16] : 0.f;
+    }
+  };
+  load(0, av, bv);
+  for (int k0 = 0; k0 < K; k0 += 16) {
+    float an[4], bn[4][2];
+    load(k0 + 16 < K ? k0 + 16 : 0, an, bn);
+    v4f g[2] = {};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        g[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s], bv[s][c], g[c], 0, 0, 0);
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[c][i] += (double)g[c][i];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      av[s] = an[s];
+      bv[s][0] = bn[s][0];
+      bv[s][1] = bn[s][1];
+    }
+  }
+  double e = 0.0;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (c == 1 && !two) break;
+    const int64_t j = j0 + 16 * c + row;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ii = i0 + 4 * kk + i;
+      double v = acc[c][i];
+      if constexpr (kScale) {
+        const int ny = (int)(j / a.N[2]), nz = (int)(j % a.N[2]);
+        const double k2 = a.ksq[0][ii] + a.ksq[1][ny] + a.ksq[2][nz];
+        const double g = k2 > 0.0 ? a.gscale * a.gfac[0][ii] * a.gfac[1][ny] * a.gfac[2][nz] / k2 : 0.0;
+        const double q = g * v;
+        e += 0.5 * q * v;
+        v = q;
+      }
+      out[(b * I + ii) * J + j] = (float)v;
+    }
+  }
+  if constexpr (kScale) {
+    for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o);
+    if (lane == 0) a.epart[wv] = e;
+  }
+}
+
+// Sum over a wave in a fixed order, in every lane.
+__device__ inline float wave_sum(float v) {
+  auto dpp = [](float x, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+        0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  v += dpp(v, std::integral_constant<int, 0xB1>());    // xor 1
+  v += dpp(v, std::integral_constant<int, 0x4E>());    // xor 2
+  v += dpp(v, std::integral_constant<int, 0x141>());   // mirror within 8
+  v += dpp(v, std::integral_constant<int, 0x140>());   // mirror within 16
+  auto at = [&](int l) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l)); };
+  return (at(0) + at(16)) + (at(32) + at(48));
+}
+
+// Forces, one workgroup of 4 waves per tile: the potential's coefficients around the tile
+// (17 x 17 x 25 points) in LDS; a wave takes an atom of the tile's bin at a time, its lanes the
+// 100 (x, y) rows of the window (two rounds), each summing its row's 10 z values from both ends
+// with phi_z and phi_z' (uniform, in scalar registers). The coefficient at the atom's own grid
+// point is taken off every value: a constant exerts no force, and the derivative's rounding
+// then scales with the potential's change over the window, not with the potential.
+__global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
+  constexpr int kRX = kTX + kW - 1, kRZ = kTZ + kW - 1;   // points around the tile
+  constexpr int kQuads = (kRZ + 3) / 4;                   // 16-byte loads per row
+  __shared__ float s_c[kRX * kRX * kRZ];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int bin = blockIdx.x;
+  const int tz = bin % a.nt[2], ty = (bin / a.nt[2]) % a.nt[1], tx = bin / (a.nt[2] * a.nt[1]);
+  const int s0 = a.start[bin], s1 = a.start[bin + 1];
+  if (s0 == s1) return;
+  // rows start 4 points before a multiple of 16 on an axis of a multiple of 16, so a quad never
+  // straddles the box edge and is aligned
+  static_assert(kLo == 4 && kTZ % 4 == 0, "aligned quads");
+#pragma unroll 4
+  for (int e = t; e < kRX * kRX * kQuads; e += 256) {
+    const int qd = e % kQuads, rw = e / kQuads;
+    int x = rw / kRX + kTX * tx - kLo, y = rw % kRX + kTX * ty - kLo, z = 4 * qd + kTZ * tz - kLo;
+    x += x < 0 ? a.M[0] : x >= a.M[0] ? -a.M[0] : 0;
+    y += y < 0 ? a.M[1] : y >= a.M[1] ? -a.M[1] : 0;
+    z += z < 0 ? a.M[2] : z >= a.M[2] ? -a.M[2] : 0;
+    const float4 v = *reinterpret_cast<const float4*>(&a.buf0[((int64_t)x * a.M[1] + y) * a.M[2] + z]);
+    float* d = s_c + rw * kRZ + 4 * qd;
+    d[0] = v.x;
+    if (4 * qd + 1 < kRZ) {
+      d[1] = v.y;
+      d[2] = v.z;
+      d[3] = v.w;
+    }
+  }
+  static_assert(kRZ % 4 == 1, "the last quad of a row holds one point");
+  // this lane's window rows, and its part of an atom's windows: lane 10 d + k point k of axis d
+  const bool in1 = lane + 64 < kW * kW;
+  const int i0 = lane / kW, j0 = lane % kW, i1 = in1 ? (lane + 64) / kW : 0,
+            j1 = in1 ? (lane + 64) % kW : 0;
+  const int r0 = (i0 * kRX + j0) * kRZ, r1 = (i1 * kRX + j1) * kRZ;
+  const int wl = min(lane, 31);
+  uint4 u = make_uint4(0, 0, 0, 0);
+  float wv = 0.f, dw = 0.f;
+  int id = 0;
+  auto fetch = [&](int s) {
+    s = min(s, s1 - 1);
+    u = a.rec[s];
+    wv = a.win[(int64_t)s * 32 + wl];
+    dw = a.dwin[(int64_t)s * 32 + wl];
+    id = a.sid[s];
+  };
+  fetch(s0 + w);
+  __syncthreads();
+  for (int s = s0 + w; s < s1; s += 4) {
+    const float q = __uint_as_float(u.w);
+    const int64_t at = 3 * (int64_t)id;
+    uint32_t f;
+    const int l = ((grid_cell(u.x, a.M[0], f) % kTX) * kRX + grid_cell(u.y, a.M[1], f) % kTX) * kRZ +
+                  grid_cell(u.z, a.M[2], f) % kTZ;
+    float wz[kW], dz[kW];
+#pragma unroll
+    for (int z = 0; z < kW; ++z) {
+      wz[z] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wv), 2 * kW + z));
+      dz[z] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(dw), 2 * kW + z));
+    }
+    const float wx0 = __shfl(wv, i0), dx0 = __shfl(dw, i0), wy0 = __shfl(wv, kW + j0),
+                dy0 = __shfl(dw, kW + j0);
+    const float wx1 = __shfl(wv, i1), dx1 = __shfl(dw, i1), wy1 = __shfl(wv, kW + j1),
+                dy1 = __shfl(dw, kW + j1);
+    fetch(s + 4);
+    const float cm = s_c[l + (kLo * kRX + kLo) * kRZ + kLo];
+    const float *ca = s_c + l + r0, *cb = s_c + l + r1;
+    float p0[2] = {0.f, 0.f}, z0[2] = {0.f, 0.f}, p1[2] = {0.f, 0.f}, z1[2] = {0.f, 0.f};
+#pragma unroll
+    for (int z = 0; z < kW / 2; ++z) {
+      const int y = kW - 1 - z;
+      const float va = ca[z] - cm, vb = ca[y] - cm, vc = cb[z] - cm, vd = cb[y] - cm;
+      p0[0] = fmaf(va, wz[z], p0[0]);
+      p0[1] = fmaf(vb, wz[y], p0[1]);
+      z0[0] = fmaf(va, dz[z], z0[0]);
+      z0[1] = fmaf(vb, dz[y], z0[1]);
+      p1[0] = fmaf(vc, wz[z], p1[0]);
+      p1[1] = fmaf(vd, wz[y], p1[1]);
+      z1[0] = fmaf(vc, dz[z], z1[0]);
+      z1[1] = fmaf(vd, dz[y], z1[1]);
+    }
+    const float pa = p0[0] + p0[1], pb = in1 ? p1[0] + p1[1] : 0.f;
+    const float za = z0[0] + z0[1], zb = in1 ? z1[0] + z1[1] : 0.f;
+    float F[3] = {fmaf(dx0 * wy0, pa, dx1 * wy1 * pb), fmaf(wx0 * dy0, pa, wx1 * dy1 * pb),
+                  fmaf(wx0 * wy0, za, wx1 * wy1 * zb)};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) F[c] = wave_sum(F[c]);
+    if (lane < 3) {
+      const double g = (double)(lane == 0 ? F[0] : lane == 1 ? F[1] : F[2]);
+      const float v = (float)((double)q * g * ((double)a.M[lane] / a.L[lane]));
+      float* out = a.force + at + lane;
+      *out = a.accumulate ? *out + v : v;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_em_energy(EwMeshArgs a) {
+  ew_energy_sum(a.epart, a.nepart, a.qpart, a.qblocks, a.L, a.alpha, a.coulomb_k, a.energy);
+}
+
+}  // namespace
+
+// Which systems take the grid: from 1.5e8 (atom, half-space wave vector) pairs on, where it is
+// both faster and no less accurate than the direct sum (whole call, and RMS force error
+// against float64, direct and grid: 5,000 atoms x 1.2e4 wave vectors 140 us 2.7e-7, 80 us
+// 4.1e-7; 9,001 x 1.9e4 226 us 3.9e-7, 94 us 3.8e-7; 20,000 x 2.5e4 292 us 5.2e-7, 114 us 3.8e-7;
+// 40,000 x 9.3e4 1205 us 9.9e-7, 134 us 5.2e-7; 92,224 x 1.78e5 4897 us 2.4e-6, 208 us 4.2e-7);
+// not where its workspace would be more than twice the direct sum's and 512 MiB (few atoms
+// with hundreds of wave numbers per axis).
+bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t direct_bytes,
+                  EwMeshPlan* pl) {
+  const double vectors = 0.5 * (2.0 * kmax[0] + 1) * (2.0 * kmax[1] + 1) * (2.0 * kmax[2] + 1);
+  if ((double)n * vectors < 1.5e8) return false;
+  for (int d = 0; d < 3; ++d) {
+    const int K = kmax[d];
+    pl->K[d] = K;
+    pl->N[d] = (2 * (K + 1) + 15) / 16 * 16;
+    int M = ((int)ceil(1.75 * (2 * K + 1)) + 15) / 16 * 16;
+    const int least = d == 2 ? 3 * kTZ : 2 * kTZ;   // at least three tiles on every axis
+    pl->M[d] = M < least ? least : M;
+    pl->nt[d] = pl->M[d] / (d == 2 ? kTZ : kTX);
+  }
+  pl->nbins = (int64_t)pl->nt[0] * pl->nt[1] * pl->nt[2];
+  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t nn = (size_t)n;
+  size_t o = al(sizeof(WsHeader));
+  pl->off_ups = o;   o = al(o + 16 * nn);
+  pl->off_rec = o;   o = al(o + 16 * nn);
+  pl->off_win = o;   o = al(o + 128 * nn);
+  pl->off_dwin = o;  o = al(o + 128 * nn);
+  pl->off_slot = o;  o = al(o + 8 * nn);
+  pl->off_ids = o;   o = al(o + 4 * nn);
+  pl->off_sid = o;   o = al(o + 4 * nn);
+  pl->off_count = o; o = al(o + 4 * (size_t)pl->nbins);
+  pl->off_start = o; o = al(o + 4 * (size_t)(pl->nbins + 1));
+  const size_t M0 = pl->M[0], M1 = pl->M[1], M2 = pl->M[2], N0 = pl->N[0], N1 = pl->N[1], N2 = pl->N[2];
+  pl->off_buf0 = o;  o = al(o + 4 * M0 * M1 * M2);
+  pl->off_buf1 = o;  o = al(o + 4 * M0 * M1 * N2);
+  pl->off_buf2 = o;  o = al(o + 4 * M0 * N1 * N2);
+  pl->off_buf3 = o;  o = al(o + 4 * N0 * N1 * N2);
+  for (int d = 0; d < 3; ++d) {
+    const size_t e = (size_t)pl->N[d] * pl->M[d];
+    pl->off_tab[d] = o;  o = al(o + 4 * e);
+    pl->off_tabT[d] = o; o = al(o + 4 * e);
+    pl->off_gfac[d] = o; o = al(o + 8 * (size_t)pl->N[d]);
+    pl->off_ksq[d] = o;  o = al(o + 8 * (size_t)pl->N[d]);
+  }
+  pl->nepart = (int64_t)(N0 / 16) * ((N1 * N2 + 31) / 32);
+  pl->off_epart = o; o = al(o + 8 * (size_t)pl->nepart);
+  pl->qblocks = (n + 255) / 256;
+  pl->off_qpart = o; o = al(o + 16 * (size_t)pl->qblocks);
+  pl->total = o;
+  return o <= 2 * direct_bytes || o <= (size_t)512 << 20;
+}
+
+hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, const float* pos,
+                          const float* q, float* force, double* energy, int accumulate, void* ws,
+                          hipStream_t st) {
+  EwMeshArgs a;
+  char* b = (char*)ws;
+  a.n = n;
+  a.pos = pos;
+  a.q = q;
+  a.force = force;
+  a.energy = energy;
+  a.accumulate = accumulate;
+  a.hdr = (WsHeader*)b;
+  a.ups = (uint4*)(b + pl.off_ups);
+  a.rec = (uint4*)(b + pl.off_rec);
+  a.win = (float*)(b + pl.off_win);
+  a.dwin = (float*)(b + pl.off_dwin);
+  a.slot = (int2*)(b + pl.off_slot);
+  a.ids = (int*)(b + pl.off_ids);
+  a.sid = (int*)(b + pl.off_sid);
+  a.count = (int*)(b + pl.off_count);
+  a.start = (int*)(b + pl.off_start);
+  a.buf0 = (float*)(b + pl.off_buf0);
+  float* buf1 = (float*)(b + pl.off_buf1);
+  float* buf2 = (float*)(b + pl.off_buf2);
+  float* buf3 = (float*)(b + pl.off_buf3);
+  a.epart = (double*)(b + pl.off_epart);
+  a.qpart = (double2*)(b + pl.off_qpart);
+  a.nepart = pl.nepart;
+  a.qblocks = pl.qblocks;
+  a.nbins = pl.nbins;
+  a.alpha = p->ewald_alpha;
+  a.coulomb_k = p->coulomb_k;
+  double V = 1;
+  int64_t entries = 0, modes = 0;
+  for (int d = 0; d < 3; ++d) {
+    a.M[d] = pl.M[d];
+    a.N[d] = pl.N[d];
+    a.K[d] = pl.K[d];
+    a.nt[d] = pl.nt[d];
+    a.L[d] = (double)(float)p->box[d];   // the float32 box
+    V *= a.L[d];
+    a.tab[d] = (float*)(b + pl.off_tab[d]);
+    a.tabT[d] = (float*)(b + pl.off_tabT[d]);
+    a.gfac[d] = (double*)(b + pl.off_gfac[d]);
+    a.ksq[d] = (double*)(b + pl.off_ksq[d]);
+    entries += (int64_t)pl.N[d] * pl.M[d];
+    modes += pl.N[d] / 2;
+    // the window's shape for the axis's oversampling (no narrower past 2.5)
+    const double sigma = fmin(2.5, (double)pl.M[d] / (2.0 * pl.K[d] + 1.0));
+    a.cb[d] = kW * M_PI * (1.0 - 0.5 / sigma) * M_LOG2E;
+  }
+  a.gscale = 4.0 * M_PI * p->coulomb_k / V;
+  const unsigned nb = (unsigned)((n + 255) / 256);
+  const unsigned nb_tab = (unsigned)((entries + 255) / 256);
+  hipLaunchKernelGGL(k_em_init, dim3(nb_tab + (unsigned)((modes + 3) / 4)), dim3(256), 0, st, a, nb_tab);
+  hipLaunchKernelGGL(k_em_setup, dim3(nb), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_em_scan, dim3(1), dim3(1024), 0, st, a);
+  hipLaunchKernelGGL(k_em_scatter, dim3(nb), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_em_sort, dim3((unsigned)((pl.nbins + 3) / 4)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_em_spread, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
+  const int64_t rows = (int64_t)a.M[0] * a.M[1];
+  auto right = [&](const float* in, const float* T, float* out, int K, int J) {
+    const int64_t waves = rows / 16 * ((J + 63) / 64);
+    hipLaunchKernelGGL(k_em_right, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, in, T, out, rows, K, J);
+  };
+  auto left = [&](auto scale, const float* in, const float* T, float* out, int64_t batch, int I, int K, int64_t J) {
+    const int64_t waves = batch * (I / 16) * ((J + 31) / 32);
+    hipLaunchKernelGGL((k_em_left<decltype(scale)::value>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st,
+                       a, in, T, out, batch, I, K, J);
+  };
+  const int64_t Jx = (int64_t)a.N[1] * a.N[2];
+  right(a.buf0, a.tabT[2], buf1, a.M[2], a.N[2]);                                      // z
+  left(std::false_type(), buf1, a.tabT[1], buf2, a.M[0], a.N[1], a.M[1], a.N[2]);      // y
+  left(std::true_type(), buf2, a.tabT[0], buf3, 1, a.N[0], a.M[0], Jx);                // x, Q, E
+  left(std::false_type(), buf3, a.tab[0], buf2, 1, a.M[0], a.N[0], Jx);                // x back
+  left(std::false_type(), buf2, a.tab[1], buf1, a.M[0], a.M[1], a.N[1], a.N[2]);       // y back
+  right(buf1, a.tab[2], a.buf0, a.N[2], a.M[2]);                                       // z back
+  hipLaunchKernelGGL(k_em_force, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_em_energy, dim3(1), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace md
