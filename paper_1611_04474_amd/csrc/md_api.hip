@@ -101,11 +101,11 @@ static bool uses_compact(const md_params* p, int real_bytes) {
 // workgroup per compute unit. The choice is the least time of a model of the kernel in
 // microseconds,
 //   rounds x (start + loops x (staging of L + groups per wave x (group + filter and force of L)))
-// with L the atoms of a slice, fitted to a sweep of 1-8 slices x 1-8 parts (pair stage and
-// binning of 3,000 to 92,224 atoms; within 15% over the sweep, and its choice within 7% of the
-// sweep's best). Whole calls, one split before (parts only, at most 4) and now: 3,000 atoms in
-// 8 cells 103 -> 66 us, 9,001 in 40 73 -> 61, 6,000 in 27 68 -> 54, 20,000 in 64 92 -> 82,
-// float64 3,000 427 -> 138. At 343 and 486 cells (one workgroup each) a second slice
+// with L the atoms of a slice, fitted to a sweep of 1-8 slices x 1-8 parts (whole calls of
+// 3,000 to 92,224 atoms; within 15% over the sweep's faster half, and its choice within 8% of
+// the sweep's best). Whole calls, one split before (parts only, at most 4) and now: 3,000 atoms
+// in 8 cells 103 -> 66 us, 9,001 in 40 73 -> 61, 6,000 in 27 68 -> 54, 20,000 in 64 92 -> 82,
+// float64 3,000 427 -> 138 (then with 16 waves a workgroup). At 343 and 486 cells (one workgroup each) a second slice
 // costs 13% and 30%, so grids of more than 256 cells stay whole. The full shell stores each
 // atom's sum without atomics, so its slices stay in one workgroup.
 FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bool half) {
@@ -113,8 +113,8 @@ FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bo
   const uint32_t v = (flags & MD_PAIR_SPLIT_MASK) >> 8;
   if (n > 0 && n_cells > 0 && n_cells <= kFsMaxCells) {
     const bool f64 = real_bytes == 8;
-    const double start = f64 ? 5.2 : 11.1, stage = 0.0033, group = f64 ? 42.5 : 9.0,
-                 pair = f64 ? 0.0252 : 0.0026, lds = f64 ? 1472 : 3008;
+    const double start = f64 ? 13.8 : 11.1, stage = f64 ? 0.0071 : 0.0033, group = f64 ? 10.2 : 9.0,
+                 pair = f64 ? 0.0011 : 0.0026, lds = f64 ? 1600 : 3008, wg_waves = f64 ? 8 : 16;
     const double groups = (double)n / (double)n_cells / 4.0;   // of 4 home atoms, per cell
     const double list = (half ? 14.0 : 27.0) * (double)n / (double)n_cells;   // staged atoms
     double t_best = 0;
@@ -123,7 +123,7 @@ FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bo
         const double wgs = (double)(n_cells * s * g) / 256.0;
         const double rounds = wgs < 3.0 ? ceil(wgs) : wgs + 0.5;
         const double cut = fmax((double)s, ceil(list / lds)), loops = ceil(cut / s);
-        const double waves = groups / g / 16.0, per_wave = waves < 1.0 ? 1.0 : waves + 0.2;
+        const double waves = groups / g / wg_waves, per_wave = waves < 1.0 ? 1.0 : waves + (f64 ? 0.03 : 0.2);
         const double t =
             rounds * (start + loops * (stage * list / cut + per_wave * (group + pair * list / cut)));
         if (t_best == 0 || t < t_best) {

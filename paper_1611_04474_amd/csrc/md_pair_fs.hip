@@ -4,7 +4,7 @@
 // design (Section 5.2, Fig. 4; Algorithm 3): several cutoff filters feed one force stage
 // through FIFOs, and the force stage only ever works on pairs that passed.
 //
-// One workgroup (16 waves) takes one home cell. It stages the atoms of its neighbour-
+// One workgroup (16 waves; float64: 8) takes one home cell. It stages the atoms of its neighbour-
 // cell images in LDS, periodic images shifted exactly (the side lying in the
 // last cell of an axis subtracts L, which is Sterbenz-exact). Each z half of a cell is
 // sorted by x, so one z half of the images of one (dy, dz) row, laid out in x order,
@@ -57,11 +57,15 @@
 namespace md {
 namespace {
 
-constexpr int kNW = 16;             // waves per workgroup
-constexpr int kThreads = 64 * kNW;
+// Waves per workgroup (one workgroup per compute unit: its LDS). float32: 16, of up to 128
+// registers each. float64: 8, of up to 256; with 16 the records and sums of two registers a
+// value did not fit (135 spilled, 328 with the erfc term), and no wave was short of company:
+// 24,000 atoms 351 -> 171 us whole call, 92,224 965 -> 434.
+template <typename Real>
+constexpr int kWaves = sizeof(Real) == 8 ? 8 : 16;
 constexpr int kQ = 4;               // home atoms filtered together by one wave, one FIFO each
 static_assert(kQ % 4 == 0, "FIFO appends are written four home atoms at a time");
-static_assert(kNW % 4 == 0 && kNW * 64 <= 1024, "waves per workgroup");
+static_assert(kWaves<float> % 4 == 0 && kWaves<float> * 64 <= 1024, "waves per workgroup");
 // Force batches of 64 drained together from a full FIFO (kDrain, a template parameter of
 // the kernel: 2 by default, 1 to 4 for the drain-depth sweep); a FIFO holds
 // 64 (kDrain + 1) uint16 neighbour indices.
@@ -189,7 +193,7 @@ __host__ __device__ inline Lds lds_layout(int cap, int n_types, bool half, bool 
   Lds L;
   L.hdr = 0;
   L.fifo = align_up(L.hdr + (int)sizeof(Hdr), 16);
-  L.lj = align_up(L.fifo + 2 * kNW * kQ * fifo_entries(drain), 16);
+  L.lj = align_up(L.fifo + 2 * kWaves<Real> * kQ * fifo_entries(drain), 16);
   L.f4 = align_up(L.lj + 2 * R * n_types * n_types, 4 * R);
   L.q = L.f4 + 4 * R * cap;
   L.typ = L.q + R * cap;
@@ -280,6 +284,16 @@ __device__ inline void global_add(long long* p, long long v) {
 //                  reciprocal space beyond the short-range kernel.
 constexpr int kCoulSwitched = 0, kCoulPlain = 1, kCoulEwald = 2;
 
+// 1/sqrt(u) in float64: the hardware's estimate (about 2^-23) and one third-order step,
+// r (1 + e/2 + 3 e^2/8) with e = 1 - u r^2 (error e^3, below the rounding), in place of a
+// correctly rounded root and a division (about 30 instructions): 24,000 atoms 171 -> 158 us,
+// 92,224 434 -> 375; the RMS force error against float64 sums 1.0e-15 -> 0.9e-15.
+__device__ inline double rsqrt64(double u) {
+  const double r = __builtin_amdgcn_rsq(u);
+  const double e = fma(-(u * r), r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
+}
+
 // Pair force factor f (F_i = f r_ij) and pair energy e at squared distance u.
 // c12 = 4 eps s^12, c6 = 4 eps s^6 (Eq. 1: A = 12 c12, B = 6 c6); qq = k q_i q_j (Eq. 2).
 // The switch in s = 1 - t = clamp((rc^2 - u)/(rc^2 - rs^2), 0, 1): S = s^2 (3 - 2s) =
@@ -298,7 +312,7 @@ __device__ inline Real pair_f(Real u, Real c12, Real c6, Real qq, Real rc2, Real
     rinv = __builtin_amdgcn_rsqf(u);
     s = __builtin_amdgcn_fmed3f((rc2 - u) * inv_sw, 0.f, 1.f);
   } else {
-    rinv = 1.0 / sqrt(u);
+    rinv = rsqrt64(u);
     s = fmin(fmax((rc2 - u) * inv_sw, 0.0), 1.0);
   }
   const Real r2 = rinv * rinv;
@@ -345,6 +359,8 @@ __device__ inline uint32_t lshl1_add(uint32_t n, uint32_t b) {
   return r;
 }
 
+// Addresses are relative: FIFO k lies k kStride bytes further (an immediate offset).
+template <int kStride>
 __device__ inline void lds_store_u16_lanes4(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3,
                                             uint32_t v, unsigned long long m0,
                                             unsigned long long m1, unsigned long long m2,
@@ -355,16 +371,56 @@ __device__ inline void lds_store_u16_lanes4(uint32_t a0, uint32_t a1, uint32_t a
       "s_and_b64 exec, %0, %6\n\t"
       "ds_write_b16 %1, %5\n\t"
       "s_and_b64 exec, %0, %7\n\t"
-      "ds_write_b16 %2, %5\n\t"
+      "ds_write_b16 %2, %5 offset:%10\n\t"
       "s_and_b64 exec, %0, %8\n\t"
-      "ds_write_b16 %3, %5\n\t"
+      "ds_write_b16 %3, %5 offset:%11\n\t"
       "s_and_b64 exec, %0, %9\n\t"
-      "ds_write_b16 %4, %5\n\t"
+      "ds_write_b16 %4, %5 offset:%12\n\t"
       "s_mov_b64 exec, %0"
       : "=&s"(saved)
-      : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(v), "s"(m0), "s"(m1), "s"(m2), "s"(m3)
+      : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(v), "s"(m0), "s"(m1), "s"(m2), "s"(m3),
+        "n"(kStride), "n"(2 * kStride), "n"(3 * kStride)
       : "memory", "scc");
 }
+
+// The prefilter of a group of home atoms: |r_j - r_i|^2 < rc^2 + margin in the expanded form
+// c_j + (-2 a_i).r_j < thr_i, with the constants that the in-cell sort wrote (SysArgs::hpre); an
+// absent atom (past nv) has a = 0 and thr = -1, which c_j >= 0 never passes.
+// Three FMAs and a compare per pair. On the matrix cores (4x4x1 products of 16 blocks, a lane's
+// neighbour against the four home atoms) the 12 FMAs of a batch become 3 to 5 instructions, but
+// their dependent latency costs more than the issue slots they free: 92,224 atoms 164.0 ->
+// 168.8 us whole call, 1,066,628 1569 -> 1623.
+template <typename Real>
+struct Pre {
+  Real ax[kQ], ay[kQ], az[kQ], thb[kQ], thr[kQ];   // thb: in the frame of no shift
+  __device__ inline void load(const SysArgs<Real>& a, int64_t s, int nv) {
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) {
+      const P4<Real> h = a.hpre[2 * (s + min(k, nv - 1))];
+      const bool in = k < nv;
+      ax[k] = in ? h.x : Real(0);
+      ay[k] = in ? h.y : Real(0);
+      az[k] = in ? h.z : Real(0);
+      thb[k] = thr[k] = in ? h.w : Real(-1);
+    }
+  }
+  // thresholds in the frame that is shifted by (hx, hy, hz): a.o_g = a.o - a.h
+  __device__ inline void shift(Real hx, Real hy, Real hz) {
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) thr[k] = thb[k] - (ax[k] * hx + ay[k] * hy + az[k] * hz);
+  }
+  __device__ inline void test(const V4<Real>& p, unsigned long long (&m)[kQ]) const {
+    Real t[kQ];
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) t[k] = mad(ax[k], p.x, p.w);
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) t[k] = mad(ay[k], p.y, t[k]);
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) t[k] = mad(az[k], p.z, t[k]);
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) m[k] = __builtin_amdgcn_ballot_w64(t[k] < thr[k]);
+  }
+};
 
 // kClamp: the whole energy is switched and the switch is on, so lanes that must add
 // nothing (a partial batch, the home atom itself) get u = kBigU instead of masks on f
@@ -377,6 +433,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
   constexpr bool kF32 = sizeof(Real) == 4;
   constexpr int kImg = kHalf ? 14 : 27;   // neighbour images
+  constexpr int kNW = kWaves<Real>, kThreads = 64 * kNW;
   constexpr int kFifo = fifo_entries(kDrain);
   constexpr int kWaveFifo = kQ * kFifo;
   constexpr uint32_t kS = sizeof(V4<Real>);   // bytes per staged atom record
@@ -642,26 +699,25 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
       // ay, az; thb, and thr, the threshold in the current frame), k q and its row of the
       // type-pair table, loaded as the in-cell sort wrote them; an absent atom (past nv)
       // repeats the last one with ax = 0 and thb = -1, which c_j >= 0 never passes
-      Real xi[kQ], yi[kQ], zi[kQ], thb[kQ];   // frame of no shift
-      Real xs[kQ], ys[kQ], zs[kQ], thr[kQ], kq[kQ], fx[kQ], fy[kQ], fz[kQ];
-      Real ax[kQ], ay[kQ], az[kQ];
+      Real xi[kQ], yi[kQ], zi[kQ];   // frame of no shift
+      Real xs[kQ], ys[kQ], zs[kQ], kq[kQ], fx[kQ], fy[kQ], fz[kQ];
+      Pre<Real> pre;
+      pre.load(a, sA + ib, nv);
       int row[kQ];
-      uint32_t fb[kQ];   // byte address of the next free slot of FIFO k
-      uint32_t fl[kQ];   // fb[k] at which FIFO k holds a full drain
+      // byte address of the next free slot of FIFO k, less the 2 k kFifo bytes by which FIFO k
+      // starts after FIFO 0: all of them hold a full drain at the same value
+      uint32_t fb[kQ];
+      const uint32_t full = fk0 + 2u * (uint32_t)(64 * kDrain);
       unsigned cnt[kQ];
       Real xmin = 0, xmax = 0, ymin = 0, ymax = 0, zmin = 0, zmax = 0;
 #pragma unroll
       for (int k = 0; k < kQ; ++k) {
         const int s = sA + ib + min(k, nv - 1);
         const P4<Real> p = a.pos[s];
-        const P4<Real> h0 = a.hpre[2 * (int64_t)s], h1 = a.hpre[2 * (int64_t)s + 1];
+        const P4<Real> h1 = a.hpre[2 * (int64_t)s + 1];
         xi[k] = p.x;
         yi[k] = p.y;
         zi[k] = p.z;
-        ax[k] = h0.x;
-        ay[k] = h0.y;
-        az[k] = h0.z;
-        thb[k] = h0.w;
         kq[k] = h1.x;
         row[k] = slot_to_int(h1.y);
         xmin = k == 0 ? p.x : vmin(xmin, p.x);
@@ -671,25 +727,14 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
         zmin = k == 0 ? p.z : vmin(zmin, p.z);
         zmax = k == 0 ? p.z : vmax(zmax, p.z);
         fx[k] = fy[k] = fz[k] = Real(0);
-        fb[k] = fk0 + 2u * (uint32_t)(k * kFifo);
-        fl[k] = fb[k] + 2u * (uint32_t)(64 * kDrain);
+        fb[k] = fk0;
         cnt[k] = 0;
-      }
-      if (nv < kQ) {
-#pragma unroll
-        for (int k = 1; k < kQ; ++k) {
-          if (k >= nv) {
-            ax[k] = ay[k] = az[k] = Real(0);
-            thb[k] = Real(-1);
-          }
-        }
       }
 #pragma unroll
       for (int k = 0; k < kQ; ++k) {
         xs[k] = xi[k];
         ys[k] = yi[k];
         zs[k] = zi[k];
-        thr[k] = thb[k];
       }
       Real e_lane = 0;
       // the largest |F_j| component |f dx| handed to the neighbour side (float32: as
@@ -726,7 +771,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
 
       // entries in FIFO k
       auto fill = [&](int k) __attribute__((always_inline)) {
-        return (int)((fb[k] - fk0) >> 1) - k * kFifo;
+        return (int)((fb[k] - fk0) >> 1);
       };
       // type of a staged atom
       auto type_of = [&](int jl, const R4& pj) __attribute__((always_inline)) {
@@ -811,7 +856,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
           if (lane < rem) v = fifo[k * kFifo + c + lane];
           if (lane < rem) fifo[k * kFifo + lane] = v;
         }
-        fb[k] = fk0 + 2u * (uint32_t)(k * kFifo + rem);
+        fb[k] = fk0 + 2u * (uint32_t)rem;
       };
       // every entry left in the FIFOs, one 64-lane pass at a time (the home side is about
       // to change frame, or the group is done)
@@ -827,7 +872,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
             const R2 lj = sLJ[row[k] + type_of(jj, pj)];
             pair_lane(k, jj, pj, qj, lj, off + lane < n);
           }
-          fb[k] = fk0 + 2u * (uint32_t)(k * kFifo);
+          fb[k] = fk0;
         }
       };
 
@@ -852,9 +897,8 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
             xs[k] = xi[k] - hx;   // exact: such home atoms lie in the last cell of the axis
             ys[k] = yi[k] - hy;
             zs[k] = zi[k] - hz;
-            // ax.o_g = ax.o - ax.h (an absent atom keeps thr = -1: its ax is 0)
-            thr[k] = thb[k] - (ax[k] * hx + ay[k] * hy + az[k] * hz);
           }
+          pre.shift(hx, hy, hz);
         }
         if (diag) slot_count += (unsigned long long)(hi - lo) * (unsigned long long)nv;
         // se: end of this segment. Lanes in [hi, se) are neighbours of this segment (this
@@ -865,16 +909,8 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
         for (int jb = lo; jb < hi; jb += 64) {
           const int j = jb + lane;
           const R4 pj = sF[j];
-          Real t[kQ];
-#pragma unroll
-          for (int k = 0; k < kQ; ++k) t[k] = mad(ax[k], pj.x, pj.w);
-#pragma unroll
-          for (int k = 0; k < kQ; ++k) t[k] = mad(ay[k], pj.y, t[k]);
-#pragma unroll
-          for (int k = 0; k < kQ; ++k) t[k] = mad(az[k], pj.z, t[k]);
           unsigned long long m[kQ];
-#pragma unroll
-          for (int k = 0; k < kQ; ++k) m[k] = __builtin_amdgcn_ballot_w64(t[k] < thr[k]);
+          pre.test(pj, m);
           if (jb + 64 > se_s) {
             const unsigned long long vm = (1ull << (se_s - jb)) - 1ull;   // se_s - jb < 64
 #pragma unroll
@@ -898,7 +934,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
           }
 #pragma unroll
           for (int k = 0; k < kQ; k += 4)
-            lds_store_u16_lanes4(adr[k], adr[k + 1], adr[k + 2], adr[k + 3], (uint32_t)j, m[k],
+            lds_store_u16_lanes4<2 * kFifo>(adr[k], adr[k + 1], adr[k + 2], adr[k + 3], (uint32_t)j, m[k],
                                  m[k + 1], m[k + 2], m[k + 3]);
 #pragma unroll
           for (int k = 0; k < kQ; ++k) fb[k] = lshl1_add((uint32_t)__builtin_popcountll(m[k]), fb[k]);
@@ -906,9 +942,11 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
 #pragma unroll
             for (int k = 0; k < kQ; ++k) filt_count += __builtin_popcountll(m[k]);
           }
+          if (max(max(fb[0], fb[1]), max(fb[2], fb[3])) >= full) {
 #pragma unroll
-          for (int k = 0; k < kQ; ++k) {
-            if (fb[k] >= fl[k]) force(k);
+            for (int k = 0; k < kQ; ++k) {
+              if (fb[k] >= full) force(k);
+            }
           }
         }
       }
@@ -1171,7 +1209,7 @@ __device__ inline void record_cost(const SysArgs<Real>& a, int64_t cell, int uni
 }
 
 template <typename Real, bool kHalf, int kCoul, bool kClamp, bool kDiag, int kDrain>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNW / 4, kNW / 4)))
+__global__ __launch_bounds__(64 * kWaves<Real>) __attribute__((amdgpu_waves_per_eu(kWaves<Real> / 4, kWaves<Real> / 4)))
 void k_pair_fs(SysArgs<Real> a, int cap) {
   // home cells in the order the binning chose (longest first)
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
@@ -1185,7 +1223,7 @@ void k_pair_fs(SysArgs<Real> a, int cap) {
 
 // One launch for a batch: block b is cell order[b - cum[s]] of system s.
 template <bool kHalf, int kCoul, bool kClamp, bool kDiag, int kDrain>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNW / 4, kNW / 4)))
+__global__ __launch_bounds__(64 * kWaves<float>) __attribute__((amdgpu_waves_per_eu(kWaves<float> / 4, kWaves<float> / 4)))
 void k_pair_fs_batch(Batch b, int cap) {
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   const uint64_t c0 = __builtin_amdgcn_s_memtime();
@@ -1229,7 +1267,7 @@ hipError_t dispatch(const SysArgs<Real>& a, const Args& args, int n_types, int64
   if (drain != kDrainDefault && !(half && clamp && sizeof(Real) == 4)) return hipErrorInvalidValue;
   const int cap = fs_cap<Real>(n_types, half, diag, drain);
   const size_t shmem = (size_t)lds_layout<Real>(cap, n_types, half, diag, drain).total;
-  const dim3 grid((unsigned)blocks), block(kThreads);
+  const dim3 grid((unsigned)blocks), block(64 * kWaves<Real>);
   auto go = [&](auto h, auto d) {
     constexpr bool H = decltype(h)::value, D = decltype(d)::value;
     if (clamp) {
