@@ -103,13 +103,13 @@ static bool uses_compact(const md_params* p, int real_bytes) {
 //   rounds x (start + loops x (staging of L + groups per wave x (group + filter and force of L)))
 // with L the atoms of a slice, fitted to a sweep of 1-8 slices x 1-8 parts (whole calls of
 // 3,000 to 92,224 atoms; within 15% over the sweep's faster half, and its choice within 8% of
-// the sweep's best). Whole calls, one split before (parts only, at most 4) and now: 3,000 atoms
+// the sweep's best). Whole calls, with at most 4 parts and no slices before, and now: 3,000 atoms
 // in 8 cells 103 -> 66 us, 9,001 in 40 73 -> 61, 6,000 in 27 68 -> 54, 20,000 in 64 92 -> 82,
 // float64 3,000 427 -> 138 (then with 16 waves a workgroup). At 343 and 486 cells (one workgroup each) a second slice
-// costs 13% and 30%, so grids of more than 256 cells stay whole. The full shell stores each
+// costs 13% and 30%, so most cells of a grid of more than 256 stay whole. The full shell stores each
 // atom's sum without atomics, so its slices stay in one workgroup.
 FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bool half) {
-  FsWork best{1, 1};
+  FsWork best{1, 1, 0, 1, 0};
   const uint32_t v = (flags & MD_PAIR_SPLIT_MASK) >> 8;
   if (n > 0 && n_cells > 0 && n_cells <= kFsMaxCells) {
     const bool f64 = real_bytes == 8;
@@ -128,11 +128,37 @@ FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bo
             rounds * (start + loops * (stage * list / cut + per_wave * (group + pair * list / cut)));
         if (t_best == 0 || t < t_best) {
           t_best = t;
-          best = FsWork{g, s};
+          best.split = g;
+          best.slices = s;
         }
       }
   }
-  if (v) best.split = v == 1 ? 1 : v == 2 ? 2 : 4;
+  if (v) {
+    best.split = v == 1 ? 1 : v == 2 ? 2 : 4;
+    return best;
+  }
+  // The last round of workgroups. What is left of a whole number of them per compute unit goes
+  // to the cells that last longest, one more part each; or, where the last round would hold
+  // 128 cells or fewer, those cells, the shortest, are cut so that it is a short one. Whole
+  // calls without and with: 180 cells 111 -> 86 us, 216 114 -> 95, 448 143 -> 139, 486 165 ->
+  // 161, 900 270 -> 262; 264 cells (8 in six parts) 131 -> 108, 300 (44 in three) 145 -> 119, 343
+  // (87 in two) 176 -> 150, 630 209 -> 200. From 2048 cells on it is under 1%.
+  if (n > 0 && n_cells > 0 && n_cells <= kFsMaxShared) {
+    const int64_t units = n_cells * best.split * best.slices, last = units % 256;
+    if (last > 128 || (units < 256 && last > 0)) {
+      const int64_t more = (256 - last) / best.slices;
+      // two half cells of under about 144 atoms take more than one whole (their groups fill the
+      // waves worse): 448 cells of 100 atoms 91 us whole, 98 with 64 of them cut
+      if (best.split < kFsMaxSplit && (n_cells <= kFsMaxCells || n >= 144 * n_cells)) {
+        best.nx = more < n_cells ? more : n_cells;
+        best.xsplit = best.split + 1;
+        best.xlong = 1;
+      }
+    } else if (n_cells > kFsMaxCells && last > 0) {
+      best.nx = last;
+      best.xsplit = last > 66 ? 2 : last < 22 ? 6 : (int)(132 / last);
+    }
+  }
   return best;
 }
 
@@ -143,10 +169,10 @@ static bool half_shell(const md_params* p) {
   return !(p->flags & (MD_ACCUM_F32_ATOMIC | MD_PAIR_FULL_SHELL));
 }
 
-// Workgroups of the compacted kernel per home cell.
+// Workgroups of the compacted kernel.
 static int64_t fs_units(const md_params* p, const Plan& pl, int64_t n) {
   const FsWork w = md_fs_work(p->flags, pl.real_bytes, pl.n_cells, n, half_shell(p));
-  return (int64_t)w.split * w.slices;
+  return ((pl.n_cells - w.nx) * w.split + w.nx * w.xsplit) * w.slices;
 }
 
 md_status make_plan(const md_params* p, int64_t n, int real_bytes, Plan* pl) {
@@ -279,7 +305,10 @@ SysArgs<Real> make_args(const md_params* p, const Plan& pl, int64_t n, const Rea
   a.compact = uses_compact(p, (int)sizeof(Real)) ? 1 : 0;
   a.half_shell = a.compact && half_shell(p) ? 1 : 0;
   const FsWork fw = a.compact ? md_fs_work(p->flags, (int)sizeof(Real), pl.n_cells, n, a.half_shell != 0)
-                              : FsWork{1, 1};
+                              : FsWork{1, 1, 0, 1, 0};
+  a.fs_nx = fw.nx;
+  a.fs_xlong = fw.xlong;
+  a.fs_xsplit = fw.xsplit;
   a.fs_split = fw.split;
   a.fs_slices = a.fs_su = fw.slices;
   return a;
@@ -332,6 +361,7 @@ static bool same_kind(const md_params* x, const md_params* y) {
 // the staging and group overhead. Systems with the costliest workgroups come first, so that
 // short ones fill the tail.
 static void batch_units(int n, SysArgs<float>* sys) {
+  if (n == 1) return;
   double cost[kBatchMax], total = 0;
   for (int s = 0; s < n; ++s) {
     const double m = (double)sys[s].n / (double)sys[s].n_cells;
@@ -341,6 +371,7 @@ static void batch_units(int n, SysArgs<float>* sys) {
   for (int s = 0; s < n; ++s) {
     SysArgs<float>& a = sys[s];
     if (!(a.flags & MD_PAIR_SPLIT_MASK)) {   // a split that the caller forces stays
+      a.fs_nx = 0;
       const int units = (int)fmin(64.0, ceil(cost[s] * 512.0 / total));
       a.fs_su = units < a.fs_su ? units : a.fs_su;
       const int split = (units + a.fs_su - 1) / a.fs_su;
@@ -430,7 +461,7 @@ md_status md_workspace_layout(const md_params* p, int64_t n_atoms, int double_pr
   out->energy_partials = pl.off_epart;
   out->n_energy_partials =
       md::uses_compact(p, double_precision ? 8 : 4)
-          ? pl.n_cells * md::fs_units(p, pl, n_atoms)
+          ? md::fs_units(p, pl, n_atoms)
           : pl.n_tasks;
   out->z_split = pl.off_zsplit;
   out->total_bytes = pl.total;

@@ -33,19 +33,24 @@ __host__ __device__ inline int md_pair_drain(uint32_t flags) {
   return v == 0 ? 2 : v == 1 ? 1 : v == 2 ? 3 : 4;
 }
 
-// Work units of the compacted pair kernel per home cell. The neighbour list of a cell is
-// cut into `slices` equal slices (more where one would not fit the LDS), the cell's groups of
-// home atoms into `split` interleaved parts, and one workgroup takes a slice and a part.
+// Work units of the compacted pair kernel. The neighbour list of a home cell is cut into
+// `slices` equal slices (more where one would not fit the LDS), the cell's groups of home atoms
+// into `split` interleaved parts (`xsplit` in nx of the cells: the longest ones or the shortest
+// ones of the launch order), and one workgroup takes a slice and a part.
 // A home atom's partial force is rounded to fixed point once per slice, so the number of
 // slices depends on the grid and the atom count alone, never on the split that a caller
 // forces or on the batch a system runs in: those change which workgroup does the work and
 // not one bit of the result.
 struct FsWork {
-  int split;    // parts of the home atoms
-  int slices;   // slices of the neighbour list
+  int split;      // parts of a cell's home atoms
+  int slices;     // slices of its neighbour list
+  int64_t nx;     // cells with another split
+  int xsplit;     // theirs
+  int xlong;      // 1: they are the first (longest) of the launch order, 0: the last
 };
 constexpr int kFsMaxSplit = 8, kFsMaxSlices = 8;
-constexpr int kFsMaxCells = 256;   // larger grids: one workgroup per cell unless forced
+constexpr int kFsMaxCells = 256;     // larger grids: one workgroup for most cells unless forced
+constexpr int kFsMaxShared = 2048;   // still larger ones: for every cell
 FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bool half);
 
 struct WsHeader {
@@ -167,12 +172,19 @@ struct SysArgs {
                                //    or, float32 only, facc with MD_ACCUM_F32_ATOMIC)
   int half_shell;              // 1: the compacted kernel visits each pair once and adds
                                //    into acc64 with integer atomics (acc64 starts at zero)
-  int fs_split;                // parts of a home cell's atoms, one workgroup each (FsWork)
+  int64_t fs_nx;               // FsWork: cells of the other split, which ends of the launch
+  int fs_xlong, fs_xsplit;     // order, and that split
+  int fs_split;                // parts of the other cells' home atoms, a workgroup each
   int fs_slices;               // slices of its neighbour list, at least (FsWork)
-  int fs_su;                   // slices spread over workgroups: fs_split x fs_su workgroups
-                               // per home cell (fs_slices, or 1 in a batch that fills the
-                               // chip: then one workgroup takes the slices in turn)
+  int fs_su;                   // slices spread over workgroups (fs_slices, or fewer in a batch
+                               // that fills the chip: then a workgroup takes several in turn)
 };
+
+// Workgroups of the compacted kernel for one system.
+template <typename Real>
+__host__ __device__ inline int64_t fs_workgroups(const SysArgs<Real>& a) {
+  return ((a.n_cells - a.fs_nx) * a.fs_split + a.fs_nx * a.fs_xsplit) * a.fs_su;
+}
 
 // Up to kBatchMax systems evaluated by one launch of each kernel of the path. Their
 // arguments (about 350 bytes each) stand in device memory, in each system's workspace, put

@@ -102,7 +102,7 @@ __device__ inline void energy(const double* epart, int64_t n_tasks, double* out,
 
 template <typename Real>
 __host__ __device__ inline int64_t energy_parts(const SysArgs<Real>& a) {
-  return a.n > 0 ? (a.compact ? a.n_cells * a.fs_split * a.fs_su : a.n_tasks) : 0;
+  return a.n > 0 ? (a.compact ? fs_workgroups(a) : a.n_tasks) : 0;
 }
 
 template <typename Real>

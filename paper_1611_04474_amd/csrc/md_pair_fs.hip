@@ -383,6 +383,34 @@ __device__ inline void lds_store_u16_lanes4(uint32_t a0, uint32_t a1, uint32_t a
       : "memory", "scc");
 }
 
+// A workgroup's work: unit `unit` of the split x su of home cell `cell`; its energy goes to
+// partial `slot`.
+struct FsUnit {
+  int64_t cell, slot;
+  int unit, split, su;
+};
+
+// Workgroup b: units 0 of the cells with the usual split in launch order, their units 1, ...,
+// then those of the fs_nx others.
+template <typename Real>
+__device__ inline FsUnit fs_unit(const SysArgs<Real>& a, int64_t b) {
+  FsUnit f;
+  f.slot = b;
+  f.su = a.fs_su;
+  uint32_t u = (uint32_t)b, nt = (uint32_t)(a.n_cells - a.fs_nx), first = a.fs_xlong ? (uint32_t)a.fs_nx : 0u;
+  f.split = a.fs_split;
+  const uint32_t usual = nt * (uint32_t)(f.split * f.su);
+  if (u >= usual) {
+    u -= usual;
+    nt = (uint32_t)a.fs_nx;
+    first = a.fs_xlong ? 0u : (uint32_t)a.n_cells - nt;
+    f.split = a.fs_xsplit;
+  }
+  f.cell = a.order[first + u % nt];
+  f.unit = (int)(u / nt);
+  return f;
+}
+
 // The prefilter of a group of home atoms: |r_j - r_i|^2 < rc^2 + margin in the expanded form
 // c_j + (-2 a_i).r_j < thr_i, with the constants that the in-cell sort wrote (SysArgs::hpre); an
 // absent atom (past nv) has a = 0 and thr = -1, which c_j >= 0 never passes.
@@ -429,7 +457,7 @@ struct Pre {
 // kHalf: the half shell (64-bit fixed-point sums only). kDrain: force batches per drain.
 template <typename Real, bool kHalf, int kCoul, bool kClamp, bool kDiag, int kDrain>
 __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real>& a, int cap,
-                                                              int64_t cellA, int unit) {
+                                                              const FsUnit& fu) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
   constexpr bool kF32 = sizeof(Real) == 4;
   constexpr int kImg = kHalf ? 14 : 27;   // neighbour images
@@ -440,6 +468,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
   constexpr int kAW = kAccWords<Real>;
   using R4 = V4<Real>;
   using R2 = V2<Real>;
+  const int64_t cellA = fu.cell;
   const Lds LL = lds_layout<Real>(cap, a.n_types, kHalf, kDiag, kDrain);
   Hdr& H = *reinterpret_cast<Hdr*>(s_dyn + LL.hdr);
   uint16_t* sFifo = reinterpret_cast<uint16_t*>(s_dyn + LL.fifo);
@@ -576,13 +605,13 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
   const int iters = H.iters;
   const int n_grp_q = (nA + kQ - 1) / kQ;
   // this workgroup's share of the home cell: groups part, part + n_split, part + 2 n_split, ..
-  const int n_split = a.fs_split;
-  const int part = unit % n_split;
+  const int n_split = fu.split;
+  const int part = fu.unit % n_split;
   // the neighbour list in n_slice slices of H.len staged atoms (the last one shorter); this
-  // workgroup takes slices unit / n_split, + fs_su, ...
+  // workgroup takes slices unit / n_split, + su, ...
   const int n_slice = H.n_slice;
   // largest home-side partial of one slice (see kAccRange)
-  const float home_max = (kHalf ? kAccRange - 14.f * (float)a.fs_split * kNbrPartialMax : kAccRange) /
+  const float home_max = (kHalf ? kAccRange - 14.f * (float)max(a.fs_split, a.fs_xsplit) * kNbrPartialMax : kAccRange) /
                          (float)n_slice;
   const Real R = vsqrt(rc2) + Real(kWin);
   // energy: float32 in units of 2^-24 kcal/mol; float64 two-word (e_fix, e_lo): exact,
@@ -599,7 +628,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
   auto slice_len = [&]() __attribute__((always_inline)) {
     return __builtin_amdgcn_readfirstlane(H.len);
   };
-  for (int P0 = (unit / n_split) * slice_len(); P0 < total; P0 += a.fs_su * slice_len()) {
+  for (int P0 = (fu.unit / n_split) * slice_len(); P0 < total; P0 += fu.su * slice_len()) {
     const int P1 = min(total, P0 + slice_len());
     // stage the neighbour-list slice [P0, P1): wave w copies images w and w + 16 (both z
     // halves, to their two segments), issuing all loads of up to 4 x 64 atoms before the
@@ -1120,7 +1149,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
       }
       // the next slice clears the accumulators; after the last one nothing waits here, so
       // the workgroup can end while its atomics are still on their way
-      if (P0 + a.fs_su * slice_len() < total) __syncthreads();
+      if (P0 + fu.su * slice_len() < total) __syncthreads();
     }
   }
 
@@ -1153,7 +1182,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
     }
     last = __builtin_amdgcn_readfirstlane(__shfl(rank, 0)) == kNW - 1;
     if (last && lane == 0) {
-      const int64_t slot = unit * a.n_cells + cellA;
+      const int64_t slot = fu.slot;
       long long* ep = reinterpret_cast<long long*>(a.epart);
       if constexpr (kF32) {
         ep[slot] = __hip_atomic_load(&H.esum[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1171,7 +1200,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
     // candidates of Algorithm 1: every (home atom, other neighbour-list atom), counted
     // from both atoms in the full shell (halved after the kernel) and once in the half
     // shell; the neighbour slots this kernel actually filtered come separately
-    if (w == 0 && unit == 0) {
+    if (w == 0 && fu.unit == 0) {
       const unsigned long long nA_ = (unsigned long long)nA;
       const unsigned long long cand =
           kHalf ? nA_ * (nA_ - 1) / 2 + nA_ * (unsigned long long)(total - nA)
@@ -1195,11 +1224,17 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
 // to the header's two clock sums: their ratio is the clock the kernel ran at, weighted by
 // workgroup time. Called by lane 0 of the workgroup's last wave to finish.
 template <typename Real>
-__device__ inline void record_cost(const SysArgs<Real>& a, int64_t cell, int unit, uint64_t t0,
+__device__ inline void record_cost(const SysArgs<Real>& a, const FsUnit& fu, uint64_t t0,
                                    uint64_t c0, bool first) {
   const uint64_t dc = __builtin_amdgcn_s_memtime() - c0;
   const uint64_t dt = __builtin_amdgcn_s_memrealtime() - t0;
-  if (unit == 0) a.cost[cell] = dt < 0xffffffffull ? (uint32_t)dt : 0xffffffffu;
+  if (fu.unit == 0) {
+    // where cells' splits differ, about the whole cell's time: the parts' without the start and
+    // staging (12 us) that each of them repeats
+    const uint64_t parts = a.fs_nx > 0 ? (uint64_t)fu.split : 1;
+    const uint64_t whole = parts * dt > (parts - 1) * 1200 ? parts * dt - (parts - 1) * 1200 : dt;
+    a.cost[fu.cell] = whole < 0xffffffffull ? (uint32_t)whole : 0xffffffffu;
+  }
   atomicAdd(&a.hdr->clock[0], (unsigned long long)dc);
   atomicAdd(&a.hdr->clock[1], (unsigned long long)dt);
   if (first) {
@@ -1214,11 +1249,9 @@ void k_pair_fs(SysArgs<Real> a, int cap) {
   // home cells in the order the binning chose (longest first)
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   const uint64_t c0 = __builtin_amdgcn_s_memtime();
-  // workgroup b: cell order[b % n_cells], unit b / n_cells (every cell's first unit first)
-  const int64_t cell = a.order[blockIdx.x % a.n_cells];
-  const int unit = (int)(blockIdx.x / a.n_cells);
-  const bool last = pair_fs<Real, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, cell, unit);
-  if (last && (threadIdx.x & 63) == 0) record_cost(a, cell, unit, t0, c0, blockIdx.x == 0);
+  const FsUnit fu = fs_unit(a, blockIdx.x);
+  const bool last = pair_fs<Real, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, fu);
+  if (last && (threadIdx.x & 63) == 0) record_cost(a, fu, t0, c0, blockIdx.x == 0);
 }
 
 // One launch for a batch: block b is cell order[b - cum[s]] of system s.
@@ -1229,10 +1262,9 @@ void k_pair_fs_batch(Batch b, int cap) {
   const uint64_t c0 = __builtin_amdgcn_s_memtime();
   int64_t blk;
   const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
-  const int64_t cell = a.order[blk % a.n_cells];
-  const int unit = (int)(blk / a.n_cells);
-  const bool last = pair_fs<float, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, cell, unit);
-  if (last && (threadIdx.x & 63) == 0) record_cost(a, cell, unit, t0, c0, blk == 0);
+  const FsUnit fu = fs_unit(a, blk);
+  const bool last = pair_fs<float, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, fu);
+  if (last && (threadIdx.x & 63) == 0) record_cost(a, fu, t0, c0, blk == 0);
 }
 
 template <bool H, int S, bool C, bool D, int R>
@@ -1300,7 +1332,7 @@ hipError_t dispatch(const SysArgs<Real>& a, const Args& args, int n_types, int64
 template <typename Real>
 hipError_t launch_pair_fs(const SysArgs<Real>& a, hipStream_t stream) {
   if (a.n == 0) return hipSuccess;
-  return dispatch(a, a, a.n_types, a.n_cells * a.fs_split * a.fs_su, stream,
+  return dispatch(a, a, a.n_types, fs_workgroups(a), stream,
                   [](auto tag, dim3 g, dim3 b, size_t sh, hipStream_t st, const SysArgs<Real>& x,
                      int cap) {
                     using Tg = decltype(tag);
@@ -1316,9 +1348,7 @@ template hipError_t launch_pair_fs<double>(const SysArgs<double>&, hipStream_t);
 hipError_t launch_pair_fs_batch(Batch& b, const SysArgs<float>* sys, hipStream_t stream) {
   int nt = 1;
   for (int s = 0; s < b.n; ++s) nt = sys[s].n_types > nt ? sys[s].n_types : nt;
-  const int64_t nb = batch_blocks(b, sys, [](const SysArgs<float>& a) {
-    return a.n_cells * a.fs_split * a.fs_su;
-  });
+  const int64_t nb = batch_blocks(b, sys, [](const SysArgs<float>& a) { return fs_workgroups(a); });
   return dispatch(sys[0], b, nt, nb, stream,
                   [](auto tag, dim3 g, dim3 bl, size_t sh, hipStream_t st, const Batch& x,
                      int cap) {

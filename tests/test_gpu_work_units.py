@@ -26,10 +26,15 @@ def _system(n, box, seed):
     (65, (24.5, 40.0, 30.0)),     # lists about one 64-atom slice long
     (3000, (30.0, 30.0, 30.0)),   # 8 cells of more groups than one workgroup's waves
     (4001, (97.0, 97.0, 49.0)),   # 8 x 8 x 4 = 256 cells: the largest grid that is cut
-    (4001, (97.0, 97.0, 62.0)),   # 8 x 8 x 5 = 320 cells: one workgroup per cell
+    (4001, (97.0, 97.0, 62.0)),   # 8 x 8 x 5 = 320 cells: the shortest 64 in two parts
+    (4003, (73.5, 73.5, 61.5)),   # 180 cells: the longest 76 in two parts
+    (4003, (121.0, 97.0, 37.0)),  # 240 cells: the longest 16
+    (4003, (133.0, 97.0, 37.0)),  # 11 x 8 x 3 = 264 cells: the shortest 8 in six parts
+    (6007, (97.0, 97.0, 85.0)),   # 448 cells: the longest 64
+    (20000, (205.0, 193.0, 97.0)),  # 17 x 16 x 8 = 2176 cells: all whole
 ])
 def test_units_match_oracle(gpu, n, box, double):
-    """Slices of the neighbour list and parts of the home atoms, from one atom to 320 cells:
+    """Slices of the neighbour list and parts of the home atoms, from one atom to 2,176 cells:
     the oracle's forces, energy and partner counts, and the same bits however the home atoms
     are split."""
     print("case:", n, box, "double", double, flush=True)
@@ -37,7 +42,7 @@ def test_units_match_oracle(gpu, n, box, double):
     pos = s.pos.astype(np.float64) if double else s.pos
     q = s.charges.astype(np.float64) if double else s.charges
     f, e, ws, cnt = run(p, pos, s.types, q, gpu, double=double, flags=api.DIAG_COUNTERS)
-    r = oracle.forces(p, s.pos, s.types, s.charges, "bruteforce")
+    r = oracle.forces(p, s.pos, s.types, s.charges, "bruteforce" if n < 5000 else "celllist")
     err = force_errors(f, r.force, r.abs_sum)
     tol = 1e-12 if double else 1e-5
     assert err["max_norm"] <= tol and err["rms"] <= tol, err
