@@ -279,14 +279,26 @@ inline int64_t batch_blocks(Batch& b, const SysArgs<float>* sys, F per_sys) {
   return b.cum[b.n];
 }
 
-// Velocity-Verlet kernels of md_run_vv_f32 (md_integrate.hip). kick_drift: v += h F/m,
-// x += dt v wrapped into [0, L). kick: v += h F/m, and the kinetic energy, from per-block
-// partials in kpart ([ke_blocks(n)] doubles) summed in a fixed order into *ke.
-int64_t ke_blocks(int64_t n);
+// Velocity-Verlet steps of md_run_vv_f32 (md_integrate.hip, md_finalize.hip). kick_drift: v += h
+// F/m, x += dt v wrapped into [0, L). finalize_vv: the force path's last kernel with the step's
+// second kick and, with drift set, the next step's kick and drift; vv_update: the two kicks and
+// the drift alone. The kinetic energies go to per-block partials kpart ([ke_blocks(n)] doubles),
+// which the next step's launch (as kpart_prev) or ke_sum sums in a fixed order.
+struct VvArgs {
+  float *pos, *vel;            // [n][3]
+  const float* inv_mass;       // [n]
+  float h, dt, L[3];
+  int drift;
+  double* kpart;
+  const double* kpart_prev;
+  double* ke_prev;             // null: no previous step
+};
+__host__ __device__ inline int64_t ke_blocks(int64_t n) { return n > 0 ? (n + 255) / 256 : 1; }
 hipError_t launch_vv_kick_drift(int64_t n, float* pos, float* vel, const float* force,
                                 const float* inv_mass, float h, float dt, const float* L,
                                 hipStream_t stream);
-hipError_t launch_vv_kick(int64_t n, float* vel, const float* force, const float* inv_mass,
-                          float h, double* kpart, double* ke, hipStream_t stream);
+hipError_t launch_finalize_vv(const SysArgs<float>& a, const VvArgs& v, hipStream_t stream);
+hipError_t launch_vv_update(int64_t n, const float* force, const VvArgs& v, hipStream_t stream);
+hipError_t launch_ke_sum(int64_t n, const double* kpart, double* ke, hipStream_t stream);
 
 }  // namespace md
