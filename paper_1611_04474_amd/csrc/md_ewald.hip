@@ -18,16 +18,18 @@
 // fixed-point fraction u, so m u (mod 2^32) is the phase of wave number m with no rounding,
 // and only the final sine and cosine round. Wave vectors are grouped in rows (mx, my), each
 // row holding every mz; the kernels are
-//   k_ew_setup    per atom: fractions u, charge, NaN check, partial sums of q^2 and q;
-//   k_ew_tables   per atom and wave number: exp(2 pi i m u) per axis, float2 [m][atom];
-//   k_ew_sf       structure factors: a wave per row, a lane per mz, atoms of a chunk in
-//                 LDS tiles of 64 (W = q X Y per (row, atom), Z per (atom, mz)); per-chunk
-//                 partial sums;
-//   k_ew_g        per wave vector: the chunks' partials summed in a fixed order (float64),
-//                 w(kv), the energy term and G; per-row energy partials;
-//   k_ew_force    a thread per atom: its Z factors in registers, per row one sine/cosine
-//                 of the exact (mx, my) phase and a complex dot product of G and Z over mz;
-//   k_ew_energy   one workgroup: fixed-order sum of the row energies, self and background.
+//   k_ew_prepare  per atom: fractions u, charge, NaN check, partial sums of q^2 and q; and per
+//                 atom and wave number exp(2 pi i m u) per axis, float2 [m][atom];
+//   k_ew_sf       structure factors as a complex matrix product over atoms on the matrix cores
+//                 (W = q X Y per (row, atom), Z per (atom, mz)); per-chunk partial sums;
+//   k_ew_g        G from the chunks' partials (float64, eight loads in flight), row energies;
+//   k_ew_force    per 64 atoms and a share of the rows: T = Z G over mz on the matrix cores and
+//                 one sine/cosine of the exact (mx, my) phase per atom and row;
+//   k_ew_final    the shares of an atom's force added; fixed-order sum of the row energies, self
+//                 and background, and the status word.
+// Systems that come here are small (larger ones take the grid), so launches and idle compute
+// units count: 3,000 atoms and 6,095 wave vectors took seven launches, 47 workgroups for the
+// forces and 47 dependent loads per wave vector, 89 us; 41 this way, the same bits.
 // Every sum runs in a fixed order, so the results are the same bits on every run.
 #include <math.h>
 
@@ -54,9 +56,12 @@ struct EwArgs {
   float2* tab;                    // [(kx+1) + (2ky+1) + (2kz+1)][n]: X, then Y, then Z
   float2* parts;                  // [chunks][R][nzc] partial structure factors
   float2* g;                      // [R][nzc_pad] G (zero where excluded and in the padding)
+  double* fpart;                  // [splits][n][3] shares of the forces (splits > 1)
+  uint32_t* stat;                 // [qblocks] status bits
   double* erow;                   // [R][zblocks] energy partials
   double2* qpart;                 // [qblocks] (sum q^2, sum q) per setup block
   int kx, ky, kz, nzc, nzc_pad, zblocks;
+  int splits, split_rows;         // shares of the rows in k_ew_force, rows (of 16) in each
   int64_t rows, chunks, chunk_atoms, qblocks;
   double L[3];
   double alpha, coulomb_k;
@@ -85,50 +90,55 @@ __device__ inline float2 ew_phase(uint32_t ph) {
   return make_float2(c, s);
 }
 
-__global__ __launch_bounds__(256) void k_ew_setup(EwArgs a) {
-  __shared__ double sq2[256], sq[256];
+// Table row t = blockIdx.y: X (mx = 0..kx), Y (my = -ky..ky), Z (mz = -kz..kz), each [m][atom];
+// the blocks of row 0 also write the atoms' fractions and partial sums.
+__global__ __launch_bounds__(256) void k_ew_prepare(EwArgs a) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  double q2 = 0.0, q1 = 0.0;
-  if (i < a.n) {
-    uint32_t st = 0;
-    a.ups[i] = ew_fractions(a.pos, a.q, a.L, i, st);
-    const float qi = __uint_as_float(a.ups[i].w);
-    q2 = (double)qi * (double)qi;
-    q1 = (double)qi;
-    if (st) atomicOr(&a.hdr->status, st);
-  }
-  sq2[threadIdx.x] = q2;
-  sq[threadIdx.x] = q1;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      sq2[threadIdx.x] += sq2[threadIdx.x + off];
-      sq[threadIdx.x] += sq[threadIdx.x + off];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.qpart[blockIdx.x] = make_double2(sq2[0], sq[0]);
-}
-
-// Table row t: X (mx = 0..kx), Y (my = -ky..ky), Z (mz = -kz..kz), each [m][atom].
-__global__ __launch_bounds__(256) void k_ew_tables(EwArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.n) return;
   const int t = blockIdx.y;
-  const uint4 u = a.ups[i];
-  int m;
-  uint32_t ua;
-  if (t <= a.kx) {
-    m = t;
-    ua = u.x;
-  } else if (t <= a.kx + 2 * a.ky + 1) {
-    m = t - (a.kx + 1) - a.ky;
-    ua = u.y;
-  } else {
-    m = t - (a.kx + 2 * a.ky + 2) - a.kz;
-    ua = u.z;
+  if (i < a.n) {
+    int m, d;
+    if (t <= a.kx) {
+      m = t;
+      d = 0;
+    } else if (t <= a.kx + 2 * a.ky + 1) {
+      m = t - (a.kx + 1) - a.ky;
+      d = 1;
+    } else {
+      m = t - (a.kx + 2 * a.ky + 2) - a.kz;
+      d = 2;
+    }
+    uint32_t st = 0;
+    a.tab[(int64_t)t * a.n + i] = ew_phase((uint32_t)m * ew_fraction(a.pos[3 * i + d], a.L[d], st));
   }
-  a.tab[(int64_t)t * a.n + i] = ew_phase((uint32_t)m * ua);
+  if (t > 0) return;
+  double q2 = 0.0, q1 = 0.0;
+  uint32_t st = 0;
+  if (i < a.n) {
+    const uint4 u = ew_fractions(a.pos, a.q, a.L, i, st);
+    a.ups[i] = u;
+    const double qi = (double)__uint_as_float(u.w);
+    q2 = qi * qi;
+    q1 = qi;
+  }
+  __shared__ double s_q2[4], s_q1[4];
+  __shared__ uint32_t s_st[4];
+  for (int off = 32; off > 0; off >>= 1) {
+    q2 += __shfl_xor(q2, off);
+    q1 += __shfl_xor(q1, off);
+    st |= __shfl_xor(st, off);
+  }
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    s_q2[w] = q2;
+    s_q1[w] = q1;
+    s_st[w] = st;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a.qpart[blockIdx.x] = make_double2((s_q2[0] + s_q2[1]) + (s_q2[2] + s_q2[3]),
+                                       (s_q1[0] + s_q1[1]) + (s_q1[2] + s_q1[3]));
+    a.stat[blockIdx.x] = s_st[0] | s_st[1] | s_st[2] | s_st[3];
+  }
 }
 
 // Structure factors as a complex matrix product over atoms, on the matrix cores:
@@ -223,44 +233,52 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
   }
 }
 
-// Per wave vector: S from the chunks (fixed order, float64), the energy term and G.
-__global__ __launch_bounds__(64) void k_ew_g(EwArgs a) {
-  __shared__ double se[64];
-  const int64_t r = blockIdx.x;
-  const int zi = blockIdx.y * 64 + threadIdx.x;
+// G of wave vector (row r, mz index zi) from the chunks' partials (fixed order, float64), zero
+// outside the half space kv != 0; e gets its energy term.
+__device__ inline float2 ew_g(const EwArgs& a, int64_t r, int zi, double& e) {
+  e = 0.0;
+  if (r >= a.rows || zi >= a.nzc) return make_float2(0.f, 0.f);
   int mx, my;
   ew_row(a, r, mx, my);
-  double e = 0.0;
-  float2 gv = make_float2(0.f, 0.f);
-  if (zi < a.nzc) {
-    const int mz = zi - a.kz;
-    const bool use = mx > 0 || my > 0 || mz > 0;   // half space, kv != 0
-    if (use) {
-      double sr = 0.0, si = 0.0;
-      for (int64_t c = 0; c < a.chunks; ++c) {
-        const float2 p = a.parts[(c * a.rows + r) * a.nzc + zi];
-        sr += (double)p.x;
-        si += (double)p.y;
+  const int mz = zi - a.kz;
+  if (!(mx > 0 || my > 0 || mz > 0)) return make_float2(0.f, 0.f);
+  double sr = 0.0, si = 0.0;
+  const float2* p = a.parts + r * a.nzc + zi;
+  const int64_t step = a.rows * a.nzc;
+  for (int64_t c = 0; c < a.chunks; c += 8) {
+    float2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = p[(c + u < a.chunks ? c + u : a.chunks - 1) * step];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (c + u < a.chunks) {
+        sr += (double)v[u].x;
+        si += (double)v[u].y;
       }
-      const double pi = 3.141592653589793;
-      const double kx = 2.0 * pi * mx / a.L[0], ky = 2.0 * pi * my / a.L[1],
-                   kz = 2.0 * pi * mz / a.L[2];
-      const double k2 = kx * kx + ky * ky + kz * kz;
-      const double wk = exp(-k2 / (4.0 * a.alpha * a.alpha)) / k2;
-      const double V = a.L[0] * a.L[1] * a.L[2];
-      e = 4.0 * pi * a.coulomb_k / V * wk * (sr * sr + si * si);
-      const double gs = 8.0 * pi * a.coulomb_k / V * wk;
-      gv = make_float2((float)(gs * sr), (float)(-gs * si));   // (8 pi k / V) w conj(S)
     }
   }
-  if (zi < a.nzc_pad) a.g[r * a.nzc_pad + zi] = gv;
-  se[threadIdx.x] = e;
-  __syncthreads();
-  for (int off = 32; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) se[threadIdx.x] += se[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.erow[r * a.zblocks + blockIdx.y] = se[0];
+  const double pi = 3.141592653589793;
+  const double kx = 2.0 * pi * mx / a.L[0], ky = 2.0 * pi * my / a.L[1],
+               kz = 2.0 * pi * mz / a.L[2];
+  const double k2 = kx * kx + ky * ky + kz * kz;
+  const double wk = exp(-k2 / (4.0 * a.alpha * a.alpha)) / k2;
+  const double V = a.L[0] * a.L[1] * a.L[2];
+  e = 4.0 * pi * a.coulomb_k / V * wk * (sr * sr + si * si);
+  const double gs = 8.0 * pi * a.coulomb_k / V * wk;
+  return make_float2((float)(gs * sr), (float)(-gs * si));   // (8 pi k / V) w conj(S)
+}
+
+// G, and the rows' energies: a wave per row and 64 values of mz.
+__global__ __launch_bounds__(256) void k_ew_g(EwArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= a.rows) return;
+  const int zi = blockIdx.y * 64 + lane;
+  double e;
+  const float2 g = ew_g(a, r, zi, e);
+  if (zi < a.nzc_pad) a.g[r * a.nzc_pad + zi] = g;
+  for (int off = 32; off > 0; off >>= 1) e += __shfl_xor(e, off);
+  if (lane == 0) a.erow[r * a.zblocks + blockIdx.y] = e;
 }
 
 // Forces as complex matrix products over mz, on the matrix cores: for atoms i and rows
@@ -272,6 +290,16 @@ __global__ __launch_bounds__(64) void k_ew_g(EwArgs a) {
 // v_mfma_f32_16x16x4f32 (T and U, re and im parts). A lane then holds 4 atoms x 1 row of T
 // and U: it adds that row's force terms for its 4 atoms in float32 and each tile's sums into
 // float64; the 16 lanes of a row group finally add their sums in a fixed butterfly.
+__device__ inline void ew_put_force(const EwArgs& a, int64_t i, const double (&F)[3]) {
+  const double qi = (double)__uint_as_float(a.ups[i].w);
+  float* out = a.force + 3 * i;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const float v = (float)(qi * F[d]);
+    out[d] = a.accumulate ? out[d] + v : v;
+  }
+}
+
 __global__ __launch_bounds__(256) void k_ew_force(EwArgs a) {
   __shared__ float2 sG[16][kEwZ + 1];   // [row][mz] of the current tile and mz chunk
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
@@ -291,6 +319,8 @@ __global__ __launch_bounds__(256) void k_ew_force(EwArgs a) {
   const float kxs = (float)(2.0 * pi / a.L[0]), kys = (float)(2.0 * pi / a.L[1]),
               kzs = (float)(2.0 * pi / a.L[2]);
   double F[4][3] = {};
+  const int64_t row0 = (int64_t)blockIdx.y * a.split_rows,
+                row1 = row0 + a.split_rows < a.rows ? row0 + a.split_rows : a.rows;
   const float2* Zt = a.tab + (int64_t)(a.kx + 2 * a.ky + 2) * a.n;
   for (int zc = 0; zc < a.nzc_pad; zc += kEwZ) {
     // A operands for this mz chunk: step s holds Z[zc + 4 s + kk][ia]; ns steps cover the
@@ -302,12 +332,11 @@ __global__ __launch_bounds__(256) void k_ew_force(EwArgs a) {
       const int zi = zc + 4 * s + kk;
       z[s] = (aok && zi < a.nzc) ? Zt[(int64_t)zi * a.n + ia] : make_float2(0.f, 0.f);
     }
-    for (int64_t r0 = 0; r0 < a.rows; r0 += 16) {
+    for (int64_t r0 = row0; r0 < row1; r0 += 16) {
       __syncthreads();
-      for (int e = t; e < 16 * kEwZ; e += 256) {
-        const int rr = e / kEwZ, k = e % kEwZ;
-        sG[rr][k] = r0 + rr < a.rows ? a.g[(r0 + rr) * a.nzc_pad + zc + k] : make_float2(0.f, 0.f);
-      }
+#pragma unroll
+      for (int rr = w; rr < 16; rr += 4)   // a wave per row
+        sG[rr][lane] = r0 + rr < a.rows ? a.g[(r0 + rr) * a.nzc_pad + zc + lane] : make_float2(0.f, 0.f);
       __syncthreads();
       ew_v4f tre = {0.f, 0.f, 0.f, 0.f}, tim = tre, ure = tre, uim = tre;
 #pragma unroll
@@ -353,27 +382,44 @@ __global__ __launch_bounds__(256) void k_ew_force(EwArgs a) {
     for (int i = 0; i < 4; ++i) {
       const int64_t id = (int64_t)blockIdx.x * 64 + 16 * w + 4 * kk + i;
       if (id >= a.n) continue;
-      const float qi = __uint_as_float(a.ups[id].w);
-      float* out = a.force + 3 * id;
-      for (int d = 0; d < 3; ++d) {
-        const float v = (float)((double)qi * F[i][d]);
-        out[d] = a.accumulate ? out[d] + v : v;
+      if (a.splits > 1) {
+        double* out = a.fpart + 3 * ((int64_t)blockIdx.y * a.n + id);
+        for (int d = 0; d < 3; ++d) out[d] = F[i][d];
+      } else {
+        ew_put_force(a, id, F[i]);
       }
     }
   }
 }
 
-// Energy: row partials, then self and background terms, in a fixed order.
-__global__ __launch_bounds__(256) void k_ew_energy(EwArgs a) {
-  ew_energy_sum(a.erow, a.rows * a.zblocks, a.qpart, a.qblocks, a.L, a.alpha, a.coulomb_k, a.energy);
+// Block 0: the energy (row partials, then self and background terms) and the status word;
+// blocks 1 ..: the shares of each atom's force added in a fixed order.
+__global__ __launch_bounds__(256) void k_ew_final(EwArgs a) {
+  if (blockIdx.x == 0) {
+    __shared__ uint32_t s_st;
+    if (threadIdx.x == 0) s_st = 0;
+    __syncthreads();
+    uint32_t st = 0;
+    for (int64_t b = threadIdx.x; b < a.qblocks; b += 256) st |= a.stat[b];
+    if (st) atomicOr(&s_st, st);
+    ew_energy_sum(a.erow, a.rows * a.zblocks, a.qpart, a.qblocks, a.L, a.alpha, a.coulomb_k, a.energy);
+    if (threadIdx.x == 0) a.hdr->status = s_st;   // past the sum's barriers
+    return;
+  }
+  const int64_t i = ((int64_t)blockIdx.x - 1) * 256 + threadIdx.x;
+  if (i >= a.n) return;
+  double F[3] = {};
+  for (int c = 0; c < a.splits; ++c)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) F[d] += a.fpart[3 * ((int64_t)c * a.n + i) + d];
+  ew_put_force(a, i, F);
 }
-
-__global__ void k_ew_clear_status(WsHeader* hdr) { hdr->status = 0; }
 
 struct EwPlan {
   int kx, ky, kz, nzc, nzc_pad, zblocks;
+  int splits, split_rows;
   int64_t rows, chunks, chunk_atoms, qblocks;
-  size_t off_ups, off_tab, off_parts, off_g, off_erow, off_qpart, total;
+  size_t off_ups, off_tab, off_parts, off_g, off_fpart, off_erow, off_qpart, off_stat, total;
 };
 
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -392,7 +438,7 @@ md_status ew_plan(const md_params* p, int64_t n, const int32_t kmax[3], EwPlan* 
   pl->kz = kmax[2];
   pl->nzc = 2 * pl->kz + 1;
   pl->nzc_pad = (pl->nzc + kEwZ - 1) / kEwZ * kEwZ;
-  pl->zblocks = (pl->nzc_pad + 63) / 64;   // covers the padding of G, which k_ew_g zeroes
+  pl->zblocks = (pl->nzc_pad + 63) / 64;
   pl->rows = ew_rows(pl->kx, pl->ky);
   // atom chunks: enough workgroups to fill the chip, chunks of whole tiles
   const int64_t rb = (pl->rows + kEwRows - 1) / kEwRows;
@@ -402,6 +448,12 @@ md_status ew_plan(const md_params* p, int64_t n, const int32_t kmax[3], EwPlan* 
   pl->chunk_atoms = (tiles + chunks - 1) / chunks * kEwTile;
   pl->chunks = n > 0 ? (n + pl->chunk_atoms - 1) / pl->chunk_atoms : 1;
   pl->qblocks = (n + 255) / 256 > 0 ? (n + 255) / 256 : 1;
+  // shares of the rows in the force kernel: about two workgroups per compute unit
+  const int64_t at = (n + 63) / 64 > 0 ? (n + 63) / 64 : 1, rt = (pl->rows + 15) / 16;
+  int64_t splits = (512 + at - 1) / at;
+  splits = splits > rt ? rt : splits;
+  pl->split_rows = (int)((rt + splits - 1) / splits * 16);
+  pl->splits = (int)((pl->rows + pl->split_rows - 1) / pl->split_rows);
   const size_t nn = (size_t)(n > 0 ? n : 1);
   const int64_t trows = (pl->kx + 1) + (2 * pl->ky + 1) + pl->nzc;
   size_t o = a256(sizeof(WsHeader));
@@ -409,8 +461,10 @@ md_status ew_plan(const md_params* p, int64_t n, const int32_t kmax[3], EwPlan* 
   pl->off_tab = o;   o = a256(o + sizeof(float2) * (size_t)trows * nn);
   pl->off_parts = o; o = a256(o + sizeof(float2) * (size_t)pl->chunks * pl->rows * pl->nzc);
   pl->off_g = o;     o = a256(o + sizeof(float2) * (size_t)pl->rows * pl->nzc_pad);
+  pl->off_fpart = o; o = a256(o + (pl->splits > 1 ? sizeof(double) * 3 * (size_t)pl->splits * nn : 0));
   pl->off_erow = o;  o = a256(o + sizeof(double) * (size_t)pl->rows * pl->zblocks);
   pl->off_qpart = o; o = a256(o + sizeof(double2) * (size_t)pl->qblocks);
+  pl->off_stat = o;  o = a256(o + sizeof(uint32_t) * (size_t)pl->qblocks);
   pl->total = o;
   return MD_OK;
 }
@@ -461,6 +515,10 @@ md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d
   a.tab = (float2*)(b + pl.off_tab);
   a.parts = (float2*)(b + pl.off_parts);
   a.g = (float2*)(b + pl.off_g);
+  a.fpart = (double*)(b + pl.off_fpart);
+  a.stat = (uint32_t*)(b + pl.off_stat);
+  a.splits = pl.splits;
+  a.split_rows = pl.split_rows;
   a.erow = (double*)(b + pl.off_erow);
   a.qpart = (double2*)(b + pl.off_qpart);
   a.kx = pl.kx;
@@ -477,24 +535,26 @@ md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d
   a.alpha = p->ewald_alpha;
   a.coulomb_k = p->coulomb_k;
   hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(md::k_ew_clear_status, dim3(1), dim3(1), 0, st, a.hdr);
+  unsigned final_blocks = 1;
   if (n_atoms > 0) {
     const unsigned nb = (unsigned)((n_atoms + 255) / 256);
     const unsigned trows = (unsigned)((pl.kx + 1) + (2 * pl.ky + 1) + pl.nzc);
-    hipLaunchKernelGGL(md::k_ew_setup, dim3(nb), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(md::k_ew_tables, dim3(nb, trows), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(md::k_ew_prepare, dim3(nb, trows), dim3(256), 0, st, a);
     hipLaunchKernelGGL(md::k_ew_sf,
                        dim3((unsigned)((pl.rows + md::kEwRows - 1) / md::kEwRows),
                             (unsigned)pl.chunks, (unsigned)pl.zblocks),
                        dim3(1024), 0, st, a);
-    hipLaunchKernelGGL(md::k_ew_g, dim3((unsigned)pl.rows, (unsigned)pl.zblocks), dim3(64), 0, st, a);
-    hipLaunchKernelGGL(md::k_ew_force, dim3((unsigned)((n_atoms + 63) / 64)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(md::k_ew_g, dim3((unsigned)((pl.rows + 3) / 4), (unsigned)pl.zblocks), dim3(256), 0,
+                       st, a);
+    hipLaunchKernelGGL(md::k_ew_force, dim3((unsigned)((n_atoms + 63) / 64), (unsigned)pl.splits),
+                       dim3(256), 0, st, a);
+    if (pl.splits > 1) final_blocks += nb;
   } else {
     // no atoms: every term is zero
     a.qblocks = 0;
     a.rows = 0;
   }
-  hipLaunchKernelGGL(md::k_ew_energy, dim3(1), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(md::k_ew_final, dim3(final_blocks), dim3(256), 0, st, a);
   return hipGetLastError() == hipSuccess ? MD_OK : MD_ERR_HIP;
 }
 

@@ -5,25 +5,29 @@
 
 namespace md {
 
-// Atom i's fractions of the box edges as 32-bit fixed point and its charge's bits; st gets
-// MD_STATUS_NAN for a NaN.
+// x as a fraction of the box edge L, 32-bit fixed point; st gets MD_STATUS_NAN for a NaN.
+__device__ inline uint32_t ew_fraction(float xf, double L, uint32_t& st) {
+  const double x = (double)xf;
+  if (x != x) {
+    st |= MD_STATUS_NAN;
+    return 0;
+  }
+  const double s = x / L;
+  const double f = s - floor(s);                                     // [0, 1)
+  return (uint32_t)(unsigned long long)llrint(f * 4294967296.0);     // 2^32 wraps to 0
+}
+
+// Atom i's fractions and its charge's bits.
 __device__ inline uint4 ew_fractions(const float* pos, const float* q, const double* L, int64_t i,
                                      uint32_t& st) {
-  uint32_t u[3];
-  for (int d = 0; d < 3; ++d) {
-    const double x = (double)pos[3 * i + d];
-    if (x != x) {
-      st |= MD_STATUS_NAN;
-      u[d] = 0;
-      continue;
-    }
-    const double s = x / L[d];
-    const double f = s - floor(s);                                     // [0, 1)
-    u[d] = (uint32_t)(unsigned long long)llrint(f * 4294967296.0);     // 2^32 wraps to 0
-  }
+  uint4 u;
+  u.x = ew_fraction(pos[3 * i + 0], L[0], st);
+  u.y = ew_fraction(pos[3 * i + 1], L[1], st);
+  u.z = ew_fraction(pos[3 * i + 2], L[2], st);
   const float qi = q[i];
   if (qi != qi) st |= MD_STATUS_NAN;
-  return make_uint4(u[0], u[1], u[2], __float_as_uint(qi));
+  u.w = __float_as_uint(qi);
+  return u;
 }
 
 // One workgroup of 256: energy partials, then self and background terms, in a fixed order.
