@@ -82,7 +82,8 @@ struct EwMeshArgs {
   WsHeader* hdr;
   uint4* ups;          // [n] fractions and charge, caller order
   uint4* rec;          // [n] the same by bin, in index order within a bin
-  float *win, *dwin;   // [n][32] by bin: window values and derivatives, 10 per axis, x, y, z
+  float *win, *dwin;   // [n][32] by bin: window values and derivatives, 10 per axis, x
+                       // (times the charge), y, z
   int2* slot;          // [n] bin and place in it
   int* ids;            // [n] indices by bin
   int* sid;            // [n] indices by bin, in order
@@ -96,7 +97,7 @@ struct EwMeshArgs {
   int64_t nepart, qblocks, nbins;
   int M[3], N[3], K[3], nt[3];
   double cb[3];        // the windows' shape: beta log2(e)
-  double L[3], alpha, coulomb_k, gscale;
+  double L[3], mL[3], alpha, coulomb_k, gscale;   // mL = M / L
 };
 
 // Fills the plan; true if the grid form takes the system (direct_bytes: the direct sum's

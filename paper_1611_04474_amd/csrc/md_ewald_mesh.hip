@@ -134,31 +134,34 @@ __global__ __launch_bounds__(256) void k_em_init(EwMeshArgs a, unsigned nb_tab) 
 }
 
 __global__ __launch_bounds__(256) void k_em_setup(EwMeshArgs a) {
-  __shared__ double sq2[256], sq[256];
+  __shared__ double s_q2[4], s_q1[4];
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   double q2 = 0.0, q1 = 0.0;
+  int b = 0, at = 0;
   if (i < a.n) {
     uint32_t st = 0;
     const uint4 u = ew_fractions(a.pos, a.q, a.L, i, st);
+    b = bin_of(a, u);
+    at = atomicAdd(&a.count[b], 1);   // on its way during the sums below
     a.ups[i] = u;
-    const float qi = __uint_as_float(u.w);
-    q2 = (double)qi * (double)qi;
-    q1 = (double)qi;
+    const double qi = (double)__uint_as_float(u.w);
+    q2 = qi * qi;
+    q1 = qi;
     if (st) atomicOr(&a.hdr->status, st);
-    const int b = bin_of(a, u);
-    a.slot[i] = make_int2(b, atomicAdd(&a.count[b], 1));
   }
-  sq2[threadIdx.x] = q2;
-  sq[threadIdx.x] = q1;
+  for (int off = 32; off > 0; off >>= 1) {
+    q2 += __shfl_xor(q2, off);
+    q1 += __shfl_xor(q1, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s_q2[threadIdx.x >> 6] = q2;
+    s_q1[threadIdx.x >> 6] = q1;
+  }
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      sq2[threadIdx.x] += sq2[threadIdx.x + off];
-      sq[threadIdx.x] += sq[threadIdx.x + off];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.qpart[blockIdx.x] = make_double2(sq2[0], sq[0]);
+  if (threadIdx.x == 0)
+    a.qpart[blockIdx.x] = make_double2((s_q2[0] + s_q2[1]) + (s_q2[2] + s_q2[3]),
+                                       (s_q1[0] + s_q1[1]) + (s_q1[2] + s_q1[3]));
+  if (i < a.n) a.slot[i] = make_int2(b, at);
 }
 
 // Exclusive scan of the bin counts, one workgroup, 4 bins per thread and round.
@@ -208,184 +211,180 @@ __global__ __launch_bounds__(256) void k_em_scatter(EwMeshArgs a) {
   a.ids[a.start[s.x] + s.y] = (int)i;
 }
 
-// One wave per bin: its atoms in index order, so that the spreading adds in a fixed order.
+// One workgroup per bin: its atoms in index order, so that the spreading adds in a fixed order.
 // Up to kRankMax members rank by counting smaller indices; a fuller bin marks them in a bit
 // map of kMapBits consecutive indices at a time and lists the marked ones. Then the atoms'
-// window values and derivatives, 10 per axis, half a wave per atom: the spreading, which meets
-// an atom in about 7 tiles, and the forces read them back.
-// LDS operations of a wave complete in order; the fence keeps the compiler to it as well.
-__device__ inline void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
-__device__ inline void put_windows(const EwMeshArgs& a, int s, int m, const uint4* rec) {
-  const int lane = threadIdx.x & 63, c = lane & 31, d = min(c / kW, 2), k = c % kW;
+// window values and derivatives, 10 per axis, half a wave per atom, those of x times the charge:
+// the spreading, which meets an atom in about 7 tiles, and the forces read them back.
+constexpr int kRankMax = 256, kMapBits = 32768;
+__global__ __launch_bounds__(256) void k_em_sort(EwMeshArgs a) {
+  __shared__ uint32_t s_map[kMapBits / 32];
+  __shared__ uint4 s_rec[kRankMax];
+  __shared__ int s_w[4];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t b = blockIdx.x;
+  const int s = a.start[b], m = a.start[b + 1] - s;
+  if (m == 0) return;
+  const bool small = m <= kRankMax;
+  if (small) {
+    const int id = t < m ? a.ids[s + t] : 0x7fffffff;
+    const uint4 u = t < m ? a.ups[id] : make_uint4(0, 0, 0, 0);
+    s_map[t] = (uint32_t)id;
+    __syncthreads();
+    int rank = 0;
+    if (t < m)
+      for (int j = 0; j < m; ++j) rank += (int)s_map[j] < id ? 1 : 0;
+    if (t < m) {
+      a.rec[s + rank] = u;
+      s_rec[rank] = u;
+      a.sid[s + rank] = id;
+    }
+  } else {
+    int out = s;
+    for (int64_t i0 = 0; i0 < a.n; i0 += kMapBits) {
+      for (int e = t; e < kMapBits / 32; e += 256) s_map[e] = 0;
+      __syncthreads();
+      for (int e = t; e < m; e += 256) {
+        const int64_t r = (int64_t)a.ids[s + e] - i0;
+        if (r >= 0 && r < kMapBits) atomicOr(&s_map[r >> 5], 1u << (r & 31));
+      }
+      __syncthreads();
+      for (int e0 = 0; e0 < kMapBits / 32; e0 += 256) {
+        uint32_t v = s_map[e0 + t];
+        const int c = __builtin_popcount(v);
+        int inc = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int y = __shfl_up(inc, o);
+          if (lane >= o) inc += y;
+        }
+        if (lane == 63) s_w[w] = inc;
+        __syncthreads();
+        int p = out + inc - c;
+        for (int k = 0; k < 4; ++k) {
+          p += k < w ? s_w[k] : 0;
+          out += s_w[k];
+        }
+        while (v) {
+          const int i = (int)(i0 + 32 * (e0 + t) + __builtin_ctz(v));
+          a.rec[p] = a.ups[i];
+          a.sid[p] = i;
+          ++p;
+          v &= v - 1;
+        }
+        __syncthreads();   // s_w and the map are used again
+      }
+    }
+    __threadfence_block();   // the records are read back
+  }
+  __syncthreads();
+  const int c = lane & 31, d = min(c / kW, 2), k = c % kW;
   const double cb = a.cb[d];
   const int M = a.M[d];
-  for (int e = lane >> 5; e < m; e += 2) {
-    const uint4 u = rec[e];
+  for (int e = t >> 5; e < m; e += 8) {
+    const uint4 u = small ? s_rec[e] : a.rec[s + e];
     uint32_t f;
     grid_cell(d == 0 ? u.x : d == 1 ? u.y : u.z, M, f);
     float dw;
-    const float w = window(k - kLo, f, cb, dw);
+    float v = window(k - kLo, f, cb, dw);
+    if (d == 0) {
+      v *= __uint_as_float(u.w);
+      dw *= __uint_as_float(u.w);
+    }
     if (c < 3 * kW) {
-      a.win[(int64_t)(s + e) * 32 + c] = w;
+      a.win[(int64_t)(s + e) * 32 + c] = v;
       a.dwin[(int64_t)(s + e) * 32 + c] = dw;
     }
   }
 }
 
-constexpr int kRankMax = 256, kMapBits = 32768;
-__global__ __launch_bounds__(256) void k_em_sort(EwMeshArgs a) {
-  __shared__ uint32_t s_map[4][kMapBits / 32];
-  __shared__ uint4 s_rec[4][kRankMax];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t b = (int64_t)blockIdx.x * 4 + w;
-  if (b >= a.nbins) return;
-  const int s = a.start[b], m = a.start[b + 1] - s;
-  uint32_t* map = s_map[w];
-  if (m <= kRankMax) {
-    int id[kRankMax / 64], r[kRankMax / 64];
-#pragma unroll
-    for (int k = 0; k < kRankMax / 64; ++k) {
-      const int e = lane + 64 * k;
-      id[k] = e < m ? a.ids[s + e] : 0x7fffffff;
-      r[k] = 0;
-      map[e] = (uint32_t)id[k];
-    }
-    wave_lds_fence();
-    for (int j = 0; j < m; ++j) {
-      const int x = (int)map[j];
-#pragma unroll
-      for (int k = 0; k < kRankMax / 64; ++k) r[k] += x < id[k] ? 1 : 0;
-    }
-#pragma unroll
-    for (int k = 0; k < kRankMax / 64; ++k) {
-      if (lane + 64 * k < m) {
-        const uint4 u = a.ups[id[k]];
-        a.rec[s + r[k]] = u;
-        s_rec[w][r[k]] = u;
-        a.sid[s + r[k]] = id[k];
-      }
-    }
-    wave_lds_fence();
-    put_windows(a, s, m, s_rec[w]);
-    return;
-  }
-  int out = s;
-  for (int64_t i0 = 0; i0 < a.n; i0 += kMapBits) {
-    wave_lds_fence();
-    for (int e = lane; e < kMapBits / 32; e += 64) map[e] = 0;
-    wave_lds_fence();
-    for (int e = lane; e < m; e += 64) {
-      const int64_t r = (int64_t)a.ids[s + e] - i0;
-      if (r >= 0 && r < kMapBits) atomicOr(&map[r >> 5], 1u << (r & 31));
-    }
-    wave_lds_fence();
-    for (int e0 = 0; e0 < kMapBits / 32; e0 += 64) {
-      uint32_t v = map[e0 + lane];
-      const int c = __builtin_popcount(v);
-      int inc = c;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(inc, o);
-        if (lane >= o) inc += y;
-      }
-      int p = out + inc - c;
-      while (v) {
-        const int i = (int)(i0 + 32 * (e0 + lane) + __builtin_ctz(v));
-        a.rec[p] = a.ups[i];
-        a.sid[p] = i;
-        ++p;
-        v &= v - 1;
-      }
-      out += __shfl(inc, 63);
-    }
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // the records are read back
-  put_windows(a, s, m, a.rec + s);
-}
-
 // The charges' grid, one workgroup of 4 waves per tile of 8 x 8 x 16 points: as a matrix
 // product over the atoms near the tile, b[(x, y)][z] = sum_j (q phi_x phi_y)[(x, y)][j]
 // phi_z[j][z], on the matrix cores, wave w taking x = 2 w and 2 w + 1. The atoms come from
-// the tile's own bin and the 26 around it (each axis has at least three); those whose window
-// meets the tile (one in four) are listed in bin order, up to kKeep at a time, and their
-// windows laid out over the tile's points kSub atoms at a time. In a 16x16x4 f32 product lane
-// l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and holds D[4 (l / 16) + i][l % 16].
-constexpr int kKeep = 1024, kSub = 64, kCand = 4;   // kCand candidates per thread and round
+// the tile's own bin and the 26 around it (each axis has at least three), wave w looking
+// through bins w, w + 4, ..; those whose window meets the tile (one in four) go to the wave's
+// list, and their windows are laid out over the tile's points kSub atoms at a time. In a
+// 16x16x4 f32 product lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and holds
+// D[4 (l / 16) + i][l % 16].
+constexpr int kList = 256, kSub = 64, kNear = 27;
 __global__ __launch_bounds__(256) void k_em_spread(EwMeshArgs a) {
-  __shared__ int s_start[27], s_cum[28];
-  __shared__ int s_at[kKeep], s_rel[kKeep];   // sorted position; x, y, z + 8 relative to the tile
+  __shared__ int s_start[28], s_cnt[28];
+  __shared__ int s_at[4][kList], s_rel[4][kList];   // sorted position; x, y, z + 8 off the tile
   __shared__ float s_w[kSub][32 + 2];         // per atom: 8 x, 8 y and 16 z points of the tile
-  __shared__ int s_n[4][kCand];
+  __shared__ int s_n[4], s_more;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
   const int tz = blockIdx.x % a.nt[2], ty = (blockIdx.x / a.nt[2]) % a.nt[1],
             tx = blockIdx.x / (a.nt[2] * a.nt[1]);
-  if (t < 64) {
-    int c = 0;
-    if (t < 27) {
-      int bx = tx + t / 9 - 1, by = ty + (t / 3) % 3 - 1, bz = tz + t % 3 - 1;
-      bx += bx < 0 ? a.nt[0] : bx >= a.nt[0] ? -a.nt[0] : 0;
-      by += by < 0 ? a.nt[1] : by >= a.nt[1] ? -a.nt[1] : 0;
-      bz += bz < 0 ? a.nt[2] : bz >= a.nt[2] ? -a.nt[2] : 0;
-      const int b = (bx * a.nt[1] + by) * a.nt[2] + bz;
-      s_start[t] = a.start[b];
-      c = a.start[b + 1] - s_start[t];
-    }
-    int inc = c;
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) {
-      const int y = __shfl_up(inc, o);
-      if (lane >= o) inc += y;
-    }
-    if (t < 28) s_cum[t] = inc - c;   // s_cum[27]: the total
+  if (t < 28) {
+    int bx = tx + t / 9 - 1, by = ty + (t / 3) % 3 - 1, bz = tz + t % 3 - 1;
+    bx += bx < 0 ? a.nt[0] : bx >= a.nt[0] ? -a.nt[0] : 0;
+    by += by < 0 ? a.nt[1] : by >= a.nt[1] ? -a.nt[1] : 0;
+    bz += bz < 0 ? a.nt[2] : bz >= a.nt[2] ? -a.nt[2] : 0;
+    const int b = t < kNear ? (bx * a.nt[1] + by) * a.nt[2] + bz : 0;
+    s_start[t] = a.start[b];
+    s_cnt[t] = t < kNear ? a.start[b + 1] - s_start[t] : 0;
   }
   __syncthreads();
-  const int total = s_cum[27];
   v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
   const int row = lane & 15, kk = lane >> 4;
-  int n = 0;   // atoms listed
-  for (int e0 = 0; e0 < total; e0 += 256 * kCand) {
-    // wave w lists candidates e0 + 256 k + 64 w + lane: its bin by bisection, its position
-    // relative to the tile
-    int pos[kCand], rel[kCand];
-    unsigned long long keep[kCand];
+  // the first 64 atoms of this wave's bins, all loads in flight
+  constexpr int kBins = (kNear + 3) / 4;
+  uint4 u[kBins];
 #pragma unroll
-    for (int k = 0; k < kCand; ++k) {
-      const int e = e0 + 256 * k + t;
-      int b = 0;
-#pragma unroll
-      for (int h = 16; h > 0; h >>= 1)
-        if (b + h < 27 && s_cum[b + h] <= e) b += h;
-      const bool in = e < total;
-      pos[k] = in ? s_start[b] + e - s_cum[b] : 0;
-      const uint4 u = a.rec[pos[k]];
-      uint32_t f;
-      const int rx = grid_cell(u.x, a.M[0], f) % kTX + kTX * (b / 9 - 1);
-      const int ry = grid_cell(u.y, a.M[1], f) % kTX + kTX * ((b / 3) % 3 - 1);
-      const int rz = grid_cell(u.z, a.M[2], f) % kTZ + kTZ * (b % 3 - 1);
-      rel[k] = (rx + 8) | (ry + 8) << 8 | (rz + 8) << 16;
-      keep[k] = __builtin_amdgcn_ballot_w64(in && rx >= -kHi && rx < kTX + kLo && ry >= -kHi &&
-                                            ry < kTX + kLo && rz >= -kHi && rz < kTZ + kLo);
-      if (lane == 0) s_n[w][k] = __builtin_popcountll(keep[k]);
+  for (int k = 0; k < kBins; ++k) {
+    const int b = 4 * k + w;   // at most 27, which is empty
+    u[k] = a.rec[lane < s_cnt[b] ? s_start[b] + lane : 0];
+  }
+  int n = 0;   // atoms listed by this wave
+  auto list = [&](int b, int e0, const uint4& v) {
+    const int e = e0 + lane;
+    const int dx = b / 9 - 1, dy = (b / 3) % 3 - 1, dz = b % 3 - 1;
+    // the grid cell relative to the tile: within the bin, and the bin's own offset
+    const int rx = (int)(__umulhi(v.x, (uint32_t)a.M[0]) % kTX) + kTX * dx;
+    const int ry = (int)(__umulhi(v.y, (uint32_t)a.M[1]) % kTX) + kTX * dy;
+    const int rz = (int)(__umulhi(v.z, (uint32_t)a.M[2]) % kTZ) + kTZ * dz;
+    const bool keep = e < s_cnt[b] && rx >= -kHi && rx < kTX + kLo && ry >= -kHi &&
+                      ry < kTX + kLo && rz >= -kHi && rz < kTZ + kLo;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+    if (keep) {
+      const int at = n + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+      s_at[w][at] = s_start[b] + e;
+      s_rel[w][at] = (rx + 8) | (ry + 8) << 8 | (rz + 8) << 16;
     }
-    __syncthreads();
+    n += __builtin_popcountll(m);
+  };
+  // next atom to look at: bin kb, from e; a list has room for 64 more before each step
+  int kb = 0, eb = 0;
+  bool first = true;
+  for (;;) {
+    if (first) {
 #pragma unroll
-    for (int k = 0; k < kCand; ++k) {
-      int at = n;
-      for (int v = 0; v < 4; ++v) {
-        at += v < w ? s_n[v][k] : 0;
-        n += s_n[v][k];
-      }
-      if (keep[k] >> lane & 1) {
-        at += __builtin_amdgcn_mbcnt_hi((unsigned)(keep[k] >> 32),
-                                        __builtin_amdgcn_mbcnt_lo((unsigned)keep[k], 0u));
-        s_at[at] = pos[k];
-        s_rel[at] = rel[k];
+      for (int k = 0; k < kBins; ++k) {
+        if (n <= kList - 64 && kb == k && eb == 0) {
+          const int b = 4 * k + w;
+          if (s_cnt[b] > 0) list(b, 0, u[k]);
+          if (s_cnt[b] > 64) eb = 64;   // the rest of a fuller bin below
+          else ++kb;
+        }
       }
     }
+    while (kb < kBins && n <= kList - 64) {
+      const int b = 4 * kb + w;
+      if (eb < s_cnt[b]) {
+        list(b, eb, a.rec[s_start[b] + min(eb + lane, s_cnt[b] - 1)]);
+        eb += 64;
+      } else {
+        ++kb;
+        eb = 0;
+      }
+    }
+    first = false;
+    if (t == 0) s_more = 0;
+    if (lane == 0) s_n[w] = n;
     __syncthreads();
-    // the next round may list up to 256 kCand more
-    if (n + 256 * kCand <= kKeep && e0 + 256 * kCand < total) continue;
+    if (lane == 0 && kb < kBins) s_more = 1;
+    const int n0 = s_n[0], n1 = n0 + s_n[1], n2 = n1 + s_n[2], tot = n2 + s_n[3];
     // window values at the tile's points, 32 per atom (past the last atom zeros), those of the
     // next kSub atoms on their way while the matrix cores take the last ones
     constexpr int kVals = 32 * kSub / 256;
@@ -398,22 +397,21 @@ __global__ __launch_bounds__(256) void k_em_spread(EwMeshArgs a) {
       for (int k = 0; k < kVals; ++k) {
         const int j = j0 + 8 * k + (t >> 5);
         val[k] = 0.f;
-        if (j < n) {
-          const int p = s_at[j], i = x - ((s_rel[j] >> sh) & 255);   // the window's point
-          if (i >= 0 && i < kW) {
-            val[k] = a.win[(int64_t)p * 32 + off + i];
-            if (c < 8) val[k] *= __uint_as_float(a.rec[p].w);
-          }
+        if (j < tot) {
+          const int v = (j >= n0) + (j >= n1) + (j >= n2);
+          const int jj = j - (v == 0 ? 0 : v == 1 ? n0 : v == 2 ? n1 : n2);
+          const int i = x - ((s_rel[v][jj] >> sh) & 255);   // the window's point
+          if (i >= 0 && i < kW) val[k] = a.win[(int64_t)s_at[v][jj] * 32 + (off + i)];
         }
       }
     };
-    if (n > 0) fetch(0);
-    for (int j0 = 0; j0 < n; j0 += kSub) {
-      const int n8 = (min(kSub, n - j0) + 7) & ~7;
+    if (tot > 0) fetch(0);
+    for (int j0 = 0; j0 < tot; j0 += kSub) {
+      const int n8 = (min(kSub, tot - j0) + 7) & ~7;
 #pragma unroll
       for (int k = 0; k < kVals; ++k) s_w[8 * k + (t >> 5)][t & 31] = val[k];
       __syncthreads();
-      if (j0 + kSub < n) fetch(j0 + kSub);
+      if (j0 + kSub < tot) fetch(j0 + kSub);
       for (int s = 0; s < n8; s += 8) {
         const float *wa = s_w[s + kk], *wb = s_w[s + 4 + kk];
         const float va = wa[2 * w + (row >> 3)] * wa[8 + (row & 7)];
@@ -423,7 +421,10 @@ __global__ __launch_bounds__(256) void k_em_spread(EwMeshArgs a) {
       }
       __syncthreads();
     }
+    __syncthreads();   // s_more is set, the lists are read
+    if (!s_more) break;
     n = 0;
+    __syncthreads();   // before s_more is cleared
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -635,7 +636,6 @@ __global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
   fetch(s0 + w);
   __syncthreads();
   for (int s = s0 + w; s < s1; s += 4) {
-    const float q = __uint_as_float(u.w);
     const int64_t at = 3 * (int64_t)id;
     uint32_t f;
     const int l = ((grid_cell(u.x, a.M[0], f) % kTX) * kRX + grid_cell(u.y, a.M[1], f) % kTX) * kRZ +
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
     for (int c = 0; c < 3; ++c) F[c] = wave_sum(F[c]);
     if (lane < 3) {
       const double g = (double)(lane == 0 ? F[0] : lane == 1 ? F[1] : F[2]);
-      const float v = (float)((double)q * g * ((double)a.M[lane] / a.L[lane]));
+      const float v = (float)(g * a.mL[lane]);
       float* out = a.force + at + lane;
       *out = a.accumulate ? *out + v : v;
     }
@@ -781,6 +781,7 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
     a.K[d] = pl.K[d];
     a.nt[d] = pl.nt[d];
     a.L[d] = (double)(float)p->box[d];   // the float32 box
+    a.mL[d] = (double)pl.M[d] / a.L[d];
     V *= a.L[d];
     a.tab[d] = (float*)(b + pl.off_tab[d]);
     a.tabT[d] = (float*)(b + pl.off_tabT[d]);
@@ -799,7 +800,7 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   hipLaunchKernelGGL(k_em_setup, dim3(nb), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_em_scan, dim3(1), dim3(1024), 0, st, a);
   hipLaunchKernelGGL(k_em_scatter, dim3(nb), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(k_em_sort, dim3((unsigned)((pl.nbins + 3) / 4)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_em_sort, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_em_spread, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
   const int64_t rows = (int64_t)a.M[0] * a.M[1];
   auto right = [&](const float* in, const float* T, float* out, int K, int J) {
