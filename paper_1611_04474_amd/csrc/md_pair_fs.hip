@@ -284,6 +284,35 @@ __device__ inline void global_add(long long* p, long long v) {
 //                  reciprocal space beyond the short-range kernel.
 constexpr int kCoulSwitched = 0, kCoulPlain = 1, kCoulEwald = 2;
 
+// erfc(x) and exp(-x^2) for x >= 0 in float32, sharing the exponential: erfc = exp(-x^2)
+// g(q) / (1 + 2 x) with q = (x - 2)/(x + 2) (the form of Shepherd and Laframboise, Math. Comp. 36
+// (1981) 249); g's coefficients from a Chebyshev interpolation of (1 + 2 x) exp(x^2) erfc(x) on
+// [0, 6.5] in float64, where the degree leaves 8e-9 (beyond, the exponential is under 1e-18).
+// x^2 and its product with log2(e) carry their rounding errors along, so exp stays within about an
+// ulp. The library's erfcf (two branches, both taken in every wave) and expf took the kernel
+// at 92,224 atoms 183 us, this 167 (RMS force error of the electrostatics alone 1.59e-7 -> 1.60e-7, of
+// its energy 1.7e-7 -> 3e-8).
+__device__ inline float erfc_exp(float x, float& ex) {
+  const float xx = x * x;
+  const float lo = fmaf(x, x, -xx);
+  const float h = -1.44269504f * xx;
+  const float l = fmaf(-1.44269504f, xx, -h) - fmaf(1.44269504f, lo, 1.92596299e-8f * xx);
+  ex = __builtin_amdgcn_exp2f(h);
+  ex = fmaf(ex, 0.693147181f * l, ex);
+  const float q = (x - 2.0f) * __builtin_amdgcn_rcpf(x + 2.0f);
+  float p = -0.000429302559f;
+  p = fmaf(p, q, -0.00128258815f);
+  p = fmaf(p, q, 0.00131015439f);
+  p = fmaf(p, q, 0.00866760268f);
+  p = fmaf(p, q, -0.00804970499f);
+  p = fmaf(p, q, -0.0542121652f);
+  p = fmaf(p, q, 0.164053117f);
+  p = fmaf(p, q, -0.166030842f);
+  p = fmaf(p, q, -0.092763879f);
+  p = fmaf(p, q, 1.27697839f);
+  return ex * (p * __builtin_amdgcn_rcpf(fmaf(2.0f, x, 1.0f)));
+}
+
 // 1/sqrt(u) in float64: the hardware's estimate (about 2^-23) and one third-order step,
 // r (1 + e/2 + 3 e^2/8) with e = 1 - u r^2 (error e^3, below the rounding), in place of a
 // correctly rounded root and a division (about 30 instructions): 24,000 atoms 171 -> 158 us,
@@ -333,8 +362,7 @@ __device__ inline Real pair_f(Real u, Real c12, Real c6, Real qq, Real rc2, Real
     const Real ar = ew.x * (u * rinv);
     Real sc, ex;
     if constexpr (sizeof(Real) == 4) {
-      sc = erfcf(ar);
-      ex = expf(-ar * ar);
+      sc = erfc_exp(ar, ex);
     } else {
       sc = erfc(ar);
       ex = exp(-ar * ar);
