@@ -68,7 +68,7 @@ struct EwMeshPlan {
                                 // points; tiles
   int64_t nbins, nepart, qblocks;
   size_t off_ups, off_rec, off_win, off_dwin, off_slot, off_ids, off_sid, off_count, off_start, off_buf0, off_buf1,
-      off_buf2, off_buf3, off_tab[3], off_tabT[3], off_gfac[3], off_ksq[3], off_epart, off_qpart,
+      off_tab[3], off_tabT[3], off_gfac[3], off_ksq[3], off_epart, off_qpart,
       total;
 };
 
@@ -90,6 +90,7 @@ struct EwMeshArgs {
   int* count;          // [nbins]
   int* start;          // [nbins + 1]
   float* buf0;         // [Mx][My][Mz] charges, then the potential's coefficients
+  float* buf1;         // [Mx][Ny][Nz] transformed along z and y
   float *tab[3], *tabT[3];   // [N][M] and [M][N] basis functions per axis
   double *gfac[3], *ksq[3];  // [N] per axis: multiplicity exp(-k^2/4 alpha^2)/phihat^2; k^2
   double* epart;       // [nepart]

@@ -29,7 +29,7 @@
 //   k_em_scan     bin starts;   k_em_scatter  atom indices to bins
 //   k_em_sort     each bin in index order (so sums run in a fixed order)
 //   k_em_spread   b, one workgroup per tile of 8 x 8 x 16 grid points
-//   k_em_right / k_em_left   the six axis transforms (Q and E after the last forward one)
+//   k_em_forward, k_em_middle, k_em_back   the axis transforms z y, x (Q and E) x, y z
 //   k_em_force    forces, one workgroup per tile
 //   k_em_energy   fixed-order sum of the energy partials, self and background
 // Every sum runs in a fixed order: the results are the same bits on every run.
@@ -436,135 +436,211 @@ __global__ __launch_bounds__(256) void k_em_spread(EwMeshArgs a) {
 
 // Axis transforms. Each group of 16 k is summed by the matrix cores in float32 from zero and
 // the groups in float64 (float32 sums over whole lines put 2e-7 into the forces); the operands
-// of the next group are on their way meanwhile.
-// Last axis: out[r][j] = sum_k in[r][k] T[k][j] for r < rows (rows, K and J multiples of 16). A
-// wave takes 16 rows x up to 64 columns; a lane reads four consecutive k of its row at once
-// (step s of a group uses k0 + 4 (l / 16) + s, for T as well).
-__global__ __launch_bounds__(256) void k_em_right(const float* __restrict__ in,
-                                                  const float* __restrict__ T,
-                                                  float* __restrict__ out, int64_t rows, int K, int J) {
-  const int lane = threadIdx.x & 63, row = lane & 15, kk = lane >> 4;
-  const int jt = (J + 63) / 64;
-  const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t r0 = wv / jt * 16;
-  if (r0 >= rows) return;
-  const int j0 = (int)(wv % jt) * 64;
-  const int nj = min(4, (J - j0) / 16);
-  double acc[4][4] = {};   // [column tile][row]
-  const float* ip = in + (r0 + row) * K + 4 * kk;
-  const float* tp = T + (int64_t)4 * kk * J + j0 + row;
-  float4 av;
-  float bv[4][4];
-  auto load = [&](int k0, float4& va, float (&vb)[4][4]) {
-    va = *reinterpret_cast<const float4*>(ip + k0);
+// of the next groups are on their way meanwhile. A lane's latency to memory, not the products
+// (1.2 GFLOP and 8 us for all six at 92,224 atoms), is what a transform takes its time for, so
+// each kernel does two of them: z and y of a plane, x forward and back of a column, y and z of a
+// plane, the intermediate (float32) in LDS. 92,224 atoms (grid 144 x 144 x 112, 80 x 80 x 64
+// modes): 60.1 us in six launches, 43.2 in these three.
+constexpr int kTrWaves = 8, kTrThreads = 64 * kTrWaves;
+
+// (p + a 32-bit byte offset: one uniform base and a lane offset per load)
+__device__ inline float word_at(const float* p, uint32_t byte) {
+  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + byte);
+}
+
+// 16 rows x 16 C columns, sum over K: step s of a group uses k0 + 4 (l / 16) + s for both sides;
+// fa(k) gives a lane its row's four consecutive k, fb(k, v) the columns of them. Each of four
+// (rows) and two (columns) groups' operands has registers of its own and is loaded again as soon
+// as it is used, so the loads of the following groups are always on their way.
+template <int C, typename FA, typename FB>
+__device__ __attribute__((always_inline)) inline void rows_times(int K, FA fa, FB fb, double (&acc)[C][4]) {
+  float4 av[4];
+  float bv[2][4][C];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) av[g] = fa(min(16 * g, K - 16));
+#pragma unroll
+  for (int g = 0; g < 2; ++g) fb(min(16 * g, K - 16), bv[g]);
+  auto step = [&](int g, int k, bool more) __attribute__((always_inline)) {
+    const float a4[4] = {av[g].x, av[g].y, av[g].z, av[g].w};
+    v4f d[C] = {};
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) vb[s][c] = c < nj ? tp[(int64_t)(k0 + s) * J + 16 * c] : 0.f;
+      for (int c = 0; c < C; ++c)
+        d[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[s], bv[g & 1][s][c], d[c], 0, 0, 0);
+    if (more) av[g] = fa(min(k + 64, K - 16));
+    fb(min(k + 32, K - 16), bv[g & 1]);
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[c][i] += (double)d[c][i];
   };
-  load(0, av, bv);
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    float4 an;
-    float bn[4][4];
-    load(k0 + 16 < K ? k0 + 16 : 0, an, bn);
-    const float a4[4] = {av.x, av.y, av.z, av.w};
-    v4f g[4] = {};
+  int k0 = 0;
+  for (; k0 + 64 <= K; k0 += 64) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        g[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[s], bv[s][c], g[c], 0, 0, 0);
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[c][i] += (double)g[c][i];
-    av = an;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) bv[s][c] = bn[s][c];
+    for (int g = 0; g < 4; ++g) step(g, k0 + 16 * g, true);
   }
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    if (c >= nj) break;
+  for (int g = 0; g < 3; ++g)
+    if (k0 + 16 * g < K) step(g, k0 + 16 * g, false);
+}
+
+// 16 rows x 16 columns, sum over K: step s of a group uses k0 + 4 s + l / 16; fa(k, s), fb(k, s)
+// give a lane its element of row and column k + 4 s. Operands of four groups on their way.
+template <typename FA, typename FB>
+__device__ __attribute__((always_inline)) inline void tile_times(int K, FA fa, FB fb, double (&acc)[4]) {
+  float av[4][4], bv[4][4];
+  auto load = [&](int k, float (&va)[4], float (&vb)[4]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) out[(r0 + 4 * kk + i) * J + j0 + 16 * c + row] = (float)acc[c][i];
+    for (int s = 0; s < 4; ++s) {
+      va[s] = fa(k, s);
+      vb[s] = fb(k, s);
+    }
+  };
+#pragma unroll
+  for (int g = 0; g < 4; ++g) load(min(16 * g, K - 16), av[g], bv[g]);
+  auto step = [&](int g, int k, bool more) __attribute__((always_inline)) {
+    v4f d = {};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(av[g][s], bv[g][s], d, 0, 0, 0);
+    if (more) load(min(k + 64, K - 16), av[g], bv[g]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] += (double)d[i];
+  };
+  int k0 = 0;
+  for (; k0 + 64 <= K; k0 += 64) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) step(g, k0 + 16 * g, true);
+  }
+#pragma unroll
+  for (int g = 0; g < 3; ++g)
+    if (k0 + 16 * g < K) step(g, k0 + 16 * g, false);
+}
+
+// z and y forward: workgroup (x, group of up to C 16-column tiles of nz). The row stride in LDS
+// is an odd number of 16s, so that the four k that a wave reads at once lie in different banks.
+template <int C>
+__global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_em_forward(EwMeshArgs a, int groups) {
+  extern __shared__ __attribute__((aligned(16))) float s_m[];   // [M1][16 (C | 1)]
+  constexpr int kStride = 16 * (C | 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int row = lane & 15, kk = lane >> 4;
+  const int64_t x = blockIdx.x / groups;
+  const int M1 = a.M[1], M2 = a.M[2], N1 = a.N[1], N2 = a.N[2];
+  const int c0 = (int)(blockIdx.x % groups) * C, nc = min(C, N2 / 16 - c0);
+  for (int r = w; r < M1 / 16; r += kTrWaves) {
+    const float *ip = a.buf0 + (x * M1 + 16 * r) * M2, *tp = a.tabT[2] + 16 * c0;
+    const uint32_t io = 4 * (row * M2 + 4 * kk), to = 4 * (4 * kk * N2 + row);
+    double acc[C][4] = {};
+    rows_times<C>(M2, [&](int k) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(ip) + (4u * k + io)); },
+                  [&](int k, float (&v)[4][C]) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+#pragma unroll
+                      for (int c = 0; c < C; ++c) v[s][c] = word_at(tp, 4u * ((k + s) * N2 + 16 * min(c, nc - 1)) + to);
+                  }, acc);
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s_m[(16 * r + 4 * kk + i) * kStride + 16 * c + row] = (float)acc[c][i];
+  }
+  __syncthreads();
+  for (int t = w; t < N1 / 16 * nc; t += kTrWaves) {
+    const int i0 = t / nc * 16, c = t % nc;
+    const float* tp = a.tabT[1] + i0;
+    const uint32_t to = 4 * (kk * N1 + row);
+    const float* bp = s_m + kk * kStride + 16 * c + row;
+    double acc[4] = {};
+    tile_times(M1, [&](int k, int s) { return word_at(tp, 4u * (k + 4 * s) * N1 + to); },
+               [&](int k, int s) { return bp[(k + 4 * s) * kStride]; }, acc);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      a.buf1[(x * N1 + i0 + 4 * kk + i) * N2 + 16 * (c0 + c) + row] = (float)acc[i];
   }
 }
 
-// Another axis: out[b][i][j] = sum_k T[k][i] in[b][k][j] for b < nb, i < I, j < J (multiples of
-// 16). A wave takes 16 rows i x 32 columns j. kScale (the last forward transform: i = nx, j =
-// (ny, nz)): R is scaled to Q in float64 and the wave's part of the energy, 1/2 sum Q R, goes
-// to epart.
-template <bool kScale>
-__global__ __launch_bounds__(256) void k_em_left(EwMeshArgs a, const float* __restrict__ in,
-                                                 const float* __restrict__ T,
-                                                 float* __restrict__ out, int64_t nb, int I, int K,
-                                                 int64_t J) {
-  const int lane = threadIdx.x & 63, row = lane & 15, kk = lane >> 4;
-  const int64_t jt = (J + 31) / 32;
-  const int it = I / 16;
-  const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wv >= nb * it * jt) return;
-  const int64_t j0 = wv % jt * 32, b = wv / (jt * it);
-  const int i0 = (int)(wv / jt % it) * 16;
-  const bool two = j0 + 32 <= J;
-  double acc[2][4] = {};   // [column tile][row]
-  const float* ip = in + (b * K + kk) * J + j0 + row;
-  const float* tp = T + (int64_t)kk * I + i0 + row;
-  float av[4], bv[4][2];
-  auto load = [&](int k0, float (&va)[4], float (&vb)[4][2]) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      va[s] = tp[(int64_t)(k0 + 4 * s) * I];
-      vb[s][0] = ip[(k0 + 4 * s) * J];
-      vb[s][1] = two ? ip[(k0 + 4 * s) * J + 16] : 0.f;
-    }
-  };
-  load(0, av, bv);
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    float an[4], bn[4][2];
-    load(k0 + 16 < K ? k0 + 16 : 0, an, bn);
-    v4f g[2] = {};
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-        g[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s], bv[s][c], g[c], 0, 0, 0);
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[c][i] += (double)g[c][i];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      av[s] = an[s];
-      bv[s][0] = bn[s][0];
-      bv[s][1] = bn[s][1];
-    }
-  }
-  double e = 0.0;
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    if (c == 1 && !two) break;
-    const int64_t j = j0 + 16 * c + row;
+// x forward, the scaling of R to Q in float64 with the energy 1/2 sum Q R (a part per 16 x 16
+// tile), and x back: workgroup j of 16 columns (ny, nz), in place.
+__global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_em_middle(EwMeshArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float s_q[];   // [N0][16]
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int row = lane & 15, kk = lane >> 4;
+  const int M0 = a.M[0], N0 = a.N[0];
+  const int64_t J = (int64_t)a.N[1] * a.N[2], j = (int64_t)blockIdx.x * 16 + row;
+  const int ny = (int)(j / a.N[2]), nz = (int)(j % a.N[2]);
+  const double k2yz = a.ksq[1][ny] + a.ksq[2][nz];
+  for (int t = w; t < N0 / 16; t += kTrWaves) {
+    const float *tp = a.tabT[0] + 16 * t, *ip = a.buf1 + (int64_t)blockIdx.x * 16;
+    const uint32_t to = 4 * (kk * N0 + row), io = 4 * (kk * (uint32_t)J + row);
+    double acc[4] = {};
+    tile_times(M0, [&](int k, int s) { return word_at(tp, 4u * (k + 4 * s) * N0 + to); },
+               [&](int k, int s) { return word_at(ip, 4u * (k + 4 * s) * (uint32_t)J + io); }, acc);
+    double e = 0.0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int ii = i0 + 4 * kk + i;
-      double v = acc[c][i];
-      if constexpr (kScale) {
-        const int ny = (int)(j / a.N[2]), nz = (int)(j % a.N[2]);
-        const double k2 = a.ksq[0][ii] + a.ksq[1][ny] + a.ksq[2][nz];
-        const double g = k2 > 0.0 ? a.gscale * a.gfac[0][ii] * a.gfac[1][ny] * a.gfac[2][nz] / k2 : 0.0;
-        const double q = g * v;
-        e += 0.5 * q * v;
-        v = q;
-      }
-      out[(b * I + ii) * J + j] = (float)v;
+      const int nx = 16 * t + 4 * kk + i;
+      const double k2 = a.ksq[0][nx] + k2yz;
+      const double g = k2 > 0.0 ? a.gscale * a.gfac[0][nx] * a.gfac[1][ny] * a.gfac[2][nz] / k2 : 0.0;
+      const double q = g * acc[i];
+      e += 0.5 * q * acc[i];
+      s_q[nx * 16 + row] = (float)q;
     }
-  }
-  if constexpr (kScale) {
     for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o);
-    if (lane == 0) a.epart[wv] = e;
+    if (lane == 0) a.epart[(int64_t)blockIdx.x * (N0 / 16) + t] = e;
+  }
+  __syncthreads();
+  for (int t = w; t < M0 / 16; t += kTrWaves) {
+    const float* tp = a.tab[0] + 16 * t;
+    const uint32_t to = 4 * (kk * M0 + row);
+    const float* bp = s_q + kk * 16 + row;
+    double acc[4] = {};
+    tile_times(N0, [&](int k, int s) { return word_at(tp, 4u * (k + 4 * s) * M0 + to); },
+               [&](int k, int s) { return bp[(k + 4 * s) * 16]; }, acc);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a.buf1[(16 * t + 4 * kk + i) * J + j] = (float)acc[i];
+  }
+}
+
+// y and z back: workgroup (x, group of up to rt 16-row tiles of y).
+__global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_em_back(EwMeshArgs a, int rt, int groups) {
+  extern __shared__ __attribute__((aligned(16))) float s_r[];   // [16 rt][N2 + 4]
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int row = lane & 15, kk = lane >> 4;
+  const int64_t x = blockIdx.x / groups;
+  const int M1 = a.M[1], M2 = a.M[2], N1 = a.N[1], N2 = a.N[2], S = N2 + 4;
+  const int r0 = (int)(blockIdx.x % groups) * rt, nr = min(rt, M1 / 16 - r0);
+  for (int t = w; t < nr * (N2 / 16); t += kTrWaves) {
+    const int r = t / (N2 / 16), c = t % (N2 / 16);
+    const float *tp = a.tab[1] + 16 * (r0 + r), *ip = a.buf1 + x * N1 * N2 + 16 * c;
+    const uint32_t to = 4 * (kk * M1 + row), io = 4 * (kk * N2 + row);
+    double acc[4] = {};
+    tile_times(N1, [&](int k, int s) { return word_at(tp, 4u * (k + 4 * s) * M1 + to); },
+               [&](int k, int s) { return word_at(ip, 4u * (k + 4 * s) * N2 + io); }, acc);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s_r[(16 * r + 4 * kk + i) * S + 16 * c + row] = (float)acc[i];
+  }
+  __syncthreads();
+  const int jt = (M2 + 63) / 64;
+  for (int t = w; t < nr * jt; t += kTrWaves) {
+    const int r = t / jt, j0 = t % jt * 64, nj = min(4, (M2 - j0) / 16);
+    const float* ap = s_r + (16 * r + row) * S + 4 * kk;
+    const float* tp = a.tab[2] + j0;
+    const uint32_t to = 4 * (4 * kk * M2 + row);
+    double acc[4][4] = {};
+    rows_times<4>(N2, [&](int k) { return *reinterpret_cast<const float4*>(ap + k); },
+                  [&](int k, float (&v)[4][4]) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+#pragma unroll
+                      for (int c = 0; c < 4; ++c) v[s][c] = word_at(tp, 4u * ((k + s) * M2 + 16 * min(c, nj - 1)) + to);
+                  }, acc);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (c >= nj) break;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        a.buf0[(x * M1 + 16 * (r0 + r) + 4 * kk + i) * M2 + j0 + 16 * c + row] = (float)acc[c][i];
+    }
   }
 }
 
@@ -692,7 +768,9 @@ __global__ __launch_bounds__(256) void k_em_energy(EwMeshArgs a) {
 // both faster and no less accurate than the direct sum (whole call, and RMS force error
 // against float64, direct and grid: 5,000 atoms x 1.2e4 wave vectors 140 us 2.7e-7, 80 us
 // 4.1e-7; 9,001 x 1.9e4 226 us 3.9e-7, 94 us 3.8e-7; 20,000 x 2.5e4 292 us 5.2e-7, 114 us 3.8e-7;
-// 40,000 x 9.3e4 1205 us 9.9e-7, 134 us 5.2e-7; 92,224 x 1.78e5 4897 us 2.4e-6, 208 us 4.2e-7);
+// 40,000 x 9.3e4 1205 us 9.9e-7, 134 us 5.2e-7; 92,224 x 1.78e5 4897 us 2.4e-6, 208 us 4.2e-7;
+// the grid's times are from before its spreading and transforms took their present form: 92,224
+// now 169 us);
 // not where its workspace would be more than twice the direct sum's and 512 MiB (few atoms
 // with hundreds of wave numbers per axis).
 bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t direct_bytes,
@@ -723,9 +801,7 @@ bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t d
   pl->off_start = o; o = al(o + 4 * (size_t)(pl->nbins + 1));
   const size_t M0 = pl->M[0], M1 = pl->M[1], M2 = pl->M[2], N0 = pl->N[0], N1 = pl->N[1], N2 = pl->N[2];
   pl->off_buf0 = o;  o = al(o + 4 * M0 * M1 * M2);
-  pl->off_buf1 = o;  o = al(o + 4 * M0 * M1 * N2);
-  pl->off_buf2 = o;  o = al(o + 4 * M0 * N1 * N2);
-  pl->off_buf3 = o;  o = al(o + 4 * N0 * N1 * N2);
+  pl->off_buf1 = o;  o = al(o + 4 * M0 * N1 * N2);
   for (int d = 0; d < 3; ++d) {
     const size_t e = (size_t)pl->N[d] * pl->M[d];
     pl->off_tab[d] = o;  o = al(o + 4 * e);
@@ -733,7 +809,7 @@ bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t d
     pl->off_gfac[d] = o; o = al(o + 8 * (size_t)pl->N[d]);
     pl->off_ksq[d] = o;  o = al(o + 8 * (size_t)pl->N[d]);
   }
-  pl->nepart = (int64_t)(N0 / 16) * ((N1 * N2 + 31) / 32);
+  pl->nepart = (int64_t)((N0 / 16) * (N1 * N2 / 16));
   pl->off_epart = o; o = al(o + 8 * (size_t)pl->nepart);
   pl->qblocks = (n + 255) / 256;
   pl->off_qpart = o; o = al(o + 16 * (size_t)pl->qblocks);
@@ -763,9 +839,7 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   a.count = (int*)(b + pl.off_count);
   a.start = (int*)(b + pl.off_start);
   a.buf0 = (float*)(b + pl.off_buf0);
-  float* buf1 = (float*)(b + pl.off_buf1);
-  float* buf2 = (float*)(b + pl.off_buf2);
-  float* buf3 = (float*)(b + pl.off_buf3);
+  a.buf1 = (float*)(b + pl.off_buf1);
   a.epart = (double*)(b + pl.off_epart);
   a.qpart = (double2*)(b + pl.off_qpart);
   a.nepart = pl.nepart;
@@ -802,23 +876,27 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   hipLaunchKernelGGL(k_em_scatter, dim3(nb), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_em_sort, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_em_spread, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
-  const int64_t rows = (int64_t)a.M[0] * a.M[1];
-  auto right = [&](const float* in, const float* T, float* out, int K, int J) {
-    const int64_t waves = rows / 16 * ((J + 63) / 64);
-    hipLaunchKernelGGL(k_em_right, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, in, T, out, rows, K, J);
+  // workgroups of the transforms: four per compute unit where the tiles allow it (with one, 288
+  // workgroups, 45 us for all three; with four 43), at most three tiles each (the registers of a
+  // wave's columns) and 64 KB of LDS (a kmax of 255 makes an axis of 896 points and 512 modes)
+  const int need = (1024 + a.M[0] - 1) / a.M[0];
+  auto share = [&](int tiles, auto bytes, int& groups) {
+    int c = (tiles + need - 1) / need;
+    c = c > 3 ? 3 : c;
+    while (c > 1 && bytes(c) > 65536) --c;
+    groups = (tiles + c - 1) / c;
+    return (tiles + groups - 1) / groups;
   };
-  auto left = [&](auto scale, const float* in, const float* T, float* out, int64_t batch, int I, int K, int64_t J) {
-    const int64_t waves = batch * (I / 16) * ((J + 31) / 32);
-    hipLaunchKernelGGL((k_em_left<decltype(scale)::value>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st,
-                       a, in, T, out, batch, I, K, J);
-  };
-  const int64_t Jx = (int64_t)a.N[1] * a.N[2];
-  right(a.buf0, a.tabT[2], buf1, a.M[2], a.N[2]);                                      // z
-  left(std::false_type(), buf1, a.tabT[1], buf2, a.M[0], a.N[1], a.M[1], a.N[2]);      // y
-  left(std::true_type(), buf2, a.tabT[0], buf3, 1, a.N[0], a.M[0], Jx);                // x, Q, E
-  left(std::false_type(), buf3, a.tab[0], buf2, 1, a.M[0], a.N[0], Jx);                // x back
-  left(std::false_type(), buf2, a.tab[1], buf1, a.M[0], a.M[1], a.N[1], a.N[2]);       // y back
-  right(buf1, a.tab[2], a.buf0, a.N[2], a.M[2]);                                       // z back
+  int gf, gb;
+  auto fb = [&](int c) { return (size_t)64 * a.M[1] * (c | 1); };
+  auto bb = [&](int c) { return (size_t)64 * c * (a.N[2] + 4); };
+  const int cf = share(a.N[2] / 16, fb, gf), rt = share(a.M[1] / 16, bb, gb);
+  const dim3 grid((unsigned)(a.M[0] * gf)), wg(kTrThreads);
+  if (cf == 1) hipLaunchKernelGGL(k_em_forward<1>, grid, wg, fb(1), st, a, gf);
+  else if (cf == 2) hipLaunchKernelGGL(k_em_forward<2>, grid, wg, fb(2), st, a, gf);
+  else hipLaunchKernelGGL(k_em_forward<3>, grid, wg, fb(3), st, a, gf);
+  hipLaunchKernelGGL(k_em_middle, dim3((unsigned)(a.N[1] * a.N[2] / 16)), wg, (size_t)64 * a.N[0], st, a);
+  hipLaunchKernelGGL(k_em_back, dim3((unsigned)(a.M[0] * gb)), wg, bb(rt), st, a, rt, gb);
   hipLaunchKernelGGL(k_em_force, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_em_energy, dim3(1), dim3(256), 0, st, a);
   return hipGetLastError();
