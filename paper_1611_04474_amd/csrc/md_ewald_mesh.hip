@@ -44,6 +44,10 @@ constexpr int kW = 10;                  // window width in grid points
 constexpr int kTX = 8, kTZ = 16;        // tile: 8 x 8 x 16 grid points
 constexpr int kLo = kW / 2 - 1;         // an atom at grid cell l covers l - 4 .. l + 5
 constexpr int kHi = kW / 2;
+// Bin counters lie 32 bytes apart: atomics of neighbouring bins no longer wait for each other's
+// line (k_em_setup of 92,224 atoms in 2,268 bins 13.2 -> 7.4 us; 128 bytes apart 6.6, but the
+// largest grids have 700,000 bins to clear and scan).
+constexpr int kPad = 8;
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 // The window phi(t) = exp(beta (sqrt(1 - x^2) - 1)), x = 2 t / w, and its derivative, for
@@ -89,7 +93,7 @@ __device__ inline int bin_of(const EwMeshArgs& a, uint4 u) {
 // cleared by every block.
 __global__ __launch_bounds__(256) void k_em_init(EwMeshArgs a, unsigned nb_tab) {
   const int64_t gt = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  for (int64_t i = gt; i < a.nbins; i += (int64_t)gridDim.x * 256) a.count[i] = 0;
+  for (int64_t i = gt; i < kPad * a.nbins; i += (int64_t)gridDim.x * 256) a.count[i] = 0;
   if (gt == 0) a.hdr->status = 0;
   if (blockIdx.x < nb_tab) {
     int64_t e = gt;
@@ -142,7 +146,7 @@ __global__ __launch_bounds__(256) void k_em_setup(EwMeshArgs a) {
     uint32_t st = 0;
     const uint4 u = ew_fractions(a.pos, a.q, a.L, i, st);
     b = bin_of(a, u);
-    at = atomicAdd(&a.count[b], 1);   // on its way during the sums below
+    at = atomicAdd(&a.count[(int64_t)kPad * b], 1);   // on its way during the sums below
     a.ups[i] = u;
     const double qi = (double)__uint_as_float(u.w);
     q2 = qi * qi;
@@ -174,7 +178,7 @@ __global__ __launch_bounds__(1024) void k_em_scan(EwMeshArgs a) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int64_t b = b0 + 4 * t + k;
-      v[k] = b < a.nbins ? a.count[b] : 0;
+      v[k] = b < a.nbins ? a.count[kPad * b] : 0;
       sum += v[k];
     }
     int inc = sum;
@@ -797,7 +801,7 @@ bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t d
   pl->off_slot = o;  o = al(o + 8 * nn);
   pl->off_ids = o;   o = al(o + 4 * nn);
   pl->off_sid = o;   o = al(o + 4 * nn);
-  pl->off_count = o; o = al(o + 4 * (size_t)pl->nbins);
+  pl->off_count = o; o = al(o + 4 * kPad * (size_t)pl->nbins);
   pl->off_start = o; o = al(o + 4 * (size_t)(pl->nbins + 1));
   const size_t M0 = pl->M[0], M1 = pl->M[1], M2 = pl->M[2], N0 = pl->N[0], N1 = pl->N[1], N2 = pl->N[2];
   pl->off_buf0 = o;  o = al(o + 4 * M0 * M1 * M2);
