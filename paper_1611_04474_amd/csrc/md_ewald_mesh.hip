@@ -648,27 +648,40 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
   }
 }
 
-// Sum over a wave in a fixed order, in every lane.
-__device__ inline float wave_sum(float v) {
-  auto dpp = [](float x, auto ctrl) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-        0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, false));
+// Sums of three values over a wave in a fixed order: x in lane 0, z in lanes 16 and 48, y in
+// lane 32. The halves of the wave, then its rows, exchange what the other one keeps
+// (v_permlane32_swap, v_permlane16_swap), so one sum over 16 lanes does for all three.
+__device__ inline float wave_sum3(float x, float y, float z) {
+  auto swap32 = [](float p, float q) {
+    const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+    return __uint_as_float(v[0]) + __uint_as_float(v[1]);
   };
-  v += dpp(v, std::integral_constant<int, 0xB1>());    // xor 1
-  v += dpp(v, std::integral_constant<int, 0x4E>());    // xor 2
-  v += dpp(v, std::integral_constant<int, 0x141>());   // mirror within 8
-  v += dpp(v, std::integral_constant<int, 0x140>());   // mirror within 16
-  auto at = [&](int l) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l)); };
-  return (at(0) + at(16)) + (at(32) + at(48));
+  const float xy = swap32(x, y), zz = swap32(z, z);
+  const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(xy), __float_as_uint(zz), false, false);
+  float t = __uint_as_float(v[0]) + __uint_as_float(v[1]);
+  auto dpp = [](float a, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+        0, __builtin_bit_cast(int, a), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  t += dpp(t, std::integral_constant<int, 0xB1>());    // xor 1
+  t += dpp(t, std::integral_constant<int, 0x4E>());    // xor 2
+  t += dpp(t, std::integral_constant<int, 0x141>());   // mirror within 8
+  t += dpp(t, std::integral_constant<int, 0x140>());   // mirror within 16
+  return t;
 }
 
-// Forces, one workgroup of 4 waves per tile: the potential's coefficients around the tile
+// Forces, one workgroup of 8 waves per tile: the potential's coefficients around the tile
 // (17 x 17 x 25 points) in LDS; a wave takes an atom of the tile's bin at a time, its lanes the
 // 100 (x, y) rows of the window (two rounds), each summing its row's 10 z values from both ends
 // with phi_z and phi_z' (uniform, in scalar registers). The coefficient at the atom's own grid
 // point is taken off every value: a constant exerts no force, and the derivative's rounding
-// then scales with the potential's change over the window, not with the potential.
-__global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
+// then scales with the potential's change over the window, not with the potential. Bound by
+// instruction issue, about 200 per atom. 92,224 atoms: 54.6 us with 4 waves and a sum per
+// component; 49.2 with one sum for the three; 46.9 with the buffer's old force read an atom
+// ahead; 39.7 with 8 waves (more than four workgroups do not fit a compute unit's LDS, and
+// four of 8 waves fill it; 10, 12 and 16 waves 47, 43 and 43).
+constexpr int kForceThreads = 512;
+__global__ __launch_bounds__(kForceThreads) void k_em_force(EwMeshArgs a) {
   constexpr int kRX = kTX + kW - 1, kRZ = kTZ + kW - 1;   // points around the tile
   constexpr int kQuads = (kRZ + 3) / 4;                   // 16-byte loads per row
   __shared__ float s_c[kRX * kRX * kRZ];
@@ -681,7 +694,7 @@ __global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
   // straddles the box edge and is aligned
   static_assert(kLo == 4 && kTZ % 4 == 0, "aligned quads");
 #pragma unroll 4
-  for (int e = t; e < kRX * kRX * kQuads; e += 256) {
+  for (int e = t; e < kRX * kRX * kQuads; e += kForceThreads) {
     const int qd = e % kQuads, rw = e / kQuads;
     int x = rw / kRX + kTX * tx - kLo, y = rw % kRX + kTX * ty - kLo, z = 4 * qd + kTZ * tz - kLo;
     x += x < 0 ? a.M[0] : x >= a.M[0] ? -a.M[0] : 0;
@@ -702,6 +715,12 @@ __global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
   const int i0 = lane / kW, j0 = lane % kW, i1 = in1 ? (lane + 64) / kW : 0,
             j1 = in1 ? (lane + 64) % kW : 0;
   const int r0 = (i0 * kRX + j0) * kRZ, r1 = (i1 * kRX + j1) * kRZ;
+  // wave_sum3 leaves the sums in lanes 0, 16 and 32
+  const bool writes = (lane & 15) == 0 && lane < 48;
+  const int axis = lane < 16 ? 0 : lane < 32 ? 2 : 1;
+  const double mL = a.mL[axis];
+  float* out = nullptr;
+  float v = 0.f, held = 0.f;
   const int wl = min(lane, 31);
   uint4 u = make_uint4(0, 0, 0, 0);
   float wv = 0.f, dw = 0.f;
@@ -715,7 +734,7 @@ __global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
   };
   fetch(s0 + w);
   __syncthreads();
-  for (int s = s0 + w; s < s1; s += 4) {
+  for (int s = s0 + w; s < s1; s += kForceThreads / 64) {
     const int64_t at = 3 * (int64_t)id;
     uint32_t f;
     const int l = ((grid_cell(u.x, a.M[0], f) % kTX) * kRX + grid_cell(u.y, a.M[1], f) % kTX) * kRZ +
@@ -730,7 +749,7 @@ __global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
                 dy0 = __shfl(dw, kW + j0);
     const float wx1 = __shfl(wv, i1), dx1 = __shfl(dw, i1), wy1 = __shfl(wv, kW + j1),
                 dy1 = __shfl(dw, kW + j1);
-    fetch(s + 4);
+    fetch(s + kForceThreads / 64);
     const float cm = s_c[l + (kLo * kRX + kLo) * kRZ + kLo];
     const float *ca = s_c + l + r0, *cb = s_c + l + r1;
     float p0[2] = {0.f, 0.f}, z0[2] = {0.f, 0.f}, p1[2] = {0.f, 0.f}, z1[2] = {0.f, 0.f};
@@ -749,17 +768,17 @@ __global__ __launch_bounds__(256) void k_em_force(EwMeshArgs a) {
     }
     const float pa = p0[0] + p0[1], pb = in1 ? p1[0] + p1[1] : 0.f;
     const float za = z0[0] + z0[1], zb = in1 ? z1[0] + z1[1] : 0.f;
-    float F[3] = {fmaf(dx0 * wy0, pa, dx1 * wy1 * pb), fmaf(wx0 * dy0, pa, wx1 * dy1 * pb),
-                  fmaf(wx0 * wy0, za, wx1 * wy1 * zb)};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) F[c] = wave_sum(F[c]);
-    if (lane < 3) {
-      const double g = (double)(lane == 0 ? F[0] : lane == 1 ? F[1] : F[2]);
-      const float v = (float)(g * a.mL[lane]);
-      float* out = a.force + at + lane;
-      *out = a.accumulate ? *out + v : v;
+    const float F = wave_sum3(fmaf(dx0 * wy0, pa, dx1 * wy1 * pb), fmaf(wx0 * dy0, pa, wx1 * dy1 * pb),
+                              fmaf(wx0 * wy0, za, wx1 * wy1 * zb));
+    if (writes) {
+      // added to what the buffer holds an atom later, when the load is back
+      if (out) *out = a.accumulate ? held + v : v;
+      out = a.force + at + axis;
+      v = (float)((double)F * mL);
+      if (a.accumulate) held = *out;
     }
   }
+  if (out) *out = a.accumulate ? held + v : v;
 }
 
 __global__ __launch_bounds__(256) void k_em_energy(EwMeshArgs a) {
@@ -901,7 +920,7 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   else hipLaunchKernelGGL(k_em_forward<3>, grid, wg, fb(3), st, a, gf);
   hipLaunchKernelGGL(k_em_middle, dim3((unsigned)(a.N[1] * a.N[2] / 16)), wg, (size_t)64 * a.N[0], st, a);
   hipLaunchKernelGGL(k_em_back, dim3((unsigned)(a.M[0] * gb)), wg, bb(rt), st, a, rt, gb);
-  hipLaunchKernelGGL(k_em_force, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_em_force, dim3((unsigned)pl.nbins), dim3(kForceThreads), 0, st, a);
   hipLaunchKernelGGL(k_em_energy, dim3(1), dim3(256), 0, st, a);
   return hipGetLastError();
 }
