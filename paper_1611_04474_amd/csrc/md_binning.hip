@@ -678,8 +678,59 @@ __device__ inline SortLds& sort_lds() {
   return l;
 }
 
+// Wrapped position and charge, type and sort key of atom i, a member of a cell in layer cz (as
+// put_atom leaves them for the in-cell sort).
+template <typename Real>
+__device__ inline P4<Real> read_atom(const SysArgs<Real>& a, int32_t i, int cz, int32_t& t,
+                                     unsigned long long& key) {
+  uint32_t st = 0;
+  P4<Real> p;
+  p.x = wrap_coord(a.pos_in[3 * (int64_t)i + 0], a.L[0], st);
+  p.y = wrap_coord(a.pos_in[3 * (int64_t)i + 1], a.L[1], st);
+  p.z = wrap_coord(a.pos_in[3 * (int64_t)i + 2], a.L[2], st);
+  p.w = a.q_in[i];
+  t = a.type_in[i];
+  if (t < 0 || t >= a.n_types) t = 0;
+  key = sort_key(a, i, (float)p.x, p.z, cz);
+  return p;
+}
+
+// Every atom's cell, by a workgroup of kSmallThreads threads: visit(i, cell) for each atom, the
+// loads of kSmallPer atoms per thread in flight; types are checked only where the status is
+// wanted.
+constexpr int kSmallThreads = 1024, kSmallPer = 2;
+template <bool kTypes, typename Real, typename Visit>
+__device__ inline uint32_t visit_atoms(const SysArgs<Real>& a, Visit visit) {
+  const int32_t n = (int32_t)a.n;
+  uint32_t st = 0;
+  for (int32_t r0 = 0; r0 < n; r0 += kSmallThreads * kSmallPer) {
+    Real x[kSmallPer], y[kSmallPer], z[kSmallPer];
+    int ty[kSmallPer];
+#pragma unroll
+    for (int u = 0; u < kSmallPer; ++u) {
+      if (r0 + u * kSmallThreads >= n) break;
+      // past the end: a repeat of the last atom, not visited
+      const int32_t i = min(r0 + u * kSmallThreads + (int32_t)threadIdx.x, n - 1);
+      x[u] = a.pos_in[3 * (int64_t)i + 0];
+      y[u] = a.pos_in[3 * (int64_t)i + 1];
+      z[u] = a.pos_in[3 * (int64_t)i + 2];
+      ty[u] = kTypes ? a.type_in[i] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kSmallPer; ++u) {
+      if (r0 + u * kSmallThreads >= n) break;
+      const int32_t i = r0 + u * kSmallThreads + (int32_t)threadIdx.x;
+      const int c = cell_from(a, x[u], y[u], z[u], ty[u], st);
+      if (i < n) visit(i, c);
+    }
+  }
+  return st;
+}
+
 // kNt: the outputs with streaming stores (grids of at most kScanFused cells: streaming).
-template <bool kNt, typename Real>
+// kSmall (k_bin_small): the workgroup, of kSmallThreads threads, finds its cell's members among
+// all atoms itself; its first kSortThreads threads sort them.
+template <bool kNt, bool kSmall, typename Real>
 __device__ inline void cell_sort(const SysArgs<Real>& a, int64_t c) {
   constexpr int kChunk = kSortChunk;
   constexpr int kPer = kChunk / kSortThreads;
@@ -693,13 +744,41 @@ __device__ inline void cell_sort(const SysArgs<Real>& a, int64_t c) {
   uint16_t* s_blist = L.blist;
   int32_t& s_low = L.low;
   int32_t& s_over = L.over;
-  const bool fused = scan_fused(a);
+  const bool fused = kSmall || scan_fused(a);
   const int t = threadIdx.x, lane = t & 63;
+  const int cz = (int)c / (a.nx * a.ny);
   int32_t s0, m;
   // the rank count's bucket counters, cleared before the first barrier
-  s_bcnt[t] = 0;
+  if (!kSmall || t < kSortThreads) s_bcnt[t] = 0;
   if (t == 0) s_over = 0;
-  if (fused) {
+  if constexpr (kSmall) {
+    // the members' indices, in any order (the keys rank them), in LDS, or for a cell of more
+    // than kChunk atoms in rank[s0 .. s0 + m) by a second pass; atoms of earlier cells counted
+    int32_t &s_m = s_tot[0], &s_before = s_tot[1], &s_again = s_tot[2];
+    if (t < 3) s_tot[t] = 0;
+    __syncthreads();
+    int32_t before = 0;
+    visit_atoms<false>(a, [&](int32_t i, int ci) {
+      before += ci < (int)c ? 1 : 0;
+      if (ci == (int)c) {
+        const int32_t at = atomicAdd(&s_m, 1);
+        if (at < kChunk) s_src[at] = i;
+      }
+    });
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+    if (lane == 0) atomicAdd(&s_before, before);
+    __syncthreads();
+    m = s_m;
+    s0 = s_before;
+    if (m > kChunk) {
+      visit_atoms<false>(a, [&](int32_t i, int ci) {
+        if (ci == (int)c) a.rank[s0 + atomicAdd(&s_again, 1)] = i;
+      });
+      __syncthreads();
+    }
+    if (t == 0) a.start[c] = s0;
+    if (t >= kSortThreads) return;   // whole waves: the barriers below are the others'
+  } else if (fused) {
     // block b's atoms of this cell are bhist[b][c + 1] - bhist[b][c] of its range, from
     // position b bin_chunk + bhist[b][c]; the cell starts at the sum over the blocks of
     // bhist[b][c] (the atoms in earlier cells). With at most 256 blocks every wave reads
@@ -776,6 +855,27 @@ __device__ inline void cell_sort(const SysArgs<Real>& a, int64_t c) {
   auto src = [&](int32_t e) -> int32_t {
     return !fused ? s0 + e : m <= kChunk ? s_src[e] : a.rank[s0 + e];
   };
+  auto member = [&](int32_t e, int32_t& ty, unsigned long long& key) -> P4<Real> {
+    const int32_t sp = src(e);
+    if constexpr (kSmall) {
+      return read_atom(a, sp, cz, ty, key);
+    } else {
+      const UKey u = a.ukey[sp];
+      key = u.key;
+      ty = u.type;
+      return a.upos[sp];
+    }
+  };
+  auto key_of = [&](int32_t e) -> unsigned long long {
+    if constexpr (kSmall) {
+      int32_t ty;
+      unsigned long long key;
+      member(e, ty, key);
+      return key;
+    } else {
+      return a.ukey[src(e)].key;
+    }
+  };
   const P4<Real> o = cell_centre(a, c);
   // the cell's x range (its lower face and width), for the rank count's buckets
   const Real cell_w = a.L[0] / (Real)a.nx;
@@ -796,15 +896,13 @@ __device__ inline void cell_sort(const SysArgs<Real>& a, int64_t c) {
     for (int k = 0; k < kPer; ++k) {
       const int32_t e = t + kSortThreads * k;
       const bool in = k < kk && e < m;
-      const int32_t sp = src(in ? e : 0);   // m >= 1 here: a valid member
-      const UKey u = a.ukey[sp];
-      my_key[k] = in ? u.key : ~0ull;
-      const P4<Real> p = a.upos[sp];
+      unsigned long long key;
+      const P4<Real> p = member(in ? e : 0, my_t[k], key);   // m >= 1 here: a valid member
+      my_key[k] = in ? key : ~0ull;
       px[k] = p.x;
       py[k] = p.y;
       pz[k] = p.z;
       pq[k] = p.w;
-      my_t[k] = u.type;
       my_rank[k] = 0;
     }
     // slots m .. kSortThreads kk - 1 (a multiple of 8) hold ~0, which is below no key
@@ -923,13 +1021,13 @@ __device__ inline void cell_sort(const SysArgs<Real>& a, int64_t c) {
     int32_t my_rank[kPer];
     for (int k = 0; k < kPer; ++k) {
       const int32_t e = a0 + t + kSortThreads * k;
-      my_key[k] = (k < kk && e < m) ? a.ukey[src(e)].key : ~0ull;
+      my_key[k] = (k < kk && e < m) ? key_of(e) : ~0ull;
       my_rank[k] = 0;
     }
     for (int32_t b0 = 0; b0 < m; b0 += kChunk) {
       const int32_t mb = min(kChunk, m - b0);
       __syncthreads();
-      for (int32_t e = t; e < mb; e += kSortThreads) s_key[e] = a.ukey[src(b0 + e)].key;
+      for (int32_t e = t; e < mb; e += kSortThreads) s_key[e] = key_of(b0 + e);
       for (int32_t e = mb + t; e < ((mb + 3) & ~3); e += kSortThreads) s_key[e] = ~0ull;
       __syncthreads();
       for (int32_t e = 0; e < mb; e += 4) {
@@ -947,9 +1045,9 @@ __device__ inline void cell_sort(const SysArgs<Real>& a, int64_t c) {
       count_low(&s_low, in && !(my_key[k] >> 63));
       if (!in) continue;
       const int32_t d = s0 + my_rank[k];
-      const int32_t sp = src(e);
-      const P4<Real> p = a.upos[sp];
-      const int32_t ty = a.ukey[sp].type;
+      int32_t ty;
+      unsigned long long key;
+      const P4<Real> p = member(e, ty, key);
       if constexpr (kNt) {
         store_nt(&a.pos[d], p);
         __builtin_nontemporal_store(ty, &a.type[d]);
@@ -1012,12 +1110,41 @@ __device__ inline void bin_tail(const SysArgs<Real>& a, const TypeTable& tt) {
 template <bool kNt, typename Real>
 __device__ inline void cell_sort_or_tail(const SysArgs<Real>& a, const TypeTable& tt, int64_t blk) {
   if (!scan_fused(a)) {
-    cell_sort<false>(a, blk);
+    cell_sort<false, false>(a, blk);
   } else if (blk == 0) {
     bin_tail(a, tt);
   } else {
-    cell_sort<kNt>(a, blk - 1);
+    cell_sort<kNt, false>(a, blk - 1);
   }
+}
+
+// The whole binning of a small system in one launch: workgroup 0 ends it (bin_tail), workgroup
+// c + 1 sorts cell c, and each finds what it needs among all atoms itself.
+template <typename Real>
+__global__ __launch_bounds__(kSmallThreads) void k_bin_small(SysArgs<Real> a, TypeTable tt) {
+  if (blockIdx.x > 0) {
+    cell_sort<true, true>(a, (int64_t)blockIdx.x - 1);
+    return;
+  }
+  SortLds& L = sort_lds();
+  uint32_t* s_k = reinterpret_cast<uint32_t*>(L.key);   // [n_cells] order keys
+  uint32_t* s_st = reinterpret_cast<uint32_t*>(&L.low);
+  const int t = threadIdx.x, nc = (int)a.n_cells;
+  const bool by_cost = have_costs(a);
+  if (t < nc) s_k[t] = 0;
+  if (t == 0) {
+    *s_st = 0;
+    a.start[nc] = (int32_t)a.n;
+  }
+  __syncthreads();
+  const uint32_t st = visit_atoms<true>(a, [&](int32_t, int c) {
+    if (!by_cost) atomicAdd(&s_k[c], 1u);
+  });
+  if (st) atomicOr(s_st, st);
+  if (by_cost && t < nc) s_k[t] = cost_key(a.cost[t]);
+  __syncthreads();
+  if (t >= kSortThreads) return;   // whole waves
+  scan_tail<kSortThreads>(a, tt, 1, L.tot, L.src, [&](int64_t c) { return s_k[c]; }, *s_st);
 }
 
 template <typename Real>
@@ -1059,8 +1186,25 @@ static bool streaming(int64_t n) {
   return n * (int64_t)(sizeof(Real) / 4) <= 131072;
 }
 
+// Whether one launch does the binning (k_bin_small): each of its workgroups reads every atom, which
+// costs less than the second launch as long as the atoms are few (whole calls with two launches
+// and with one: 2,000 atoms 44.0 and 39.6 us, 3,000 48.5 and 44.6, 6,000 49.0 and 46.6, 8,000
+// 53.1 and 52.3, 9,001 52.7 and 51.9, 10,000 61.5 and 61.8; float64 3,000 61.9 and 57.6; 6,000 in
+// 216 cells 44.7 and 41.9). Bound by latency and by the issue of n / 1024 atoms' cells per thread.
+// A batch keeps the two kernels, whose other systems hide the launch.
+constexpr int64_t kSmallAtoms = 9216, kSmallCells = 256;
+template <typename Real>
+static bool one_launch(const SysArgs<Real>& a) {
+  return a.n > 0 && a.bin_blocks > 0 && a.n <= kSmallAtoms && a.n_cells <= kSmallCells;
+}
+
 template <typename Real>
 hipError_t launch_binning(const SysArgs<Real>& a, const TypeTable& tt, hipStream_t stream) {
+  if (one_launch(a)) {
+    hipLaunchKernelGGL(k_bin_small<Real>, dim3((unsigned)(a.n_cells + 1)), dim3(kSmallThreads), 0, stream,
+                       a, tt);
+    return hipGetLastError();
+  }
   int own_header = 1;
   const bool nt = streaming<Real>(a.n);
   if (a.n > 0 && a.bin_blocks > 0) {
