@@ -314,6 +314,7 @@ SysArgs<Real> make_args(const md_params* p, const Plan& pl, int64_t n, const Rea
   a.fs_xsplit = fw.xsplit;
   a.fs_split = fw.split;
   a.fs_slices = a.fs_su = fw.slices;
+  a.fs_parts = fs_workgroups(a);
   return a;
 }
 

@@ -172,6 +172,7 @@ struct SysArgs {
                                //    or, float32 only, facc with MD_ACCUM_F32_ATOMIC)
   int half_shell;              // 1: the compacted kernel visits each pair once and adds
                                //    into acc64 with integer atomics (acc64 starts at zero)
+  int64_t fs_parts;            // energy partials of a call on its own (a batched one may write fewer)
   int64_t fs_nx;               // FsWork: cells of the other split, which ends of the launch
   int fs_xlong, fs_xsplit;     // order, and that split
   int fs_split;                // parts of the other cells' home atoms, a workgroup each

@@ -123,8 +123,11 @@ template <typename Real>
 __device__ inline void energy_fixed(const SysArgs<Real>& a, int64_t n_parts) {
   if (halve_diag(a) && threadIdx.x < 5) a.hdr->diag[threadIdx.x] /= 2;
   __shared__ long long s_hi[256], s_lo[256];
-  const long long* ep = reinterpret_cast<const long long*>(a.epart);
+  long long* ep = reinterpret_cast<long long*>(a.epart);
   constexpr bool f64 = sizeof(Real) == 8;
+  // those that a batched launch's fewer workgroups did not write
+  if (!f64)
+    for (int64_t t = n_parts + threadIdx.x; t < a.fs_parts; t += 256) ep[t] = 0;
   long long hi = 0, lo = 0;
   for (int64_t t = threadIdx.x; t < n_parts; t += 256) {
     if (f64) {

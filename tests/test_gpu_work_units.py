@@ -98,3 +98,33 @@ def test_batch_units_same_bits(gpu, sizes):
         torch.cuda.synchronize()
         for d, (f, e) in zip(systems, alone):
             assert torch.equal(d["force"], f) and torch.equal(d["energy"], e)
+
+
+def test_batched_energy_partials(gpu):
+    """A batched call may take fewer workgroups for a system than a call of its own: the energy
+    partials in its workspace still add up to the energy, all of them."""
+    import torch
+    systems = []
+    for k, (n, box) in enumerate([(3000, (30.0, 30.0, 30.0)), (4003, (73.5, 73.5, 61.5)),
+                                  (20000, (58.5, 58.5, 58.5)), (30000, (97.0, 97.0, 85.0))]):
+        s, p = _system(n, box, 3 + k)
+        P = api.Params.from_dict(p)
+        d = dict(params=P, pos=s.pos, types=s.types, charges=s.charges)
+        d = dict(d, **{x: torch.as_tensor(d[x]).to(gpu) for x in ("pos", "types", "charges")})
+        systems.append(dict(d, force=torch.empty((n, 3), dtype=torch.float32, device=gpu),
+                            energy=torch.empty(1, dtype=torch.float64, device=gpu),
+                            workspace=api.alloc_workspace(P, n, gpu)))
+
+    def check(d):
+        lay = api.workspace_layout(d["params"], d["pos"].shape[0])
+        at, m = lay["energy_partials"], lay["n_energy_partials"]
+        part = d["workspace"][at: at + 8 * m].view(torch.int64).cpu().numpy()
+        assert int(part.sum()) * 2.0 ** -24 == d["energy"].item()
+
+    for d in systems:   # alone first: what a batch leaves unwritten would be these
+        api.forces(d["params"], d["pos"], d["types"], d["charges"], force=d["force"], energy=d["energy"],
+                   workspace=d["workspace"])
+        check(d)
+    api.forces_batched(systems)
+    for d in systems:
+        check(d)
