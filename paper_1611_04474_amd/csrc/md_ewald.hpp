@@ -87,7 +87,7 @@ struct EwMeshArgs {
   int2* slot;          // [n] bin and place in it
   int* ids;            // [n] indices by bin
   int* sid;            // [n] indices by bin, in order
-  int* count;          // [nbins]
+  int* count;          // [nbins], pad words apart
   int* start;          // [nbins + 1]
   float* buf0;         // [Mx][My][Mz] charges, then the potential's coefficients
   float* buf1;         // [Mx][Ny][Nz] transformed along z and y
@@ -96,6 +96,7 @@ struct EwMeshArgs {
   double* epart;       // [nepart]
   double2* qpart;      // [qblocks] sum q^2, sum q
   int64_t nepart, qblocks, nbins;
+  int pad;
   int M[3], N[3], K[3], nt[3];
   double cb[3];        // the windows' shape: beta log2(e)
   double L[3], mL[3], alpha, coulomb_k, gscale;   // mL = M / L

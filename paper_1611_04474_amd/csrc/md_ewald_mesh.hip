@@ -26,7 +26,7 @@
 // that are not the bound. Kernels:
 //   k_em_init     tables, window transforms, counters
 //   k_em_setup    per atom: fractions, NaN check, partial sums of q^2 and q; bin count
-//   k_em_scan     bin starts;   k_em_scatter  atom indices to bins
+//   k_em_place    bin starts and atom indices to bins; many bins: k_em_scan, k_em_scatter
 //   k_em_sort     each bin in index order (so sums run in a fixed order)
 //   k_em_spread   b, one workgroup per tile of 8 x 8 x 16 grid points
 //   k_em_forward, k_em_middle, k_em_back   the axis transforms z y, x (Q and E) x, y z
@@ -44,10 +44,13 @@ constexpr int kW = 10;                  // window width in grid points
 constexpr int kTX = 8, kTZ = 16;        // tile: 8 x 8 x 16 grid points
 constexpr int kLo = kW / 2 - 1;         // an atom at grid cell l covers l - 4 .. l + 5
 constexpr int kHi = kW / 2;
-// Bin counters lie 32 bytes apart: atomics of neighbouring bins no longer wait for each other's
-// line (k_em_setup of 92,224 atoms in 2,268 bins 13.2 -> 7.4 us; 128 bytes apart 6.6, but the
-// largest grids have 700,000 bins to clear and scan).
-constexpr int kPad = 8;
+// Grids of at most kPlaceBins bins (EwMeshArgs::pad): the bin counters lie 32 bytes apart, so
+// that atomics of neighbouring bins do not wait for each other's line (k_em_setup of 92,224
+// atoms in 2,268 bins 13.2 -> 7.4 us; 128 bytes apart 6.6). With more bins the atomics spread
+// by themselves, and one workgroup scans the counts (100,000 atoms in 32,000 bins, whole sum:
+// 1142 us apart, 1128 packed).
+constexpr int kPad = 8, kPlaceBins = 4096;
+inline int64_t mesh_pad(int64_t nbins) { return nbins <= kPlaceBins ? kPad : 1; }
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 // The window phi(t) = exp(beta (sqrt(1 - x^2) - 1)), x = 2 t / w, and its derivative, for
@@ -93,7 +96,7 @@ __device__ inline int bin_of(const EwMeshArgs& a, uint4 u) {
 // cleared by every block.
 __global__ __launch_bounds__(256) void k_em_init(EwMeshArgs a, unsigned nb_tab) {
   const int64_t gt = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  for (int64_t i = gt; i < kPad * a.nbins; i += (int64_t)gridDim.x * 256) a.count[i] = 0;
+  for (int64_t i = gt; i < a.pad * a.nbins; i += (int64_t)gridDim.x * 256) a.count[i] = 0;
   if (gt == 0) a.hdr->status = 0;
   if (blockIdx.x < nb_tab) {
     int64_t e = gt;
@@ -146,7 +149,7 @@ __global__ __launch_bounds__(256) void k_em_setup(EwMeshArgs a) {
     uint32_t st = 0;
     const uint4 u = ew_fractions(a.pos, a.q, a.L, i, st);
     b = bin_of(a, u);
-    at = atomicAdd(&a.count[(int64_t)kPad * b], 1);   // on its way during the sums below
+    at = atomicAdd(&a.count[(int64_t)a.pad * b], 1);   // on its way during the sums below
     a.ups[i] = u;
     const double qi = (double)__uint_as_float(u.w);
     q2 = qi * qi;
@@ -178,7 +181,7 @@ __global__ __launch_bounds__(1024) void k_em_scan(EwMeshArgs a) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int64_t b = b0 + 4 * t + k;
-      v[k] = b < a.nbins ? a.count[kPad * b] : 0;
+      v[k] = b < a.nbins ? a.count[b] : 0;
       sum += v[k];
     }
     int inc = sum;
@@ -213,6 +216,46 @@ __global__ __launch_bounds__(256) void k_em_scatter(EwMeshArgs a) {
   if (i >= a.n) return;
   const int2 s = a.slot[i];
   a.ids[a.start[s.x] + s.y] = (int)i;
+}
+
+// Grids of at most kPlaceBins bins: every block scans the counts itself and then places its atoms,
+// which costs less than the launch of a scan between (92,224 atoms in 2,268 bins: 9.5 us for
+// both, 5.4 this way; the reciprocal call 151.5 -> 149.9). Block 0 writes the starts.
+constexpr int kPlaceThreads = 1024;
+__global__ __launch_bounds__(kPlaceThreads) void k_em_place(EwMeshArgs a) {
+  constexpr int kPer = kPlaceBins / kPlaceThreads, kNW = kPlaceThreads / 64;
+  __shared__ int s_start[kPlaceBins], s_w[kNW];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, nb = (int)a.nbins;
+  const int64_t i = (int64_t)blockIdx.x * kPlaceThreads + t;
+  const int2 s = i < a.n ? a.slot[i] : make_int2(0, 0);
+  int v[kPer], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int b = kPer * t + k;
+    v[k] = b < nb ? a.count[kPad * b] : 0;
+    sum += v[k];
+  }
+  int inc = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(inc, o);
+    if (lane >= o) inc += y;
+  }
+  if (lane == 63) s_w[w] = inc;
+  __syncthreads();
+  int ex = inc - sum;
+#pragma unroll
+  for (int k = 0; k < kNW; ++k) ex += k < w ? s_w[k] : 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int b = kPer * t + k;
+    s_start[b] = ex;
+    if (blockIdx.x == 0 && b < nb) a.start[b] = ex;
+    ex += v[k];
+  }
+  if (blockIdx.x == 0 && t == 0) a.start[nb] = (int)a.n;
+  __syncthreads();
+  if (i < a.n) a.ids[s_start[s.x] + s.y] = (int)i;
 }
 
 // One workgroup per bin: its atoms in index order, so that the spreading adds in a fixed order.
@@ -820,7 +863,7 @@ bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t d
   pl->off_slot = o;  o = al(o + 8 * nn);
   pl->off_ids = o;   o = al(o + 4 * nn);
   pl->off_sid = o;   o = al(o + 4 * nn);
-  pl->off_count = o; o = al(o + 4 * kPad * (size_t)pl->nbins);
+  pl->off_count = o; o = al(o + 4 * (size_t)(mesh_pad(pl->nbins) * pl->nbins));
   pl->off_start = o; o = al(o + 4 * (size_t)(pl->nbins + 1));
   const size_t M0 = pl->M[0], M1 = pl->M[1], M2 = pl->M[2], N0 = pl->N[0], N1 = pl->N[1], N2 = pl->N[2];
   pl->off_buf0 = o;  o = al(o + 4 * M0 * M1 * M2);
@@ -868,6 +911,7 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   a.nepart = pl.nepart;
   a.qblocks = pl.qblocks;
   a.nbins = pl.nbins;
+  a.pad = (int)mesh_pad(pl.nbins);
   a.alpha = p->ewald_alpha;
   a.coulomb_k = p->coulomb_k;
   double V = 1;
@@ -895,8 +939,13 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   const unsigned nb_tab = (unsigned)((entries + 255) / 256);
   hipLaunchKernelGGL(k_em_init, dim3(nb_tab + (unsigned)((modes + 3) / 4)), dim3(256), 0, st, a, nb_tab);
   hipLaunchKernelGGL(k_em_setup, dim3(nb), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(k_em_scan, dim3(1), dim3(1024), 0, st, a);
-  hipLaunchKernelGGL(k_em_scatter, dim3(nb), dim3(256), 0, st, a);
+  if (a.nbins <= kPlaceBins) {
+    hipLaunchKernelGGL(k_em_place, dim3((unsigned)((n + kPlaceThreads - 1) / kPlaceThreads)), dim3(kPlaceThreads),
+                       0, st, a);
+  } else {
+    hipLaunchKernelGGL(k_em_scan, dim3(1), dim3(1024), 0, st, a);
+    hipLaunchKernelGGL(k_em_scatter, dim3(nb), dim3(256), 0, st, a);
+  }
   hipLaunchKernelGGL(k_em_sort, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_em_spread, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
   // workgroups of the transforms: four per compute unit where the tiles allow it (with one, 288
