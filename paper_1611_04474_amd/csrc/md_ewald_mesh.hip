@@ -713,7 +713,7 @@ __device__ inline float wave_sum3(float x, float y, float z) {
   return t;
 }
 
-// Forces, one workgroup of 8 waves per tile: the potential's coefficients around the tile
+// Forces, one workgroup of 8 (4 on the largest grids) waves per tile: the potential's coefficients around the tile
 // (17 x 17 x 25 points) in LDS; a wave takes an atom of the tile's bin at a time, its lanes the
 // 100 (x, y) rows of the window (two rounds), each summing its row's 10 z values from both ends
 // with phi_z and phi_z' (uniform, in scalar registers). The coefficient at the atom's own grid
@@ -723,8 +723,8 @@ __device__ inline float wave_sum3(float x, float y, float z) {
 // component; 49.2 with one sum for the three; 46.9 with the buffer's old force read an atom
 // ahead; 39.7 with 8 waves (more than four workgroups do not fit a compute unit's LDS, and
 // four of 8 waves fill it; 10, 12 and 16 waves 47, 43 and 43).
-constexpr int kForceThreads = 512;
-__global__ __launch_bounds__(kForceThreads) void k_em_force(EwMeshArgs a) {
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_em_force(EwMeshArgs a) {
   constexpr int kRX = kTX + kW - 1, kRZ = kTZ + kW - 1;   // points around the tile
   constexpr int kQuads = (kRZ + 3) / 4;                   // 16-byte loads per row
   __shared__ float s_c[kRX * kRX * kRZ];
@@ -737,7 +737,7 @@ __global__ __launch_bounds__(kForceThreads) void k_em_force(EwMeshArgs a) {
   // straddles the box edge and is aligned
   static_assert(kLo == 4 && kTZ % 4 == 0, "aligned quads");
 #pragma unroll 4
-  for (int e = t; e < kRX * kRX * kQuads; e += kForceThreads) {
+  for (int e = t; e < kRX * kRX * kQuads; e += kThreads) {
     const int qd = e % kQuads, rw = e / kQuads;
     int x = rw / kRX + kTX * tx - kLo, y = rw % kRX + kTX * ty - kLo, z = 4 * qd + kTZ * tz - kLo;
     x += x < 0 ? a.M[0] : x >= a.M[0] ? -a.M[0] : 0;
@@ -777,7 +777,7 @@ __global__ __launch_bounds__(kForceThreads) void k_em_force(EwMeshArgs a) {
   };
   fetch(s0 + w);
   __syncthreads();
-  for (int s = s0 + w; s < s1; s += kForceThreads / 64) {
+  for (int s = s0 + w; s < s1; s += kThreads / 64) {
     const int64_t at = 3 * (int64_t)id;
     uint32_t f;
     const int l = ((grid_cell(u.x, a.M[0], f) % kTX) * kRX + grid_cell(u.y, a.M[1], f) % kTX) * kRZ +
@@ -792,7 +792,7 @@ __global__ __launch_bounds__(kForceThreads) void k_em_force(EwMeshArgs a) {
                 dy0 = __shfl(dw, kW + j0);
     const float wx1 = __shfl(wv, i1), dx1 = __shfl(dw, i1), wy1 = __shfl(wv, kW + j1),
                 dy1 = __shfl(dw, kW + j1);
-    fetch(s + kForceThreads / 64);
+    fetch(s + kThreads / 64);
     const float cm = s_c[l + (kLo * kRX + kLo) * kRZ + kLo];
     const float *ca = s_c + l + r0, *cb = s_c + l + r1;
     float p0[2] = {0.f, 0.f}, z0[2] = {0.f, 0.f}, p1[2] = {0.f, 0.f}, z1[2] = {0.f, 0.f};
@@ -969,7 +969,12 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   else hipLaunchKernelGGL(k_em_forward<3>, grid, wg, fb(3), st, a, gf);
   hipLaunchKernelGGL(k_em_middle, dim3((unsigned)(a.N[1] * a.N[2] / 16)), wg, (size_t)64 * a.N[0], st, a);
   hipLaunchKernelGGL(k_em_back, dim3((unsigned)(a.M[0] * gb)), wg, bb(rt), st, a, rt, gb);
-  hipLaunchKernelGGL(k_em_force, dim3((unsigned)pl.nbins), dim3(kForceThreads), 0, st, a);
+  // 8 waves a tile, but 4 on the largest grids, whose tiles hold a few atoms each while their
+  // staging reads past the caches: five workgroups of 4 waves fit a compute unit, four of 8.
+  // Whole sums with 8 and with 4: 92,224 atoms in 2,268 bins 149 and 156 us, 40,000 in 16,384 467
+  // and 479, 100,000 in 32,000 1128 and 1078, 30,000 in 32,000 959 and 962.
+  if (a.nbins > 24576) hipLaunchKernelGGL(k_em_force<256>, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(k_em_force<512>, dim3((unsigned)pl.nbins), dim3(512), 0, st, a);
   hipLaunchKernelGGL(k_em_energy, dim3(1), dim3(256), 0, st, a);
   return hipGetLastError();
 }

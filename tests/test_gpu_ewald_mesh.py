@@ -22,6 +22,7 @@ pytestmark = pytest.mark.gpu
     ("a bin of hundreds, bit map over two index ranges", 40000, (74.0, 71.0, 73.0), (14, 16, 15), 900),
     ("long axis: two column tiles a workgroup, the last one alone", 4000, (260.0, 22.0, 40.0), (170, 5, 20), 0),
     ("long axis: three column tiles, three row tiles", 300, (100.0, 30.0, 30.0), (150, 40, 40), 0),
+    ("over 24,576 tiles", 100, (30.0, 31.0, 32.0), (90, 90, 90), 0),
     ("outside the box, net charge", 12000, (48.0, 51.0, 50.0), (18, 18, 18), 0),
 ])
 def test_mesh_matches_oracle(gpu, case, n, box, kmax, crowd):
