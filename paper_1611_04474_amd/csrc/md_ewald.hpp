@@ -91,7 +91,7 @@ struct EwMeshArgs {
   int* start;          // [nbins + 1]
   float* buf0;         // [Mx][My][Mz] charges, then the potential's coefficients
   float* buf1;         // [Mx][Ny][Nz] transformed along z and y
-  float *tab[3], *tabT[3];   // [N][M] and [M][N] basis functions per axis
+  double *tab[3], *tabT[3];  // [N][M] and [M][N] basis functions per axis
   double *gfac[3], *ksq[3];  // [N] per axis: multiplicity exp(-k^2/4 alpha^2)/phihat^2; k^2
   double* epart;       // [nepart]
   double2* qpart;      // [qblocks] sum q^2, sum q

@@ -4,8 +4,8 @@
 // The charges are spread to a regular grid with a window wide enough that the gridding error
 // (3e-8 of the forces at an oversampling of 1.75, from a float64 comparison with the direct
 // sum) lies below float32 rounding, so this is not a particle-mesh approximation with an
-// accuracy to choose: results agree with the direct sum to its own rounding (see the
-// accuracy at launch_ew_mesh). With real separable basis functions t_n(l), n = 2 m + a:
+// accuracy to choose: forces and energy are no further from a float64 sum than the direct sum's
+// (see the accuracy at launch_ew_mesh). With real separable basis functions t_n(l), n = 2 m + a:
 // cos (a = 0) or sin (a = 1) of 2 pi m l / M, the pieces are
 //   b[l]    = sum_j q_j phi(l_x - X_j) phi(l_y - Y_j) phi(l_z - Z_j),   X = M_x u_x, ...
 //   R[n]    = sum_l b[l] t_nx(l_x) t_ny(l_y) t_nz(l_z)
@@ -22,7 +22,7 @@
 //
 // Grids have a few million points at most and only the modes |m| <= kmax are wanted, so the
 // transforms are products with a table of sines and cosines per axis on the matrix cores
-// (float32 MFMA), any grid size, a few GFLOP; a fast Fourier transform would save operations
+// (float64 MFMA), any grid size, a few GFLOP; a fast Fourier transform would save operations
 // that are not the bound. Kernels:
 //   k_em_init     tables, window transforms, counters
 //   k_em_setup    per atom: fractions, NaN check, partial sums of q^2 and q; bin count
@@ -52,27 +52,36 @@ constexpr int kHi = kW / 2;
 constexpr int kPad = 8, kPlaceBins = 4096;
 inline int64_t mesh_pad(int64_t nbins) { return nbins <= kPlaceBins ? kPad : 1; }
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 // The window phi(t) = exp(beta (sqrt(1 - x^2) - 1)), x = 2 t / w, and its derivative, for
 // t = r - f with r a whole number of grid points and f a 32-bit fraction (both exact); c =
-// beta log2(e). The exponent is formed in float64 (its root from a float32 one and a Newton
-// step; float64 FMAs issue at float32's rate here), so that phi carries little more than the
-// rounding of the hardware's 2^x: in float32 throughout the exponent's rounding alone put
-// 3e-7 into the forces.
+// beta log2(e). Formed in float64 and rounded once (the reciprocal root from a float32 one and a
+// Newton step, 2^h by the exponential series to h^8, 2e-10): the hardware's 2^x is a little low on
+// average, 2e-8 of the energy and 3e-8 of the forces over three axes (k_em_sort, which forms the
+// windows, 12.8 us with it, 14.0 without). In float32 throughout the exponent's
+// rounding alone put 3e-7 into the forces.
 __device__ inline float window(int r, uint32_t f, double c, float& d) {
   const double t = fma((double)f, -2.3283064365386963e-10, (double)r);   // 2^-32
   const double x = t * (2.0 / kW);
   const double y = fma(-x, x, 1.0);
-  const float yf = fmaxf((float)y, 1e-7f);
-  const float rs = __builtin_amdgcn_rsqf(yf);
-  const double s0 = (double)(yf * rs);
-  const double s = fma(fma(-s0, s0, y), (double)(0.5f * rs), s0);
-  const double g = c * (s - 1.0);
-  const float hi = (float)g, lo = (float)(g - (double)hi);
-  const float e = __builtin_amdgcn_exp2f(hi);
-  const float v = y > 1e-7 ? fmaf(e, lo * 0.6931472f, e) : 0.f;
-  d = v * ((float)(-x * (c * (0.6931471805599453 * 2.0 / kW))) * rs);
-  return v;
+  const float rs = __builtin_amdgcn_rsqf(fmaxf((float)y, 1e-7f));
+  const double r0 = (double)rs;
+  const double ri = fma(0.5 * r0, fma(-y * r0, r0, 1.0), r0);   // 1/sqrt(y)
+  const double g = c * fma(y, ri, -1.0);
+  const double k = rint(g), h = (g - k) * 0.6931471805599453;
+  double e = 1.0 / 40320.0;
+  e = fma(e, h, 1.0 / 5040.0);
+  e = fma(e, h, 1.0 / 720.0);
+  e = fma(e, h, 1.0 / 120.0);
+  e = fma(e, h, 1.0 / 24.0);
+  e = fma(e, h, 1.0 / 6.0);
+  e = fma(e, h, 0.5);
+  e = fma(e, h, 1.0);
+  e = fma(e, h, 1.0);
+  e = y > 1e-7 ? __builtin_amdgcn_ldexp(e, (int)k) : 0.0;
+  d = (float)(e * (-x * (c * (0.6931471805599453 * 2.0 / kW))) * ri);
+  return (float)e;
 }
 
 // Grid cell of a 32-bit fraction u on an axis of M points; f: the offset within it as a 32-bit
@@ -107,7 +116,7 @@ __global__ __launch_bounds__(256) void k_em_init(EwMeshArgs a, unsigned nb_tab) 
         const int m = n >> 1;
         double s = 0.0, c = 0.0;
         if (m <= a.K[d]) sincospi(2.0 * (double)(((int64_t)m * l) % a.M[d]) / (double)a.M[d], &s, &c);
-        const float v = (float)((n & 1) ? s : c);
+        const double v = (n & 1) ? s : c;
         a.tab[d][e] = v;                                   // [n][l]
         a.tabT[d][(int64_t)l * a.N[d] + n] = v;            // [l][n]
         return;
@@ -481,46 +490,45 @@ __global__ __launch_bounds__(256) void k_em_spread(EwMeshArgs a) {
   }
 }
 
-// Axis transforms. Each group of 16 k is summed by the matrix cores in float32 from zero and
-// the groups in float64 (float32 sums over whole lines put 2e-7 into the forces); the operands
-// of the next groups are on their way meanwhile. A lane's latency to memory, not the products
-// (1.2 GFLOP and 8 us for all six at 92,224 atoms), is what a transform takes its time for, so
-// each kernel does two of them: z and y of a plane, x forward and back of a column, y and z of a
-// plane, the intermediate (float32) in LDS. 92,224 atoms (grid 144 x 144 x 112, 80 x 80 x 64
-// modes): 60.1 us in six launches, 43.2 in these three.
+// Axis transforms, on the matrix cores in float64: with float32 products, summed in float64 by
+// groups of 16, the rounding of a group left noise of a grid point's width in the potential, which the
+// derivative multiplies by the points per wavelength (92,224 atoms 4.4e-7 in the forces, 1.4e-7
+// this way; 9,001 with twice the wave numbers they need 5.9e-7 and 1.9e-7), and float32 tables put
+// 7e-8 into the energy. A lane's latency to memory, not the products (1.2 GFLOP, 15 us for all
+// six at 92,224 atoms), is what a transform takes its time for, so each kernel does two of them: z
+// and y of a plane, x forward and back of a column, y and z of a plane, the intermediate (float32)
+// in LDS. 92,224 atoms (grid 144 x 144 x 112, 80 x 80 x 64 modes): 60.1 us in six launches of
+// float32 products, 43.2 in these three, 60.7 with float64 products and tables.
 constexpr int kTrWaves = 8, kTrThreads = 64 * kTrWaves;
 
 // (p + a 32-bit byte offset: one uniform base and a lane offset per load)
-__device__ inline float word_at(const float* p, uint32_t byte) {
-  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + byte);
+template <typename T>
+__device__ inline T word_at(const T* p, uint32_t byte) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + byte);
 }
 
 // 16 rows x 16 C columns, sum over K: step s of a group uses k0 + 4 (l / 16) + s for both sides;
 // fa(k) gives a lane its row's four consecutive k, fb(k, v) the columns of them. Each of four
 // (rows) and two (columns) groups' operands has registers of its own and is loaded again as soon
-// as it is used, so the loads of the following groups are always on their way.
+// as it is used, so the loads of the following groups are always on their way. In a 16x16x4 f64
+// product lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and holds D[l / 16 + 4 i][l % 16].
 template <int C, typename FA, typename FB>
-__device__ __attribute__((always_inline)) inline void rows_times(int K, FA fa, FB fb, double (&acc)[C][4]) {
+__device__ __attribute__((always_inline)) inline void rows_times(int K, FA fa, FB fb, v4d (&acc)[C]) {
   float4 av[4];
-  float bv[2][4][C];
+  double bv[2][4][C];
 #pragma unroll
   for (int g = 0; g < 4; ++g) av[g] = fa(min(16 * g, K - 16));
 #pragma unroll
   for (int g = 0; g < 2; ++g) fb(min(16 * g, K - 16), bv[g]);
   auto step = [&](int g, int k, bool more) __attribute__((always_inline)) {
     const float a4[4] = {av[g].x, av[g].y, av[g].z, av[g].w};
-    v4f d[C] = {};
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int c = 0; c < C; ++c)
-        d[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[s], bv[g & 1][s][c], d[c], 0, 0, 0);
+        acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a4[s], bv[g & 1][s][c], acc[c], 0, 0, 0);
     if (more) av[g] = fa(min(k + 64, K - 16));
     fb(min(k + 32, K - 16), bv[g & 1]);
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[c][i] += (double)d[c][i];
   };
   int k0 = 0;
   for (; k0 + 64 <= K; k0 += 64) {
@@ -532,12 +540,11 @@ __device__ __attribute__((always_inline)) inline void rows_times(int K, FA fa, F
     if (k0 + 16 * g < K) step(g, k0 + 16 * g, false);
 }
 
-// 16 rows x 16 columns, sum over K: step s of a group uses k0 + 4 s + l / 16; fa(k, s), fb(k, s)
-// give a lane its element of row and column k + 4 s. Operands of four groups on their way.
 template <typename FA, typename FB>
-__device__ __attribute__((always_inline)) inline void tile_times(int K, FA fa, FB fb, double (&acc)[4]) {
-  float av[4][4], bv[4][4];
-  auto load = [&](int k, float (&va)[4], float (&vb)[4]) __attribute__((always_inline)) {
+__device__ __attribute__((always_inline)) inline void tile_times(int K, FA fa, FB fb, v4d& acc) {
+  double av[4][4];
+  float bv[4][4];
+  auto load = [&](int k, double (&va)[4], float (&vb)[4]) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       va[s] = fa(k, s);
@@ -547,12 +554,10 @@ __device__ __attribute__((always_inline)) inline void tile_times(int K, FA fa, F
 #pragma unroll
   for (int g = 0; g < 4; ++g) load(min(16 * g, K - 16), av[g], bv[g]);
   auto step = [&](int g, int k, bool more) __attribute__((always_inline)) {
-    v4f d = {};
 #pragma unroll
-    for (int s = 0; s < 4; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(av[g][s], bv[g][s], d, 0, 0, 0);
+    for (int s = 0; s < 4; ++s)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[g][s], (double)bv[g][s], acc, 0, 0, 0);
     if (more) load(min(k + 64, K - 16), av[g], bv[g]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] += (double)d[i];
   };
   int k0 = 0;
   for (; k0 + 64 <= K; k0 += 64) {
@@ -576,33 +581,34 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
   const int M1 = a.M[1], M2 = a.M[2], N1 = a.N[1], N2 = a.N[2];
   const int c0 = (int)(blockIdx.x % groups) * C, nc = min(C, N2 / 16 - c0);
   for (int r = w; r < M1 / 16; r += kTrWaves) {
-    const float *ip = a.buf0 + (x * M1 + 16 * r) * M2, *tp = a.tabT[2] + 16 * c0;
-    const uint32_t io = 4 * (row * M2 + 4 * kk), to = 4 * (4 * kk * N2 + row);
-    double acc[C][4] = {};
+    const float* ip = a.buf0 + (x * M1 + 16 * r) * M2;
+    const double* tp = a.tabT[2] + 16 * c0;
+    const uint32_t io = 4 * (row * M2 + 4 * kk), to = 8 * (4 * kk * N2 + row);
+    v4d acc[C] = {};
     rows_times<C>(M2, [&](int k) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(ip) + (4u * k + io)); },
-                  [&](int k, float (&v)[4][C]) {
+                  [&](int k, double (&v)[4][C]) {
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
 #pragma unroll
-                      for (int c = 0; c < C; ++c) v[s][c] = word_at(tp, 4u * ((k + s) * N2 + 16 * min(c, nc - 1)) + to);
+                      for (int c = 0; c < C; ++c) v[s][c] = word_at(tp, 8u * ((k + s) * N2 + 16 * min(c, nc - 1)) + to);
                   }, acc);
 #pragma unroll
     for (int c = 0; c < C; ++c)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) s_m[(16 * r + 4 * kk + i) * kStride + 16 * c + row] = (float)acc[c][i];
+      for (int i = 0; i < 4; ++i) s_m[(16 * r + kk + 4 * i) * kStride + 16 * c + row] = (float)acc[c][i];
   }
   __syncthreads();
   for (int t = w; t < N1 / 16 * nc; t += kTrWaves) {
     const int i0 = t / nc * 16, c = t % nc;
-    const float* tp = a.tabT[1] + i0;
-    const uint32_t to = 4 * (kk * N1 + row);
+    const double* tp = a.tabT[1] + i0;
+    const uint32_t to = 8 * (kk * N1 + row);
     const float* bp = s_m + kk * kStride + 16 * c + row;
-    double acc[4] = {};
-    tile_times(M1, [&](int k, int s) { return word_at(tp, 4u * (k + 4 * s) * N1 + to); },
+    v4d acc = {};
+    tile_times(M1, [&](int k, int s) { return word_at(tp, 8u * (k + 4 * s) * N1 + to); },
                [&](int k, int s) { return bp[(k + 4 * s) * kStride]; }, acc);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      a.buf1[(x * N1 + i0 + 4 * kk + i) * N2 + 16 * (c0 + c) + row] = (float)acc[i];
+      a.buf1[(x * N1 + i0 + kk + 4 * i) * N2 + 16 * (c0 + c) + row] = (float)acc[i];
   }
 }
 
@@ -617,15 +623,16 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
   const int ny = (int)(j / a.N[2]), nz = (int)(j % a.N[2]);
   const double k2yz = a.ksq[1][ny] + a.ksq[2][nz];
   for (int t = w; t < N0 / 16; t += kTrWaves) {
-    const float *tp = a.tabT[0] + 16 * t, *ip = a.buf1 + (int64_t)blockIdx.x * 16;
-    const uint32_t to = 4 * (kk * N0 + row), io = 4 * (kk * (uint32_t)J + row);
-    double acc[4] = {};
-    tile_times(M0, [&](int k, int s) { return word_at(tp, 4u * (k + 4 * s) * N0 + to); },
+    const double* tp = a.tabT[0] + 16 * t;
+    const float* ip = a.buf1 + (int64_t)blockIdx.x * 16;
+    const uint32_t to = 8 * (kk * N0 + row), io = 4 * (kk * (uint32_t)J + row);
+    v4d acc = {};
+    tile_times(M0, [&](int k, int s) { return word_at(tp, 8u * (k + 4 * s) * N0 + to); },
                [&](int k, int s) { return word_at(ip, 4u * (k + 4 * s) * (uint32_t)J + io); }, acc);
     double e = 0.0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int nx = 16 * t + 4 * kk + i;
+      const int nx = 16 * t + kk + 4 * i;
       const double k2 = a.ksq[0][nx] + k2yz;
       const double g = k2 > 0.0 ? a.gscale * a.gfac[0][nx] * a.gfac[1][ny] * a.gfac[2][nz] / k2 : 0.0;
       const double q = g * acc[i];
@@ -637,14 +644,14 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
   }
   __syncthreads();
   for (int t = w; t < M0 / 16; t += kTrWaves) {
-    const float* tp = a.tab[0] + 16 * t;
-    const uint32_t to = 4 * (kk * M0 + row);
+    const double* tp = a.tab[0] + 16 * t;
+    const uint32_t to = 8 * (kk * M0 + row);
     const float* bp = s_q + kk * 16 + row;
-    double acc[4] = {};
-    tile_times(N0, [&](int k, int s) { return word_at(tp, 4u * (k + 4 * s) * M0 + to); },
+    v4d acc = {};
+    tile_times(N0, [&](int k, int s) { return word_at(tp, 8u * (k + 4 * s) * M0 + to); },
                [&](int k, int s) { return bp[(k + 4 * s) * 16]; }, acc);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a.buf1[(16 * t + 4 * kk + i) * J + j] = (float)acc[i];
+    for (int i = 0; i < 4; ++i) a.buf1[(16 * t + kk + 4 * i) * J + j] = (float)acc[i];
   }
 }
 
@@ -658,35 +665,36 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
   const int r0 = (int)(blockIdx.x % groups) * rt, nr = min(rt, M1 / 16 - r0);
   for (int t = w; t < nr * (N2 / 16); t += kTrWaves) {
     const int r = t / (N2 / 16), c = t % (N2 / 16);
-    const float *tp = a.tab[1] + 16 * (r0 + r), *ip = a.buf1 + x * N1 * N2 + 16 * c;
-    const uint32_t to = 4 * (kk * M1 + row), io = 4 * (kk * N2 + row);
-    double acc[4] = {};
-    tile_times(N1, [&](int k, int s) { return word_at(tp, 4u * (k + 4 * s) * M1 + to); },
+    const double* tp = a.tab[1] + 16 * (r0 + r);
+    const float* ip = a.buf1 + x * N1 * N2 + 16 * c;
+    const uint32_t to = 8 * (kk * M1 + row), io = 4 * (kk * N2 + row);
+    v4d acc = {};
+    tile_times(N1, [&](int k, int s) { return word_at(tp, 8u * (k + 4 * s) * M1 + to); },
                [&](int k, int s) { return word_at(ip, 4u * (k + 4 * s) * N2 + io); }, acc);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s_r[(16 * r + 4 * kk + i) * S + 16 * c + row] = (float)acc[i];
+    for (int i = 0; i < 4; ++i) s_r[(16 * r + kk + 4 * i) * S + 16 * c + row] = (float)acc[i];
   }
   __syncthreads();
   const int jt = (M2 + 63) / 64;
   for (int t = w; t < nr * jt; t += kTrWaves) {
     const int r = t / jt, j0 = t % jt * 64, nj = min(4, (M2 - j0) / 16);
     const float* ap = s_r + (16 * r + row) * S + 4 * kk;
-    const float* tp = a.tab[2] + j0;
-    const uint32_t to = 4 * (4 * kk * M2 + row);
-    double acc[4][4] = {};
+    const double* tp = a.tab[2] + j0;
+    const uint32_t to = 8 * (4 * kk * M2 + row);
+    v4d acc[4] = {};
     rows_times<4>(N2, [&](int k) { return *reinterpret_cast<const float4*>(ap + k); },
-                  [&](int k, float (&v)[4][4]) {
+                  [&](int k, double (&v)[4][4]) {
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
 #pragma unroll
-                      for (int c = 0; c < 4; ++c) v[s][c] = word_at(tp, 4u * ((k + s) * M2 + 16 * min(c, nj - 1)) + to);
+                      for (int c = 0; c < 4; ++c) v[s][c] = word_at(tp, 8u * ((k + s) * M2 + 16 * min(c, nj - 1)) + to);
                   }, acc);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       if (c >= nj) break;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        a.buf0[(x * M1 + 16 * (r0 + r) + 4 * kk + i) * M2 + j0 + 16 * c + row] = (float)acc[c][i];
+        a.buf0[(x * M1 + 16 * (r0 + r) + kk + 4 * i) * M2 + j0 + 16 * c + row] = (float)acc[c][i];
     }
   }
 }
@@ -870,8 +878,8 @@ bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t d
   pl->off_buf1 = o;  o = al(o + 4 * M0 * N1 * N2);
   for (int d = 0; d < 3; ++d) {
     const size_t e = (size_t)pl->N[d] * pl->M[d];
-    pl->off_tab[d] = o;  o = al(o + 4 * e);
-    pl->off_tabT[d] = o; o = al(o + 4 * e);
+    pl->off_tab[d] = o;  o = al(o + 8 * e);
+    pl->off_tabT[d] = o; o = al(o + 8 * e);
     pl->off_gfac[d] = o; o = al(o + 8 * (size_t)pl->N[d]);
     pl->off_ksq[d] = o;  o = al(o + 8 * (size_t)pl->N[d]);
   }
@@ -924,8 +932,8 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
     a.L[d] = (double)(float)p->box[d];   // the float32 box
     a.mL[d] = (double)pl.M[d] / a.L[d];
     V *= a.L[d];
-    a.tab[d] = (float*)(b + pl.off_tab[d]);
-    a.tabT[d] = (float*)(b + pl.off_tabT[d]);
+    a.tab[d] = (double*)(b + pl.off_tab[d]);
+    a.tabT[d] = (double*)(b + pl.off_tabT[d]);
     a.gfac[d] = (double*)(b + pl.off_gfac[d]);
     a.ksq[d] = (double*)(b + pl.off_ksq[d]);
     entries += (int64_t)pl.N[d] * pl.M[d];
@@ -949,12 +957,14 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   hipLaunchKernelGGL(k_em_sort, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_em_spread, dim3((unsigned)pl.nbins), dim3(256), 0, st, a);
   // workgroups of the transforms: four per compute unit where the tiles allow it (with one, 288
-  // workgroups, 45 us for all three; with four 43), at most three tiles each (the registers of a
-  // wave's columns) and 64 KB of LDS (a kmax of 255 makes an axis of 896 points and 512 modes)
+  // workgroups, 45 us for all three; with four 43, float32 products), at most two column tiles or
+  // three row tiles each (with three column tiles 21 registers of k_em_forward spill: kmax (150, 40,
+  // 40) 492 us for the whole sum, 471 with two) and 64 KB of LDS (a kmax of 255 makes an axis of 896
+  // points and 512 modes)
   const int need = (1024 + a.M[0] - 1) / a.M[0];
-  auto share = [&](int tiles, auto bytes, int& groups) {
+  auto share = [&](int tiles, int most, auto bytes, int& groups) {
     int c = (tiles + need - 1) / need;
-    c = c > 3 ? 3 : c;
+    c = c > most ? most : c;
     while (c > 1 && bytes(c) > 65536) --c;
     groups = (tiles + c - 1) / c;
     return (tiles + groups - 1) / groups;
@@ -962,11 +972,10 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   int gf, gb;
   auto fb = [&](int c) { return (size_t)64 * a.M[1] * (c | 1); };
   auto bb = [&](int c) { return (size_t)64 * c * (a.N[2] + 4); };
-  const int cf = share(a.N[2] / 16, fb, gf), rt = share(a.M[1] / 16, bb, gb);
+  const int cf = share(a.N[2] / 16, 2, fb, gf), rt = share(a.M[1] / 16, 3, bb, gb);
   const dim3 grid((unsigned)(a.M[0] * gf)), wg(kTrThreads);
   if (cf == 1) hipLaunchKernelGGL(k_em_forward<1>, grid, wg, fb(1), st, a, gf);
-  else if (cf == 2) hipLaunchKernelGGL(k_em_forward<2>, grid, wg, fb(2), st, a, gf);
-  else hipLaunchKernelGGL(k_em_forward<3>, grid, wg, fb(3), st, a, gf);
+  else hipLaunchKernelGGL(k_em_forward<2>, grid, wg, fb(2), st, a, gf);
   hipLaunchKernelGGL(k_em_middle, dim3((unsigned)(a.N[1] * a.N[2] / 16)), wg, (size_t)64 * a.N[0], st, a);
   hipLaunchKernelGGL(k_em_back, dim3((unsigned)(a.M[0] * gb)), wg, bb(rt), st, a, rt, gb);
   // 8 waves a tile, but 4 on the largest grids, whose tiles hold a few atoms each while their
