@@ -67,9 +67,9 @@ struct EwMeshPlan {
   int K[3], N[3], M[3], nt[3];  // kmax; basis functions (2 (K + 1) up to a multiple of 16); grid
                                 // points; tiles
   int64_t nbins, nepart, qblocks;
-  size_t off_ups, off_rec, off_win, off_dwin, off_slot, off_ids, off_sid, off_count, off_start, off_buf0, off_buf1,
-      off_tab[3], off_tabT[3], off_gfac[3], off_ksq[3], off_epart, off_qpart,
-      total;
+  size_t off_ups, off_rec, off_win, off_dwin, off_slot, off_ids, off_sid, off_count, off_start,
+      off_buf0, off_buf1, off_buf2, off_tab[3], off_tabT[3], off_gfac[3], off_ksq[3], off_epart,
+      off_qpart, total;
 };
 
 struct EwMeshArgs {
@@ -90,7 +90,8 @@ struct EwMeshArgs {
   int* count;          // [nbins], pad words apart
   int* start;          // [nbins + 1]
   float* buf0;         // [Mx][My][Mz] charges, then the potential's coefficients
-  float* buf1;         // [Mx][Ny][Nz] transformed along z and y
+  float* buf1;         // [Mx][Ny][Nz] charges transformed along z and y
+  double* buf2;        // the same of the potential, transformed back along x
   double *tab[3], *tabT[3];  // [N][M] and [M][N] basis functions per axis
   double *gfac[3], *ksq[3];  // [N] per axis: multiplicity exp(-k^2/4 alpha^2)/phihat^2; k^2
   double* epart;       // [nepart]

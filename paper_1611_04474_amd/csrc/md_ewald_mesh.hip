@@ -490,15 +490,18 @@ __global__ __launch_bounds__(256) void k_em_spread(EwMeshArgs a) {
   }
 }
 
-// Axis transforms, on the matrix cores in float64: with float32 products, summed in float64 by
+// Axis transforms, on the matrix cores in float64. With float32 products, summed in float64 by
 // groups of 16, the rounding of a group left noise of a grid point's width in the potential, which the
-// derivative multiplies by the points per wavelength (92,224 atoms 4.4e-7 in the forces, 1.4e-7
-// this way; 9,001 with twice the wave numbers they need 5.9e-7 and 1.9e-7), and float32 tables put
-// 7e-8 into the energy. A lane's latency to memory, not the products (1.2 GFLOP, 15 us for all
+// derivative multiplies by the points per wavelength, and float32 tables put 7e-8 into the energy;
+// the potential's intermediates are kept in float64 too, since noise along one axis alone counts
+// four times that of the stored grid, which the window averages over the other two. RMS force
+// error, float32 products, float64 ones, and float64 intermediates: 92,224 atoms 4.4e-7, 1.4e-7, 8.4e-8; 9,001
+// with twice the wave numbers they need 5.9e-7, 1.8e-7, 9.4e-8; 2,018 with six times 1.9e-7 and 1.0e-7.
+// A lane's latency to memory, not the products (1.2 GFLOP, 15 us for all
 // six at 92,224 atoms), is what a transform takes its time for, so each kernel does two of them: z
-// and y of a plane, x forward and back of a column, y and z of a plane, the intermediate (float32)
-// in LDS. 92,224 atoms (grid 144 x 144 x 112, 80 x 80 x 64 modes): 60.1 us in six launches of
-// float32 products, 43.2 in these three, 60.7 with float64 products and tables.
+// and y of a plane, x forward and back of a column, y and z of a plane, the intermediate in LDS.
+// 92,224 atoms (grid 144 x 144 x 112, 80 x 80 x 64 modes): 60.1 us in six launches of
+// float32 products, 43.2 in these three, 60.3 in float64.
 constexpr int kTrWaves = 8, kTrThreads = 64 * kTrWaves;
 
 // (p + a 32-bit byte offset: one uniform base and a lane offset per load)
@@ -507,44 +510,49 @@ __device__ inline T word_at(const T* p, uint32_t byte) {
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + byte);
 }
 
-// 16 rows x 16 C columns, sum over K: step s of a group uses k0 + 4 (l / 16) + s for both sides;
-// fa(k) gives a lane its row's four consecutive k, fb(k, v) the columns of them. Each of four
-// (rows) and two (columns) groups' operands has registers of its own and is loaded again as soon
-// as it is used, so the loads of the following groups are always on their way. In a 16x16x4 f64
-// product lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and holds D[l / 16 + 4 i][l % 16].
-template <int C, typename FA, typename FB>
+// 16 rows x 16 C columns, sum over K: step s of a group of 16 k uses k0 + 4 (l / 16) + s for both
+// sides; fa(k) gives a lane its row's four consecutive k (a float4 or double4), fb(k, v) the columns of
+// them. Each of A (rows) and two (columns) groups' operands has registers of its own and is loaded
+// again as soon as it is used, so the loads of the following groups are always on their way. In a
+// 16x16x4 f64 product lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and holds
+// D[l / 16 + 4 i][l % 16].
+template <int C, int A, typename FA, typename FB>
 __device__ __attribute__((always_inline)) inline void rows_times(int K, FA fa, FB fb, v4d (&acc)[C]) {
-  float4 av[4];
+  decltype(fa(0)) av[A];
   double bv[2][4][C];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) av[g] = fa(min(16 * g, K - 16));
+  for (int g = 0; g < A; ++g) av[g] = fa(min(16 * g, K - 16));
 #pragma unroll
   for (int g = 0; g < 2; ++g) fb(min(16 * g, K - 16), bv[g]);
-  auto step = [&](int g, int k, bool more) __attribute__((always_inline)) {
-    const float a4[4] = {av[g].x, av[g].y, av[g].z, av[g].w};
+  auto step = [&](int g, int k) __attribute__((always_inline)) {
+    const double a4[4] = {(double)av[g % A].x, (double)av[g % A].y, (double)av[g % A].z, (double)av[g % A].w};
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int c = 0; c < C; ++c)
-        acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a4[s], bv[g & 1][s][c], acc[c], 0, 0, 0);
-    if (more) av[g] = fa(min(k + 64, K - 16));
+        acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a4[s], bv[g & 1][s][c], acc[c], 0, 0, 0);
+    av[g % A] = fa(min(k + 16 * A, K - 16));
     fb(min(k + 32, K - 16), bv[g & 1]);
   };
   int k0 = 0;
   for (; k0 + 64 <= K; k0 += 64) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) step(g, k0 + 16 * g, true);
+    for (int g = 0; g < 4; ++g) step(g, k0 + 16 * g);
   }
 #pragma unroll
   for (int g = 0; g < 3; ++g)
-    if (k0 + 16 * g < K) step(g, k0 + 16 * g, false);
+    if (k0 + 16 * g < K) step(g, k0 + 16 * g);
 }
 
+// 16 rows x 16 columns, sum over K: step s of a group uses k0 + 4 s + l / 16; fa(k, s), fb(k, s)
+// give a lane its element of row and column k + 4 s. Operands of four groups on their way.
 template <typename FA, typename FB>
 __device__ __attribute__((always_inline)) inline void tile_times(int K, FA fa, FB fb, v4d& acc) {
-  double av[4][4];
-  float bv[4][4];
-  auto load = [&](int k, double (&va)[4], float (&vb)[4]) __attribute__((always_inline)) {
+  typedef decltype(fa(0, 0)) TA;
+  typedef decltype(fb(0, 0)) TB;
+  TA av[4][4];
+  TB bv[4][4];
+  auto load = [&](int k, TA (&va)[4], TB (&vb)[4]) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       va[s] = fa(k, s);
@@ -556,7 +564,7 @@ __device__ __attribute__((always_inline)) inline void tile_times(int K, FA fa, F
   auto step = [&](int g, int k, bool more) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[g][s], (double)bv[g][s], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[g][s], (double)bv[g][s], acc, 0, 0, 0);
     if (more) load(min(k + 64, K - 16), av[g], bv[g]);
   };
   int k0 = 0;
@@ -585,7 +593,7 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
     const double* tp = a.tabT[2] + 16 * c0;
     const uint32_t io = 4 * (row * M2 + 4 * kk), to = 8 * (4 * kk * N2 + row);
     v4d acc[C] = {};
-    rows_times<C>(M2, [&](int k) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(ip) + (4u * k + io)); },
+    rows_times<C, 4>(M2, [&](int k) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(ip) + (4u * k + io)); },
                   [&](int k, double (&v)[4][C]) {
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
@@ -613,7 +621,7 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
 }
 
 // x forward, the scaling of R to Q in float64 with the energy 1/2 sum Q R (a part per 16 x 16
-// tile), and x back: workgroup j of 16 columns (ny, nz), in place.
+// tile), and x back: workgroup j of 16 columns (ny, nz).
 __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_em_middle(EwMeshArgs a) {
   extern __shared__ __attribute__((aligned(16))) float s_q[];   // [N0][16]
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -651,13 +659,13 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
     tile_times(N0, [&](int k, int s) { return word_at(tp, 8u * (k + 4 * s) * M0 + to); },
                [&](int k, int s) { return bp[(k + 4 * s) * 16]; }, acc);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a.buf1[(16 * t + kk + 4 * i) * J + j] = (float)acc[i];
+    for (int i = 0; i < 4; ++i) a.buf2[(16 * t + kk + 4 * i) * J + j] = acc[i];
   }
 }
 
 // y and z back: workgroup (x, group of up to rt 16-row tiles of y).
 __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_em_back(EwMeshArgs a, int rt, int groups) {
-  extern __shared__ __attribute__((aligned(16))) float s_r[];   // [16 rt][N2 + 4]
+  extern __shared__ __attribute__((aligned(16))) double s_r[];   // [16 rt][N2 + 4]
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int row = lane & 15, kk = lane >> 4;
   const int64_t x = blockIdx.x / groups;
@@ -666,23 +674,23 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
   for (int t = w; t < nr * (N2 / 16); t += kTrWaves) {
     const int r = t / (N2 / 16), c = t % (N2 / 16);
     const double* tp = a.tab[1] + 16 * (r0 + r);
-    const float* ip = a.buf1 + x * N1 * N2 + 16 * c;
-    const uint32_t to = 8 * (kk * M1 + row), io = 4 * (kk * N2 + row);
+    const double* ip = a.buf2 + x * N1 * N2 + 16 * c;
+    const uint32_t to = 8 * (kk * M1 + row), io = 8 * (kk * N2 + row);
     v4d acc = {};
     tile_times(N1, [&](int k, int s) { return word_at(tp, 8u * (k + 4 * s) * M1 + to); },
-               [&](int k, int s) { return word_at(ip, 4u * (k + 4 * s) * N2 + io); }, acc);
+               [&](int k, int s) { return word_at(ip, 8u * (k + 4 * s) * N2 + io); }, acc);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s_r[(16 * r + kk + 4 * i) * S + 16 * c + row] = (float)acc[i];
+    for (int i = 0; i < 4; ++i) s_r[(16 * r + kk + 4 * i) * S + 16 * c + row] = acc[i];
   }
   __syncthreads();
   const int jt = (M2 + 63) / 64;
   for (int t = w; t < nr * jt; t += kTrWaves) {
     const int r = t / jt, j0 = t % jt * 64, nj = min(4, (M2 - j0) / 16);
-    const float* ap = s_r + (16 * r + row) * S + 4 * kk;
+    const double* ap = s_r + (16 * r + row) * S + 4 * kk;
     const double* tp = a.tab[2] + j0;
     const uint32_t to = 8 * (4 * kk * M2 + row);
     v4d acc[4] = {};
-    rows_times<4>(N2, [&](int k) { return *reinterpret_cast<const float4*>(ap + k); },
+    rows_times<4, 2>(N2, [&](int k) { return *reinterpret_cast<const double4*>(ap + k); },
                   [&](int k, double (&v)[4][4]) {
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
@@ -876,6 +884,7 @@ bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t d
   const size_t M0 = pl->M[0], M1 = pl->M[1], M2 = pl->M[2], N0 = pl->N[0], N1 = pl->N[1], N2 = pl->N[2];
   pl->off_buf0 = o;  o = al(o + 4 * M0 * M1 * M2);
   pl->off_buf1 = o;  o = al(o + 4 * M0 * N1 * N2);
+  pl->off_buf2 = o;  o = al(o + 8 * M0 * N1 * N2);
   for (int d = 0; d < 3; ++d) {
     const size_t e = (size_t)pl->N[d] * pl->M[d];
     pl->off_tab[d] = o;  o = al(o + 8 * e);
@@ -914,6 +923,7 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   a.start = (int*)(b + pl.off_start);
   a.buf0 = (float*)(b + pl.off_buf0);
   a.buf1 = (float*)(b + pl.off_buf1);
+  a.buf2 = (double*)(b + pl.off_buf2);
   a.epart = (double*)(b + pl.off_epart);
   a.qpart = (double2*)(b + pl.off_qpart);
   a.nepart = pl.nepart;
@@ -971,7 +981,7 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   };
   int gf, gb;
   auto fb = [&](int c) { return (size_t)64 * a.M[1] * (c | 1); };
-  auto bb = [&](int c) { return (size_t)64 * c * (a.N[2] + 4); };
+  auto bb = [&](int c) { return (size_t)128 * c * (a.N[2] + 4); };
   const int cf = share(a.N[2] / 16, 2, fb, gf), rt = share(a.M[1] / 16, 3, bb, gb);
   const dim3 grid((unsigned)(a.M[0] * gf)), wg(kTrThreads);
   if (cf == 1) hipLaunchKernelGGL(k_em_forward<1>, grid, wg, fb(1), st, a, gf);

@@ -85,3 +85,23 @@ def test_grid_form_keeps_float32_accuracy(gpu, case, n, box, alpha, kmax):
     print("RMS force error", rms, "energy", e, flush=True)
     assert rms <= 2.0 ** -22
     assert e <= 2.0 ** -25
+
+
+@pytest.mark.parametrize("case,n,box,kmax", [
+    ("fewest tiles per axis, unequal", 30000, (50.0, 62.0, 40.0), (8, 9, 46)),
+    ("one axis without modes", 60001, (70.0, 76.0, 90.0), (60, 0, 50)),
+    ("long axis: two column tiles a workgroup, the last one alone", 22880, (260.0, 22.0, 40.0), (170, 5, 20)),
+    ("long axis: two column tiles, three row tiles", 9000, (100.0, 30.0, 30.0), (150, 40, 40)),
+    ("over 4,096 tiles: bins scanned by a kernel of their own", 2000, (30.0, 31.0, 32.0), (50, 50, 50)),
+    ("over 24,576 tiles: four waves a tile", 2100, (30.0, 31.0, 32.0), (90, 90, 90)),
+])
+def test_grid_form_branches(gpu, case, n, box, kmax):
+    """The grid form's launch shapes, at sizes that take it. The bar grows with the wave numbers
+    beyond twice what alpha needs (exp(-k^2/4 alpha^2) = 1e-6), as the potential's share does."""
+    print("case:", case, n, box, kmax, flush=True)
+    alpha = 0.3
+    beyond = max(k * math.pi / (alpha * L * math.sqrt(-math.log(1e-6))) for k, L in zip(kmax, box))
+    rms, e = errors(gpu, n, box, alpha, kmax)
+    print("RMS force error", rms, "energy", e, "kmax over need", beyond, flush=True)
+    assert rms <= 2.0 ** -22 * max(1.0, beyond / 2)
+    assert e <= 2.0 ** -25
