@@ -217,8 +217,8 @@ md_status md_forces_f64(const md_params* p, int64_t n_atoms, const double* d_pos
  * -dE/dr_i. alpha is p->ewald_alpha (> 0); the box is p->box rounded to float32, r_cut and
  * the type table are not used. Each atom's phase is exact modulo one turn (32-bit
  * fixed-point fractional coordinates); sums run in float32 within tiles and float64
- * across them, in a fixed order. Larger systems (from 1.5e8 products of atoms and half-space
- * wave vectors) are summed through a grid, to the direct sum's own rounding.
+ * across them, in a fixed order. Larger systems with many wave vectors (from about 2,000 atoms
+ * on, by n_atoms and kmax alone) are summed through a grid, to the same accuracy or better.
  *   d_pos     [n_atoms][3] float32, any coordinates (the sum is periodic)
  *   d_charge  [n_atoms] float32
  *   kmax      host int32[3], each 0..255, not all 0

@@ -480,8 +480,10 @@ extern "C" {
 size_t md_ewald_workspace_bytes(const md_params* p, int64_t n_atoms, const int32_t kmax[3]) {
   md::EwPlan pl;
   if (md::ew_plan(p, n_atoms, kmax, &pl) != MD_OK) return 0;
+  if (n_atoms < md::ew_mesh_from(kmax)) return pl.total;
   md::EwMeshPlan mesh;
-  return md::ew_mesh_plan(p, n_atoms, kmax, pl.total, &mesh) ? mesh.total : pl.total;
+  md::ew_mesh_plan(n_atoms, kmax, &mesh);
+  return mesh.total;
 }
 
 md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d_pos,
@@ -496,7 +498,8 @@ md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d
                       (((uintptr_t)d_pos | (uintptr_t)d_charge | (uintptr_t)d_force) & 3)))
     return MD_ERR_INVALID_ARG;
   md::EwMeshPlan mesh;
-  const bool grid = md::ew_mesh_plan(p, n_atoms, kmax, pl.total, &mesh);
+  const bool grid = n_atoms >= md::ew_mesh_from(kmax);
+  if (grid) md::ew_mesh_plan(n_atoms, kmax, &mesh);
   if (!d_ws || ((uintptr_t)d_ws & 255) || ws_bytes < (grid ? mesh.total : pl.total))
     return MD_ERR_WORKSPACE;
   if (grid)

@@ -103,10 +103,9 @@ struct EwMeshArgs {
   double L[3], mL[3], alpha, coulomb_k, gscale;   // mL = M / L
 };
 
-// Fills the plan; true if the grid form takes the system (direct_bytes: the direct sum's
-// workspace).
-bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t direct_bytes,
-                  EwMeshPlan* pl);
+// The grid form takes systems of at least so many atoms with these wave numbers.
+int64_t ew_mesh_from(const int32_t kmax[3]);
+void ew_mesh_plan(int64_t n, const int32_t kmax[3], EwMeshPlan* pl);
 hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, const float* pos,
                           const float* q, float* force, double* energy, int accumulate, void* ws,
                           hipStream_t st);

@@ -5,7 +5,7 @@
 // (3e-8 of the forces at an oversampling of 1.75, from a float64 comparison with the direct
 // sum) lies below float32 rounding, so this is not a particle-mesh approximation with an
 // accuracy to choose: forces and energy are no further from a float64 sum than the direct sum's
-// (see the accuracy at launch_ew_mesh). With real separable basis functions t_n(l), n = 2 m + a:
+// (see the accuracy at ew_mesh_from). With real separable basis functions t_n(l), n = 2 m + a:
 // cos (a = 0) or sin (a = 1) of 2 pi m l / M, the pieces are
 //   b[l]    = sum_j q_j phi(l_x - X_j) phi(l_y - Y_j) phi(l_z - Z_j),   X = M_x u_x, ...
 //   R[n]    = sum_l b[l] t_nx(l_x) t_ny(l_y) t_nz(l_z)
@@ -846,19 +846,7 @@ __global__ __launch_bounds__(256) void k_em_energy(EwMeshArgs a) {
 
 }  // namespace
 
-// Which systems take the grid: from 1.5e8 (atom, half-space wave vector) pairs on, where it is
-// both faster and no less accurate than the direct sum (whole call, and RMS force error
-// against float64, direct and grid: 5,000 atoms x 1.2e4 wave vectors 140 us 2.7e-7, 80 us
-// 4.1e-7; 9,001 x 1.9e4 226 us 3.9e-7, 94 us 3.8e-7; 20,000 x 2.5e4 292 us 5.2e-7, 114 us 3.8e-7;
-// 40,000 x 9.3e4 1205 us 9.9e-7, 134 us 5.2e-7; 92,224 x 1.78e5 4897 us 2.4e-6, 208 us 4.2e-7;
-// the grid's times are from before its spreading and transforms took their present form: 92,224
-// now 169 us);
-// not where its workspace would be more than twice the direct sum's and 512 MiB (few atoms
-// with hundreds of wave numbers per axis).
-bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t direct_bytes,
-                  EwMeshPlan* pl) {
-  const double vectors = 0.5 * (2.0 * kmax[0] + 1) * (2.0 * kmax[1] + 1) * (2.0 * kmax[2] + 1);
-  if ((double)n * vectors < 1.5e8) return false;
+static void mesh_sizes(const int32_t kmax[3], EwMeshPlan* pl) {
   for (int d = 0; d < 3; ++d) {
     const int K = kmax[d];
     pl->K[d] = K;
@@ -869,6 +857,47 @@ bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t d
     pl->nt[d] = pl->M[d] / (d == 2 ? kTZ : kTX);
   }
   pl->nbins = (int64_t)pl->nt[0] * pl->nt[1] * pl->nt[2];
+}
+
+// Which systems take the grid: those of at least so many atoms, by a model of both forms' times in
+// microseconds,
+//   direct  26 + n x (rows and mz, up to multiples of 64) / 4e6
+//   grid    40 + (operations of the transforms) / 3.5e7 + n x 0.57 / (tiles, at most 500)
+// fitted to whole calls of 500 to 1,066,628 atoms with kmax 2 to 90 on each axis, and unequal ones up
+// to 255. The direct sum's cost is in its products; the grid's in the transforms, whatever the
+// atoms, and in the atoms of a tile, which one workgroup takes in turn: with few wave numbers there
+// are 48 tiles, and no number of atoms makes it the faster one. Direct and grid, us:
+//   kmax 4: 5,000 atoms 35 and 91, 92,224 129 and 1025, 1,066,628 719 and 12,604
+//   kmax 12: 9,001 76 and 82, 92,224 442 and 495
+//   kmax 16: 2,000 52 and 48, 9,001 108 and 62, 92,224 656 and 244
+//   kmax 30: 1,000 71 and 78, 2,000 99 and 81, 40,000 1419 and 106
+//   kmax 90: 500 487 and 1272, 3,000 2807 and 1318
+// Of 160 points measured it picks the slower form at 3, by 8-14% (2,000-4,000 atoms). The tiles are taken
+// as evenly filled: a system packed into a few of them takes the grid longer.
+// Accuracy does not decide: the grid is the closer one to a float64 sum at all points compared, since the
+// direct sum's float32 sums run over the atoms of a workgroup. RMS force error, direct and grid, alpha
+// 0.3 at 0.1 atoms/A^3, with the wave numbers that alpha needs: 3,000 atoms 2.3e-7 and 8.5e-8, 40,000
+// 1.05e-6 and 8.1e-8; with twice as many 9,001 8.2e-7 and 9.4e-8, with six times as many 2,500 1.7e-7
+// and 9.5e-8. Not under 2,000 atoms, nor where the grids take more than 512 MiB and more than the
+// direct sum's phase tables.
+int64_t ew_mesh_from(const int32_t kmax[3]) {
+  EwMeshPlan pl;
+  mesh_sizes(kmax, &pl);
+  const double N[3] = {(double)pl.N[0], (double)pl.N[1], (double)pl.N[2]},
+               M[3] = {(double)pl.M[0], (double)pl.M[1], (double)pl.M[2]};
+  const double rows = kmax[0] * (2.0 * kmax[1] + 1) + kmax[1] + 1;
+  const double direct = ceil(rows / 64) * 64 * ((2 * kmax[2] + 64) / 64) * 64 / 4e6;
+  const double grid = 0.57 / (pl.nbins < 500 ? (double)pl.nbins : 500.0);
+  if (direct <= grid) return INT64_MAX;
+  const double ops = 4 * M[0] * (M[1] * M[2] * N[2] + M[1] * N[1] * N[2] + N[0] * N[1] * N[2]);
+  double n = (14 + ops / 3.5e7) / (direct - grid);
+  const double bytes = 4 * M[0] * (M[1] * M[2] + 3 * N[1] * N[2]);
+  if (bytes > 536870912.0) n = fmax(n, bytes / (8.0 * (kmax[0] + 2 * kmax[1] + 2 * kmax[2] + 3)));
+  return n < 2000 ? 2000 : (int64_t)ceil(n);
+}
+
+void ew_mesh_plan(int64_t n, const int32_t kmax[3], EwMeshPlan* pl) {
+  mesh_sizes(kmax, pl);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t nn = (size_t)n;
   size_t o = al(sizeof(WsHeader));
@@ -897,7 +926,6 @@ bool ew_mesh_plan(const md_params* p, int64_t n, const int32_t kmax[3], size_t d
   pl->qblocks = (n + 255) / 256;
   pl->off_qpart = o; o = al(o + 16 * (size_t)pl->qblocks);
   pl->total = o;
-  return o <= 2 * direct_bytes || o <= (size_t)512 << 20;
 }
 
 hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, const float* pos,

@@ -1,0 +1,36 @@
+"""Host side of the Ewald reciprocal sum: which systems take the grid form, and the workspace. No
+call here reaches the GPU."""
+import pytest
+
+from paper_1611_04474_amd import api
+from paper_1611_04474_amd import workloads as W
+
+
+def params():
+    return dict(W.small_system().params(), flags=api.COULOMB_EWALD, ewald_alpha=0.3)
+
+
+def takes_grid(n, kmax):
+    """Whether n atoms (and 2 n) take the grid form: its workspace grows by 304 bytes an atom,
+    the direct sum's by more than its phase tables, 8 bytes for each of the axes' wave numbers."""
+    tables = 8 * ((kmax[0] + 1) + (2 * kmax[1] + 1) + (2 * kmax[2] + 1))
+    assert tables > 320, "the two cannot be told apart"
+    p = api.Params.from_dict(params())
+    return api.ewald_workspace_bytes(p, 2 * n, kmax) - api.ewald_workspace_bytes(p, n, kmax) < tables * n
+
+
+@pytest.mark.parametrize("n,kmax,grid", [
+    # many atoms, few wave numbers: few tiles, each with thousands of atoms for one workgroup
+    (1066628, (8, 8, 8), False), (92224, (8, 8, 8), False), (300000, (12, 12, 12), False),
+    # few atoms, many wave numbers: transforms that cost more than the direct sum's products
+    (100, (90, 90, 90), False), (300, (60, 55, 64), False), (900, (60, 60, 60), False),
+    (300, (150, 40, 40), False), (2000, (20, 255, 255), False),
+    # small systems with alpha's own wave numbers
+    (3000, (12, 12, 12), False),
+    # larger ones
+    (5000, (19, 19, 20), True), (9001, (16, 16, 16), True), (20000, (21, 21, 21), True),
+    (92224, (39, 39, 28), True), (22880, (170, 5, 20), True), (12000, (18, 18, 18), True),
+    (1066628, (20, 20, 20), True),
+])
+def test_form(n, kmax, grid):
+    assert takes_grid(n, kmax) == grid

@@ -16,6 +16,7 @@ import pytest
 from paper_1611_04474_amd import api
 from paper_1611_04474_amd import workloads as W
 
+from test_ewald_forms import takes_grid
 from test_gpu_ewald import _recip_gpu, ewald_params
 
 pytestmark = pytest.mark.gpu
@@ -81,6 +82,7 @@ def errors(gpu, n, box, alpha, kmax, seed=3):
 ])
 def test_grid_form_keeps_float32_accuracy(gpu, case, n, box, alpha, kmax):
     print("case:", case, n, box, alpha, kmax, flush=True)
+    assert takes_grid(n, kmax)
     rms, e = errors(gpu, n, box, alpha, kmax)
     print("RMS force error", rms, "energy", e, flush=True)
     assert rms <= 2.0 ** -22
@@ -99,6 +101,7 @@ def test_grid_form_branches(gpu, case, n, box, kmax):
     """The grid form's launch shapes, at sizes that take it. The bar grows with the wave numbers
     beyond twice what alpha needs (exp(-k^2/4 alpha^2) = 1e-6), as the potential's share does."""
     print("case:", case, n, box, kmax, flush=True)
+    assert takes_grid(n, kmax)
     alpha = 0.3
     beyond = max(k * math.pi / (alpha * L * math.sqrt(-math.log(1e-6))) for k, L in zip(kmax, box))
     rms, e = errors(gpu, n, box, alpha, kmax)
