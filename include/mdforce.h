@@ -225,8 +225,8 @@ md_status md_forces_f64(const md_params* p, int64_t n_atoms, const double* d_pos
  *   d_force   [n_atoms][3] float32 out, caller order: written, or added to when
  *             accumulate != 0 (e.g. onto the short-range forces)
  *   d_energy  [1] float64 out: reciprocal + self + background energy
- *   d_ws      workspace of md_ewald_workspace_bytes(p, n_atoms, kmax) bytes, 256-B aligned;
- *             its first word is a status word (MD_STATUS_NAN for a NaN position or charge),
+ *   d_ws      workspace of md_ewald_workspace_bytes(p, n_atoms, kmax) bytes (which depends on
+ *             n_atoms and kmax alone and never falls as n_atoms grows), 256-B aligned; its first word is a status word (MD_STATUS_NAN for a NaN position or charge),
  *             read with md_read_device_status
  * Errors: MD_ERR_INVALID_ARG (alpha, box, kmax, pointers), MD_ERR_WORKSPACE, MD_ERR_HIP.
  * md_ewald_workspace_bytes returns 0 for invalid arguments. */

@@ -56,7 +56,7 @@ struct EwArgs {
   float2* tab;                    // [(kx+1) + (2ky+1) + (2kz+1)][n]: X, then Y, then Z
   float2* parts;                  // [chunks][R][nzc] partial structure factors
   float2* g;                      // [R][nzc_pad] G (zero where excluded and in the padding)
-  double* fpart;                  // [splits][n][3] shares of the forces (splits > 1)
+  double* fpart;                  // [splits][n][3] shares of the forces (splits > 1), where parts was
   uint32_t* stat;                 // [qblocks] status bits
   double* erow;                   // [R][zblocks] energy partials
   double2* qpart;                 // [qblocks] (sum q^2, sum q) per setup block
@@ -421,7 +421,7 @@ struct EwPlan {
   int kx, ky, kz, nzc, nzc_pad, zblocks;
   int splits, split_rows;
   int64_t rows, chunks, chunk_atoms, qblocks;
-  size_t off_ups, off_tab, off_parts, off_g, off_fpart, off_erow, off_qpart, off_stat, total;
+  size_t off_ups, off_tab, off_parts, off_g, off_erow, off_qpart, off_stat, total;
 };
 
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -447,6 +447,7 @@ md_status ew_plan(const md_params* p, int64_t n, const int32_t kmax[3], EwPlan* 
   const int64_t tiles = (n + kEwTile - 1) / kEwTile > 0 ? (n + kEwTile - 1) / kEwTile : 1;
   int64_t chunks = (512 + rb * pl->zblocks - 1) / (rb * pl->zblocks);   // two per compute unit
   chunks = chunks < 1 ? 1 : chunks > tiles ? tiles : chunks;
+  const int64_t most_chunks = chunks;
   pl->chunk_atoms = (tiles + chunks - 1) / chunks * kEwTile;
   pl->chunks = n > 0 ? (n + pl->chunk_atoms - 1) / pl->chunk_atoms : 1;
   pl->qblocks = (n + 255) / 256 > 0 ? (n + 255) / 256 : 1;
@@ -461,9 +462,14 @@ md_status ew_plan(const md_params* p, int64_t n, const int32_t kmax[3], EwPlan* 
   size_t o = a256(sizeof(WsHeader));
   pl->off_ups = o;   o = a256(o + sizeof(uint4) * nn);
   pl->off_tab = o;   o = a256(o + sizeof(float2) * (size_t)trows * nn);
-  pl->off_parts = o; o = a256(o + sizeof(float2) * (size_t)pl->chunks * pl->rows * pl->nzc);
+  // the partial structure factors, and after them the shares of the forces in the same place. Both by
+  // bounds that never fall as n grows (the chunks before they are evened out; splits x n, with splits at most
+  // 512 / at + 1 and one share only from 32,768 atoms on), so that a workspace holds every smaller system
+  const int64_t shares = rt == 1 ? 0 : rt * at < 512 + at ? rt * at : at < 512 ? 512 + at : 1024;   // of 64 atoms
+  const size_t part_bytes = sizeof(float2) * (size_t)most_chunks * pl->rows * pl->nzc;
+  const size_t share_bytes = sizeof(double) * 3 * 64 * (size_t)shares;
+  pl->off_parts = o; o = a256(o + (part_bytes > share_bytes ? part_bytes : share_bytes));
   pl->off_g = o;     o = a256(o + sizeof(float2) * (size_t)pl->rows * pl->nzc_pad);
-  pl->off_fpart = o; o = a256(o + (pl->splits > 1 ? sizeof(double) * 3 * (size_t)pl->splits * nn : 0));
   pl->off_erow = o;  o = a256(o + sizeof(double) * (size_t)pl->rows * pl->zblocks);
   pl->off_qpart = o; o = a256(o + sizeof(double2) * (size_t)pl->qblocks);
   pl->off_stat = o;  o = a256(o + sizeof(uint32_t) * (size_t)pl->qblocks);
@@ -471,8 +477,18 @@ md_status ew_plan(const md_params* p, int64_t n, const int32_t kmax[3], EwPlan* 
   return MD_OK;
 }
 
-}  // namespace
+// Workspace of a call: it holds every call of fewer atoms too, whichever form those take.
+size_t ew_bytes(const md_params* p, int64_t n, const int32_t kmax[3], const EwPlan* direct) {
+  const int64_t from = ew_mesh_from(kmax);
+  if (n < from) return direct->total;
+  EwMeshPlan mesh;
+  ew_mesh_plan(n, kmax, &mesh);
+  EwPlan last;
+  ew_plan(p, from - 1, kmax, &last);
+  return mesh.total > last.total ? mesh.total : last.total;
+}
 
+}  // namespace
 }  // namespace md
 
 extern "C" {
@@ -480,10 +496,7 @@ extern "C" {
 size_t md_ewald_workspace_bytes(const md_params* p, int64_t n_atoms, const int32_t kmax[3]) {
   md::EwPlan pl;
   if (md::ew_plan(p, n_atoms, kmax, &pl) != MD_OK) return 0;
-  if (n_atoms < md::ew_mesh_from(kmax)) return pl.total;
-  md::EwMeshPlan mesh;
-  md::ew_mesh_plan(n_atoms, kmax, &mesh);
-  return mesh.total;
+  return md::ew_bytes(p, n_atoms, kmax, &pl);
 }
 
 md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d_pos,
@@ -497,16 +510,16 @@ md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d
   if (n_atoms > 0 && (!d_pos || !d_charge || !d_force ||
                       (((uintptr_t)d_pos | (uintptr_t)d_charge | (uintptr_t)d_force) & 3)))
     return MD_ERR_INVALID_ARG;
-  md::EwMeshPlan mesh;
-  const bool grid = n_atoms >= md::ew_mesh_from(kmax);
-  if (grid) md::ew_mesh_plan(n_atoms, kmax, &mesh);
-  if (!d_ws || ((uintptr_t)d_ws & 255) || ws_bytes < (grid ? mesh.total : pl.total))
+  if (!d_ws || ((uintptr_t)d_ws & 255) || ws_bytes < md::ew_bytes(p, n_atoms, kmax, &pl))
     return MD_ERR_WORKSPACE;
-  if (grid)
+  if (n_atoms >= md::ew_mesh_from(kmax)) {
+    md::EwMeshPlan mesh;
+    md::ew_mesh_plan(n_atoms, kmax, &mesh);
     return md::launch_ew_mesh(mesh, p, n_atoms, d_pos, d_charge, d_force, d_energy, accumulate ? 1 : 0,
                               d_ws, (hipStream_t)stream) == hipSuccess
                ? MD_OK
                : MD_ERR_HIP;
+  }
   md::EwArgs a;
   char* b = (char*)d_ws;
   a.n = n_atoms;
@@ -520,7 +533,7 @@ md_status md_ewald_recip_f32(const md_params* p, int64_t n_atoms, const float* d
   a.tab = (float2*)(b + pl.off_tab);
   a.parts = (float2*)(b + pl.off_parts);
   a.g = (float2*)(b + pl.off_g);
-  a.fpart = (double*)(b + pl.off_fpart);
+  a.fpart = (double*)(b + pl.off_parts);
   a.stat = (uint32_t*)(b + pl.off_stat);
   a.splits = pl.splits;
   a.split_rows = pl.split_rows;

@@ -34,3 +34,22 @@ def takes_grid(n, kmax):
 ])
 def test_form(n, kmax, grid):
     assert takes_grid(n, kmax) == grid
+
+
+@pytest.mark.parametrize("kmax", [(5, 5, 5), (9, 9, 9), (12, 12, 12), (14, 14, 14), (18, 18, 18), (21, 21, 21),
+                                  (1, 0, 0), (60, 0, 50), (8, 9, 46), (170, 5, 20), (40, 40, 40),
+                                  (20, 255, 255)])
+def test_workspace_holds_smaller_systems(kmax):
+    """One workspace sized for the largest system serves every smaller one, across the chunks and
+    shares of the direct sum and the number of atoms from which the grid takes over."""
+    p = api.Params.from_dict(params())
+    sizes = list(range(0, 2000, 7)) + list(range(2000, 50000, 61)) + list(range(50000, 1000000, 9973))
+    last = 0
+    for n in sizes:
+        nb = api.ewald_workspace_bytes(p, n, kmax)
+        assert nb >= last, n
+        last = nb
+    # the box and alpha do not enter: a run at constant pressure keeps its workspace
+    other = api.Params.from_dict(dict(params(), box=(77.0, 31.0, 290.0), ewald_alpha=1.1))
+    assert all(api.ewald_workspace_bytes(other, n, kmax) == api.ewald_workspace_bytes(p, n, kmax)
+               for n in sizes[::50])
