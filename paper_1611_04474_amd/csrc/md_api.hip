@@ -218,12 +218,12 @@ md_status make_plan(const md_params* p, int64_t n, int real_bytes, Plan* pl) {
                             : (size_t)real_bytes * kSlots * 3 * nn));
   pl->off_facc = o;      o = align_up(o + sizeof(float) * 3 * nn);
   // energy partials: one float64 per task, or one (float64: two) int64 per workgroup of the
-  // compacted kernel, as many as any flags could choose
+  // compacted kernel, as many as any flags could choose. Grids of more than kFsMaxCells cells have
+  // fewer, but keep the room of kFsMaxCells, so that a workspace serves a shrinking box
   pl->off_epart = o;
   const size_t task_parts = align_up(sizeof(double) * pl->n_tasks);
-  const size_t unit_parts = cells <= kFsMaxCells ? align_up(sizeof(long long) * (real_bytes / 4) *
-                                                            kFsMaxSplit * kFsMaxSlices * cells)
-                                                 : 0;
+  const size_t unit_parts = align_up(sizeof(long long) * (real_bytes / 4) * kFsMaxSplit * kFsMaxSlices *
+                                     (cells < kFsMaxCells ? cells : kFsMaxCells));
   o += task_parts > unit_parts ? task_parts : unit_parts;
   if (unit_parts > task_parts) pl->uncounted += unit_parts - task_parts;
   pl->off_lj = o;        o = align_up(o + (size_t)real_bytes * 2 * kMaxTypes * kMaxTypes);

@@ -103,9 +103,9 @@ struct Plan {
       off_part, off_facc, off_epart, off_lj, off_paircount, off_bhist, off_bstat, off_order,
       off_cost,
       off_zsplit, off_ukey, off_upos, off_kpart, total;
-  size_t uncounted;             // bytes that the no-allocation call's limit does not count:
-                                // the batch arguments, and the energy partials of a grid of
-                                // at most kFsMaxCells cells beyond one word per task
+  size_t uncounted;             // bytes that the no-allocation call's limit does not count: the
+                                // batch arguments, the energy partials beyond one word per task, and
+                                // the second set of kinetic-energy partials
   int bin_blocks;               // blocks of the LDS-histogram binning pass (0: global atomics)
   int64_t bin_chunk;            // atoms per such block
 };
