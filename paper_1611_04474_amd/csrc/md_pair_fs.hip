@@ -286,31 +286,37 @@ constexpr int kCoulSwitched = 0, kCoulPlain = 1, kCoulEwald = 2;
 
 // erfc(x) and exp(-x^2) for x >= 0 in float32, sharing the exponential: erfc = exp(-x^2)
 // g(q) / (1 + 2 x) with q = (x - 2)/(x + 2) (the form of Shepherd and Laframboise, Math. Comp. 36
-// (1981) 249); g's coefficients from a Chebyshev interpolation of (1 + 2 x) exp(x^2) erfc(x) on
-// [0, 6.5] in float64, where the degree leaves 8e-9 (beyond, the exponential is under 1e-18).
-// x^2 and its product with log2(e) carry their rounding errors along, so exp stays within about an
-// ulp. The library's erfcf (two branches, both taken in every wave) and expf took the kernel
-// at 92,224 atoms 183 us, this 167 (RMS force error of the electrostatics alone 1.59e-7 -> 1.60e-7, of
-// its energy 1.7e-7 -> 3e-8).
+// (1981) 249); g's coefficients by least squares of (1 + 2 x) exp(x^2) erfc(x) on [0, 6.5] in float64,
+// rounded to float32 one after the other and the rest fitted again each time, which leaves 1e-8 (beyond, the
+// exponential is under 1e-18). x^2 and its product with log2(e) carry their rounding errors along, and so do
+// 1 + 2 x, the quotient and the exponential in the last product. RMS error over x in 0.5 .. 4.5: erfc 5e-8, the
+// exponential 4e-8 (erfcf 5e-8, expf(-x x) 3e-8 .. 4e-7). The library's erfcf (two branches, both
+// taken in every wave) and expf took a whole call at 92,224 atoms 208 us, this 175; RMS force error against
+// float64 1.800e-7 and 1.798e-7, of the electrostatics alone 1.586e-7 and 1.586e-7 (without the three
+// corrections 173 us, 1.808e-7 and 1.596e-7).
 __device__ inline float erfc_exp(float x, float& ex) {
   const float xx = x * x;
   const float lo = fmaf(x, x, -xx);
   const float h = -1.44269504f * xx;
   const float l = fmaf(-1.44269504f, xx, -h) - fmaf(1.44269504f, lo, 1.92596299e-8f * xx);
-  ex = __builtin_amdgcn_exp2f(h);
-  ex = fmaf(ex, 0.693147181f * l, ex);
+  const float e0 = __builtin_amdgcn_exp2f(h);
+  const float e1 = e0 * (0.693147181f * l);
+  ex = e0 + e1;
   const float q = (x - 2.0f) * __builtin_amdgcn_rcpf(x + 2.0f);
-  float p = -0.000429302559f;
-  p = fmaf(p, q, -0.00128258815f);
-  p = fmaf(p, q, 0.00131015439f);
-  p = fmaf(p, q, 0.00866760268f);
-  p = fmaf(p, q, -0.00804970499f);
-  p = fmaf(p, q, -0.0542121652f);
-  p = fmaf(p, q, 0.164053117f);
-  p = fmaf(p, q, -0.166030842f);
-  p = fmaf(p, q, -0.092763879f);
-  p = fmaf(p, q, 1.27697839f);
-  return ex * (p * __builtin_amdgcn_rcpf(fmaf(2.0f, x, 1.0f)));
+  float p = -0.000429934531f;
+  p = fmaf(p, q, -0.00128212711f);
+  p = fmaf(p, q, 0.00131415739f);
+  p = fmaf(p, q, 0.00867054798f);
+  p = fmaf(p, q, -0.0080512343f);
+  p = fmaf(p, q, -0.054213874f);
+  p = fmaf(p, q, 0.164053246f);
+  p = fmaf(p, q, -0.166030556f);
+  p = fmaf(p, q, -0.0927638784f);
+  p = fmaf(p, q, 1.27697837f);
+  const float d = fmaf(2.0f, x, 1.0f), rd = __builtin_amdgcn_rcpf(d), dl = fmaf(2.0f, x, 1.0f - d);
+  float y = p * rd;
+  y = fmaf(fmaf(-y, dl, fmaf(-y, d, p)), rd, y);
+  return fmaf(e0, y, e1 * y);
 }
 
 // 1/sqrt(u) in float64: the hardware's estimate (about 2^-23) and one third-order step,
