@@ -303,7 +303,11 @@ SysArgs<Real> make_args(const md_params* p, const Plan& pl, int64_t n, const Rea
   a.rs2 = (Real)rs2;
   a.inv_sw = p->r_switch < p->r_cut ? (Real)(1.0 / (rc2 - rs2)) : Real(0);
   a.coulomb_k = (Real)p->coulomb_k;
-  a.ewald_alpha = (p->flags & MD_COULOMB_EWALD) ? (Real)p->ewald_alpha : Real(0);
+  // float32: at most 1e17 / r_cut, where erfc(alpha r) is 0 for every distance that counts, so that
+  // (alpha r)^2 stays finite
+  double alpha = (p->flags & MD_COULOMB_EWALD) ? p->ewald_alpha : 0.0;
+  if (sizeof(Real) == 4) alpha = fmin(alpha, 1e17 / p->r_cut);
+  a.ewald_alpha = (Real)alpha;
   a.flags = p->flags;
   a.compact = uses_compact(p, (int)sizeof(Real)) ? 1 : 0;
   a.half_shell = a.compact && half_shell(p) ? 1 : 0;

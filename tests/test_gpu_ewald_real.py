@@ -64,3 +64,13 @@ def test_lone_pairs(gpu, alpha, r_lo, r_hi):
     rel = err / (2.0 ** -24 * (8 + 3 * (2 * x ** 2 + 1)) * np.linalg.norm(ref, axis=1))[inside]
     print("largest error over its bar", rel.max(), "RMS", np.sqrt((rel ** 2).mean()), flush=True)
     assert rel.max() <= 1.0 and np.sqrt((rel ** 2).mean()) <= 1.0 / 3.0
+
+
+@pytest.mark.parametrize("alpha", [30.0, 1.0e10, 1.0e20, 3.0e37])
+def test_large_alpha_leaves_nothing(gpu, alpha):
+    """erfc and the exponential of an argument from 9 on to beyond the root of the largest float32 are 0 (or
+    under the sums' units), never NaN."""
+    print("case: large alpha", alpha, flush=True)
+    params, pos, q = lone_pairs(1.0, 0.5, 6.0)
+    f, e, status = run(gpu, dict(params, ewald_alpha=alpha), pos, np.full_like(q, 0.5))
+    assert status == 0 and e == 0.0 and not f.any()
