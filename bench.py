@@ -543,8 +543,9 @@ def ablation(steps, dev):
     out["drain_depth_sweep_half_shell"] = sweep
     out["speedup_half_over_full_shell"] = (out["compacted_full_shell"]["pair_ms_median"] /
                                            out["compacted_half_shell"]["pair_ms_median"])
-    # workgroups per home cell: the 92,224-atom system (486 cells) and a 20,000-atom cube
-    # of 4^3 cells (a median serving request), whole evaluations
+    # parts of each home cell's atoms: the 92,224-atom system (486 cells) and a 20,000-atom cube
+    # of 4^3 cells (a median serving request), whole evaluations, with the workgroups that each
+    # takes (the library also cuts small grids' neighbour lists into slices)
     split = {}
     for label, sysm in (("apoa1_92k_486_cells", s), ("cube_20k_64_cells",
                                                     W.gen_system(20000, (58.5, 58.5, 58.5), 12))):
@@ -569,12 +570,11 @@ def ablation(steps, dev):
                 api.forces_stages(P, pos_s, typ_s, q_s, f_s, energy, ws, api.STAGE_FINALIZE)
             torch.cuda.synchronize()
             pair_ms = pct([e[1].elapsed_time(e[2]) for e in evs[2:]], 50)
-            row[str(sv)] = {"pair_ms_median": pair_ms, "pairs_per_s_pair_stage": pairs / (pair_ms * 1e-3)}
-        cells = int(np.prod(api.workspace_layout(sysm.params(), sysm.n)["dims"]))
-        sa = 256 // cells
-        row["automatic"] = 4 if sa >= 4 else 2 if sa >= 2 else 1
+            row[str(sv)] = {"pair_ms_median": pair_ms, "pairs_per_s_pair_stage": pairs / (pair_ms * 1e-3),
+                            "workgroups": api.workspace_layout(P, sysm.n)["n_energy_partials"]}
+        row["automatic"] = {"workgroups": api.workspace_layout(sysm.params(), sysm.n)["n_energy_partials"]}
         split[label] = row
-    out["workgroups_per_home_cell"] = split
+    out["parts_per_home_cell"] = split
     return out
 
 

@@ -92,12 +92,17 @@ enum {
 #define MD_PAIR_DRAIN_MASK (3u << 5)
 #define MD_PAIR_DRAIN(d) ((uint32_t)((d) == 1 ? 1 : (d) == 3 ? 2 : (d) == 4 ? 3 : 0) << 5)
 
-/* md_params.flags bits 8-9: workgroups of the compacted kernel per home cell, each taking
+/* md_params.flags bits 8-9: parts of a home cell's atoms in the compacted kernel, each taking
  * every s-th group of the cell's home atoms (the work units of the loop over home atoms of
- * Algorithm 1, spread over more compute units). 0 chooses automatically (1 on grids of more
- * than 256 cells, more on smaller ones); MD_PAIR_SPLIT(s) forces s = 1, 2 or 4. On grids of
- * at most 256 cells the neighbour list may also be cut into slices of a workgroup each,
- * chosen from the grid and the atom count alone. Results are the same bits for every s. Not with MD_PAIR_PREDICATED (MD_ERR_INVALID_ARG). */
+ * Algorithm 1, spread over more compute units). 0 chooses automatically: 1 to 8 on grids of at
+ * most 256 cells, 1 on larger ones, of which up to 128 cells of a grid of at most 2,048 (those of
+ * the last round of workgroups) take 2 to 6; MD_PAIR_SPLIT(s) forces s = 1, 2 or 4 on every
+ * cell. On grids of at most 256 cells the half shell also cuts a cell's neighbour list into
+ * up to 8 slices of a workgroup each, whatever s is, so a cell has s times as many workgroups;
+ * their number follows the grid, the atom count, the precision and the shell (and a list longer
+ * than the LDS holds is cut into more, which depends on the type count, MD_DIAG_COUNTERS and
+ * the drain depth too). Results are the same bits for every s. Not with MD_PAIR_PREDICATED
+ * (MD_ERR_INVALID_ARG). */
 #define MD_PAIR_SPLIT_MASK (3u << 8)
 #define MD_PAIR_SPLIT(s) ((uint32_t)((s) == 1 ? 1 : (s) == 2 ? 2 : (s) == 4 ? 3 : 0) << 8)
 
@@ -106,7 +111,10 @@ enum {
   MD_STATUS_NAN = 1u << 0,          /* a position is NaN */
   MD_STATUS_OUT_OF_BOX = 1u << 1,   /* a coordinate lies outside [-L, 2L) */
   MD_STATUS_BAD_TYPE = 1u << 2,     /* a type index outside [0, n_types) */
-  MD_STATUS_FIXED_OVERFLOW = 1u << 3/* a force does not fit the 64-bit fixed-point range */
+  MD_STATUS_FIXED_OVERFLOW = 1u << 3/* a force does not fit the 64-bit fixed-point range: a pair's
+                                       or a neighbour-side sum's component of 1.3e8 kcal/mol/A or
+                                       more, or an atom's sum, which is guaranteed to fit up
+                                       to 2.4e9 (more with fewer slices, MD_PAIR_SPLIT) */
 };
 
 /* Problem description. The box is orthorhombic and periodic on all three axes;
@@ -128,7 +136,8 @@ typedef struct {
 /* Library support (no passage of the paper defines it: the caller owns all device memory).
  * Bytes of device workspace needed by md_forces_f32 (double_precision = 0) or
  * md_forces_f64 (double_precision = 1) for n_atoms atoms with p->flags (the flags
- * choose the pair kernel, whose per-atom buffers differ in size). Returns 0 when the
+ * choose the pair kernel, whose per-atom buffers differ in size). At a given number of
+ * atoms the size does not grow as the box shrinks (up to 32,768 cells). Returns 0 when the
  * parameters are invalid. The workspace must be 256-byte aligned; its contents
  * need no initialisation. Between calls they are scratch, except that the
  * compacted kernel leaves each home cell's measured time there: the next call on the
@@ -178,9 +187,11 @@ md_status md_forces_f32_stages(const md_params* p, int64_t n_atoms, const float*
  *     per device, created when the library's code is first used on that device and held
  *     until the process ends. Its device address is looked up once per device, on the
  *     first call with that device current.
- *   - Systems whose md_workspace_bytes(p, n_atoms, 0), without the up to 128 KiB of energy
- *     partials of small grids, exceeds that size are rejected with MD_ERR_CAPACITY before anything is enqueued (at 8 atom types about 230,000 atoms
- *     of the 0.1 atoms/A^3 systems). Other argument errors as for md_forces_f32.
+ *   - Systems whose md_workspace_bytes(p, n_atoms, 0) exceeds that size are rejected with
+ *     MD_ERR_CAPACITY before anything is enqueued (at 8 atom types about 230,000 atoms
+ *     of the 0.1 atoms/A^3 systems); not counted are the arguments of a batched call (512
+ *     bytes), up to 128 KiB of energy partials and the second set of kinetic-energy
+ *     partials (8 bytes per 256 atoms). Other argument errors as for md_forces_f32.
  *   - Every call on one device uses that device's one array: calls that overlap on one
  *     device (other streams, other host threads) race and give undefined results;
  *     serialise them. Each call starts from whatever the previous one left, which is

@@ -32,7 +32,7 @@ PAIR_SPLIT_MASK = 3 << 8
 
 
 def PAIR_SPLIT(s):
-    """Flag bits forcing s = 1, 2 or 4 workgroups per home cell (0: automatic)."""
+    """Flag bits forcing s = 1, 2 or 4 parts of each home cell's atoms (0: automatic)."""
     return {1: 1 << 8, 2: 2 << 8, 4: 3 << 8}[int(s)]
 
 

@@ -162,9 +162,6 @@ FsWork md_fs_work(uint32_t flags, int real_bytes, int64_t n_cells, int64_t n, bo
   return best;
 }
 
-// Grid rule: n_d = floor(L_d / r_cut), one cell fewer when L_d/n_d exceeds r_cut by
-// less than 1e-3 A (so rounding of a coordinate at a cell face never hides a pair),
-// and at least 2 cells per axis (L >= 2 r_cut keeps the minimum image unique).
 static bool half_shell(const md_params* p) {
   return !(p->flags & (MD_ACCUM_F32_ATOMIC | MD_PAIR_FULL_SHELL));
 }
@@ -175,6 +172,9 @@ static int64_t fs_units(const md_params* p, const Plan& pl, int64_t n) {
   return ((pl.n_cells - w.nx) * w.split + w.nx * w.xsplit) * w.slices;
 }
 
+// Grid rule: n_d = floor(L_d / r_cut), one cell fewer when L_d/n_d exceeds r_cut by
+// less than 1e-3 A (so rounding of a coordinate at a cell face never hides a pair),
+// and at least 2 cells per axis (L >= 2 r_cut keeps the minimum image unique).
 md_status make_plan(const md_params* p, int64_t n, int real_bytes, Plan* pl) {
   md_status s = check_params(p);
   if (s != MD_OK) return s;

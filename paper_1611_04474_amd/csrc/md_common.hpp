@@ -38,9 +38,10 @@ __host__ __device__ inline int md_pair_drain(uint32_t flags) {
 // into `split` interleaved parts (`xsplit` in nx of the cells: the longest ones or the shortest
 // ones of the launch order), and one workgroup takes a slice and a part.
 // A home atom's partial force is rounded to fixed point once per slice, so the number of
-// slices depends on the grid and the atom count alone, never on the split that a caller
-// forces or on the batch a system runs in: those change which workgroup does the work and
-// not one bit of the result.
+// slices depends on the grid, the atom count, the precision and the shell (and, where a list
+// does not fit the LDS, on what its capacity depends on: types, counters, drain depth), never on the
+// split that a caller forces or on the batch a system runs in: those change which workgroup
+// does the work and not one bit of the result.
 struct FsWork {
   int split;      // parts of a cell's home atoms
   int slices;     // slices of its neighbour list

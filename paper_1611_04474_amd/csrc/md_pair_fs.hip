@@ -664,7 +664,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
   };
   for (int P0 = (fu.unit / n_split) * slice_len(); P0 < total; P0 += fu.su * slice_len()) {
     const int P1 = min(total, P0 + slice_len());
-    // stage the neighbour-list slice [P0, P1): wave w copies images w and w + 16 (both z
+    // stage the neighbour-list slice [P0, P1): wave w copies images w, w + kNW, .. (both z
     // halves, to their two segments), issuing all loads of up to 4 x 64 atoms before the
     // LDS stores; the half shell also clears the slots' accumulators
     for (int m = w; m < kImg; m += kNW) {
@@ -1170,7 +1170,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
     }
     __syncthreads();
     if (kHalf) {
-      // neighbour-side sums of this slice to the per-atom sums (wave w: images w, w + 16)
+      // neighbour-side sums of this slice to the per-atom sums (wave w: images w, w + kNW, ..)
       for (int m = w; m < kImg; m += kNW) {
         const Img im = H.img[m];
         for (int e = lane; e < im.count; e += 64) {
@@ -1314,7 +1314,7 @@ void k_pair_fs(SysArgs<Real> a, int cap) {
   if (last && (threadIdx.x & 63) == 0) record_cost(a, fu, t0, c0, blockIdx.x == 0);
 }
 
-// One launch for a batch: block b is cell order[b - cum[s]] of system s.
+// One launch for a batch: block b is unit b - cum[s] of system s (fs_unit).
 template <bool kHalf, int kCoul, bool kClamp, bool kDiag, int kDrain>
 __global__ __launch_bounds__(64 * kWaves<float>) __attribute__((amdgpu_waves_per_eu(kWaves<float> / 4, kWaves<float> / 4)))
 void k_pair_fs_batch(Batch b, int cap) {
