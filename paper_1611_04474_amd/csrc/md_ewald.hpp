@@ -68,8 +68,8 @@ struct EwMeshPlan {
                                 // points; tiles
   int64_t nbins, nepart, qblocks;
   size_t off_ups, off_rec, off_win, off_dwin, off_slot, off_ids, off_sid, off_count, off_start,
-      off_buf0, off_buf1, off_buf2, off_tab[3], off_tabT[3], off_gfac[3], off_ksq[3], off_epart,
-      off_qpart, total;
+      off_buf0, off_buf1, off_buf2, off_pot, off_tab[3], off_tabT[3], off_gfac[3], off_ksq[3],
+      off_epart, off_qpart, total;
 };
 
 struct EwMeshArgs {
@@ -89,7 +89,8 @@ struct EwMeshArgs {
   int* sid;            // [n] indices by bin, in order
   int* count;          // [nbins], pad words apart
   int* start;          // [nbins + 1]
-  float* buf0;         // [Mx][My][Mz] charges, then the potential's coefficients
+  float* buf0;         // [Mx][My][Mz] charges
+  double* pot;         // [Mx][My][Mz] the potential's coefficients, in the same place
   float* buf1;         // [Mx][Ny][Nz] charges transformed along z and y
   double* buf2;        // the same of the potential, transformed back along x
   double *tab[3], *tabT[3];  // [N][M] and [M][N] basis functions per axis

@@ -494,14 +494,16 @@ __global__ __launch_bounds__(256) void k_em_spread(EwMeshArgs a) {
 // groups of 16, the rounding of a group left noise of a grid point's width in the potential, which the
 // derivative multiplies by the points per wavelength, and float32 tables put 7e-8 into the energy;
 // the potential's intermediates are kept in float64 too, since noise along one axis alone counts
-// four times that of the stored grid, which the window averages over the other two. RMS force
-// error, float32 products, float64 ones, and float64 intermediates: 92,224 atoms 4.4e-7, 1.4e-7, 8.4e-8; 9,001
-// with twice the wave numbers they need 5.9e-7, 1.8e-7, 9.4e-8; 2,018 with six times 1.9e-7 and 1.0e-7.
+// four times that of the stored grid, which the window averages over the other two, and so is the
+// stored grid, whose rounding follows the longest waves of the box. RMS force error, float32 products, float64
+// ones, float64 intermediates, and grid: 92,224 atoms 4.4e-7, 1.4e-7, 8.4e-8, 7.7e-8; 9,001 with twice
+// the wave numbers they need 5.9e-7, 1.8e-7, 9.4e-8, 7.8e-8; 33,880 in a 22 x 22 x 700 A box
+// 5.8e-7 with float64 intermediates, 8.9e-8 with the grid.
 // A lane's latency to memory, not the products (1.2 GFLOP, 15 us for all
 // six at 92,224 atoms), is what a transform takes its time for, so each kernel does two of them: z
 // and y of a plane, x forward and back of a column, y and z of a plane, the intermediate in LDS.
 // 92,224 atoms (grid 144 x 144 x 112, 80 x 80 x 64 modes): 60.1 us in six launches of
-// float32 products, 43.2 in these three, 60.3 in float64.
+// float32 products, 43.2 in these three, 61.5 in float64.
 constexpr int kTrWaves = 8, kTrThreads = 64 * kTrWaves;
 
 // (p + a 32-bit byte offset: one uniform base and a lane offset per load)
@@ -702,7 +704,7 @@ __global__ __launch_bounds__(kTrThreads) __attribute__((amdgpu_waves_per_eu(4)))
       if (c >= nj) break;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        a.buf0[(x * M1 + 16 * (r0 + r) + kk + 4 * i) * M2 + j0 + 16 * c + row] = (float)acc[c][i];
+        a.pot[(x * M1 + 16 * (r0 + r) + kk + 4 * i) * M2 + j0 + 16 * c + row] = acc[c][i];
     }
   }
 }
@@ -730,7 +732,7 @@ __device__ inline float wave_sum3(float x, float y, float z) {
 }
 
 // Forces, one workgroup of 8 (4 on the largest grids) waves per tile: the potential's coefficients around the tile
-// (17 x 17 x 25 points) in LDS; a wave takes an atom of the tile's bin at a time, its lanes the
+// (17 x 17 x 25 points) in LDS, in float32 less the value at the tile's corner; a wave takes an atom of the tile's bin at a time, its lanes the
 // 100 (x, y) rows of the window (two rounds), each summing its row's 10 z values from both ends
 // with phi_z and phi_z' (uniform, in scalar registers). The coefficient at the atom's own grid
 // point is taken off every value: a constant exerts no force, and the derivative's rounding
@@ -738,11 +740,11 @@ __device__ inline float wave_sum3(float x, float y, float z) {
 // instruction issue, about 200 per atom. 92,224 atoms: 54.6 us with 4 waves and a sum per
 // component; 49.2 with one sum for the three; 46.9 with the buffer's old force read an atom
 // ahead; 39.7 with 8 waves (more than four workgroups do not fit a compute unit's LDS, and
-// four of 8 waves fill it; 10, 12 and 16 waves 47, 43 and 43).
+// four of 8 waves fill it; 10, 12 and 16 waves 47, 43 and 43); 41.3 with the potential read in float64.
 template <int kThreads>
 __global__ __launch_bounds__(kThreads) void k_em_force(EwMeshArgs a) {
   constexpr int kRX = kTX + kW - 1, kRZ = kTZ + kW - 1;   // points around the tile
-  constexpr int kQuads = (kRZ + 3) / 4;                   // 16-byte loads per row
+  constexpr int kQuads = (kRZ + 3) / 4;                   // 32-byte loads per row
   __shared__ float s_c[kRX * kRX * kRZ];
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
   const int bin = blockIdx.x;
@@ -752,6 +754,7 @@ __global__ __launch_bounds__(kThreads) void k_em_force(EwMeshArgs a) {
   // rows start 4 points before a multiple of 16 on an axis of a multiple of 16, so a quad never
   // straddles the box edge and is aligned
   static_assert(kLo == 4 && kTZ % 4 == 0, "aligned quads");
+  const double ref = a.pot[((int64_t)(kTX * tx) * a.M[1] + kTX * ty) * a.M[2] + kTZ * tz];
 #pragma unroll 4
   for (int e = t; e < kRX * kRX * kQuads; e += kThreads) {
     const int qd = e % kQuads, rw = e / kQuads;
@@ -759,13 +762,13 @@ __global__ __launch_bounds__(kThreads) void k_em_force(EwMeshArgs a) {
     x += x < 0 ? a.M[0] : x >= a.M[0] ? -a.M[0] : 0;
     y += y < 0 ? a.M[1] : y >= a.M[1] ? -a.M[1] : 0;
     z += z < 0 ? a.M[2] : z >= a.M[2] ? -a.M[2] : 0;
-    const float4 v = *reinterpret_cast<const float4*>(&a.buf0[((int64_t)x * a.M[1] + y) * a.M[2] + z]);
+    const double4 v = *reinterpret_cast<const double4*>(&a.pot[((int64_t)x * a.M[1] + y) * a.M[2] + z]);
     float* d = s_c + rw * kRZ + 4 * qd;
-    d[0] = v.x;
+    d[0] = (float)(v.x - ref);
     if (4 * qd + 1 < kRZ) {
-      d[1] = v.y;
-      d[2] = v.z;
-      d[3] = v.w;
+      d[1] = (float)(v.y - ref);
+      d[2] = (float)(v.z - ref);
+      d[3] = (float)(v.w - ref);
     }
   }
   static_assert(kRZ % 4 == 1, "the last quad of a row holds one point");
@@ -862,23 +865,23 @@ static void mesh_sizes(const int32_t kmax[3], EwMeshPlan* pl) {
 // Which systems take the grid: those of at least so many atoms, by a model of both forms' times in
 // microseconds,
 //   direct  26 + n x (rows and mz, up to multiples of 64) / 4e6
-//   grid    40 + (operations of the transforms) / 3.5e7 + n x 0.57 / (tiles, at most 500)
+//   grid    42 + (operations of the transforms) / 3.5e7 + n x 0.57 / (tiles, at most 500)
 // fitted to whole calls of 500 to 1,066,628 atoms with kmax 2 to 90 on each axis, and unequal ones up
 // to 255. The direct sum's cost is in its products; the grid's in the transforms, whatever the
 // atoms, and in the atoms of a tile, which one workgroup takes in turn: with few wave numbers there
 // are 48 tiles, and no number of atoms makes it the faster one. Direct and grid, us:
-//   kmax 4: 5,000 atoms 35 and 91, 92,224 129 and 1025, 1,066,628 719 and 12,604
-//   kmax 12: 9,001 76 and 82, 92,224 442 and 495
-//   kmax 16: 2,000 52 and 48, 9,001 108 and 62, 92,224 656 and 244
-//   kmax 30: 1,000 71 and 78, 2,000 99 and 81, 40,000 1419 and 106
-//   kmax 90: 500 487 and 1272, 3,000 2807 and 1318
-// Of 160 points measured it picks the slower form at 3, by 8-14% (2,000-4,000 atoms). The tiles are taken
+//   kmax 4: 5,000 atoms 35 and 92, 92,224 130 and 1024, 1,066,628 724 and 12,603
+//   kmax 12: 9,001 78 and 83, 92,224 447 and 494
+//   kmax 16: 2,000 53 and 51, 9,001 108 and 63, 92,224 663 and 245
+//   kmax 30: 1,000 72 and 82, 2,000 100 and 83, 40,000 1422 and 109
+//   kmax 90: 500 489 and 1314, 3,000 2803 and 1371
+// Of 160 points measured it picks the slower form at 2, by 5 and 17% (3,000 and 4,000 atoms). The tiles are taken
 // as evenly filled: a system packed into a few of them takes the grid longer.
 // Accuracy does not decide: the grid is the closer one to a float64 sum at all points compared, since the
 // direct sum's float32 sums run over the atoms of a workgroup. RMS force error, direct and grid, alpha
-// 0.3 at 0.1 atoms/A^3, with the wave numbers that alpha needs: 3,000 atoms 2.3e-7 and 8.5e-8, 40,000
-// 1.05e-6 and 8.1e-8; with twice as many 9,001 8.2e-7 and 9.4e-8, with six times as many 2,500 1.7e-7
-// and 9.5e-8. Not under 2,000 atoms, nor where the grids take more than 512 MiB and more than the
+// 0.3 at 0.1 atoms/A^3, with the wave numbers that alpha needs: 3,000 atoms 2.3e-7 and 8e-8, 40,000
+// 1.05e-6 and 7.6e-8; with twice as many 9,001 8.2e-7 and 7.8e-8, with six times as many 2,500 1.7e-7
+// and 8e-8; 33,880 in a 22 x 22 x 700 A box 5.3e-7 and 8.9e-8. Not under 2,000 atoms, nor where the grids take more than 512 MiB and more than the
 // direct sum's phase tables.
 int64_t ew_mesh_from(const int32_t kmax[3]) {
   EwMeshPlan pl;
@@ -890,8 +893,8 @@ int64_t ew_mesh_from(const int32_t kmax[3]) {
   const double grid = 0.57 / (pl.nbins < 500 ? (double)pl.nbins : 500.0);
   if (direct <= grid) return INT64_MAX;
   const double ops = 4 * M[0] * (M[1] * M[2] * N[2] + M[1] * N[1] * N[2] + N[0] * N[1] * N[2]);
-  double n = (14 + ops / 3.5e7) / (direct - grid);
-  const double bytes = 4 * M[0] * (M[1] * M[2] + 3 * N[1] * N[2]);
+  double n = (16 + ops / 3.5e7) / (direct - grid);
+  const double bytes = 8 * M[0] * (M[1] * M[2] + N[1] * N[2]);
   if (bytes > 536870912.0) n = fmax(n, bytes / (8.0 * (kmax[0] + 2 * kmax[1] + 2 * kmax[2] + 3)));
   return n < 2000 ? 2000 : (int64_t)ceil(n);
 }
@@ -900,20 +903,25 @@ void ew_mesh_plan(int64_t n, const int32_t kmax[3], EwMeshPlan* pl) {
   mesh_sizes(kmax, pl);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t nn = (size_t)n;
+  const size_t M0 = pl->M[0], M1 = pl->M[1], M2 = pl->M[2], N0 = pl->N[0], N1 = pl->N[1], N2 = pl->N[2];
   size_t o = al(sizeof(WsHeader));
-  pl->off_ups = o;   o = al(o + 16 * nn);
+  // the fractions, bins and indices in the callers' order are done with when k_em_middle writes buf2
+  pl->off_buf2 = pl->off_ups = o;
+  pl->off_slot = pl->off_ups + al(16 * nn);
+  pl->off_ids = pl->off_slot + al(8 * nn);
+  const size_t atoms = al(16 * nn) + al(8 * nn) + al(4 * nn), back = al(8 * M0 * N1 * N2);
+  o += atoms > back ? atoms : back;
   pl->off_rec = o;   o = al(o + 16 * nn);
   pl->off_win = o;   o = al(o + 128 * nn);
   pl->off_dwin = o;  o = al(o + 128 * nn);
-  pl->off_slot = o;  o = al(o + 8 * nn);
-  pl->off_ids = o;   o = al(o + 4 * nn);
   pl->off_sid = o;   o = al(o + 4 * nn);
   pl->off_count = o; o = al(o + 4 * (size_t)(mesh_pad(pl->nbins) * pl->nbins));
   pl->off_start = o; o = al(o + 4 * (size_t)(pl->nbins + 1));
-  const size_t M0 = pl->M[0], M1 = pl->M[1], M2 = pl->M[2], N0 = pl->N[0], N1 = pl->N[1], N2 = pl->N[2];
-  pl->off_buf0 = o;  o = al(o + 4 * M0 * M1 * M2);
-  pl->off_buf1 = o;  o = al(o + 4 * M0 * N1 * N2);
-  pl->off_buf2 = o;  o = al(o + 8 * M0 * N1 * N2);
+  // the charges, and their transform along z and y (each axis has fewer modes than points), are done with
+  // when k_em_back writes the potential
+  pl->off_pot = pl->off_buf0 = o;
+  pl->off_buf1 = o + 4 * M0 * M1 * M2;
+  o = al(o + 8 * M0 * M1 * M2);
   for (int d = 0; d < 3; ++d) {
     const size_t e = (size_t)pl->N[d] * pl->M[d];
     pl->off_tab[d] = o;  o = al(o + 8 * e);
@@ -950,6 +958,7 @@ hipError_t launch_ew_mesh(const EwMeshPlan& pl, const md_params* p, int64_t n, c
   a.count = (int*)(b + pl.off_count);
   a.start = (int*)(b + pl.off_start);
   a.buf0 = (float*)(b + pl.off_buf0);
+  a.pot = (double*)(b + pl.off_pot);
   a.buf1 = (float*)(b + pl.off_buf1);
   a.buf2 = (double*)(b + pl.off_buf2);
   a.epart = (double*)(b + pl.off_epart);

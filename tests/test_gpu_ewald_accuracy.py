@@ -96,6 +96,7 @@ def test_grid_form_keeps_float32_accuracy(gpu, case, n, box, alpha, kmax):
     ("long axis: two column tiles, three row tiles", 9000, (100.0, 30.0, 30.0), (150, 40, 40)),
     ("over 4,096 tiles: bins scanned by a kernel of their own", 2000, (30.0, 31.0, 32.0), (50, 50, 50)),
     ("over 24,576 tiles: four waves a tile", 2100, (30.0, 31.0, 32.0), (90, 90, 90)),
+    ("the longest axis: over 64 KB of LDS in the last transform", 33880, (22.0, 22.0, 700.0), (7, 7, 255)),
 ])
 def test_grid_form_branches(gpu, case, n, box, kmax):
     """The grid form's launch shapes, at sizes that take it. The bar grows with the wave numbers
