@@ -41,8 +41,8 @@ METRIC = "within-cutoff pair-interactions/s @92k atoms; p50/p99 latency mixed ba
 # HBM bytes per launch of the pair kernel at 92,224 atoms, from the FETCH_SIZE and
 # WRITE_SIZE counters scaled by a copy of known size (profiles/traffic_pair_fs_92k.md);
 # valid only for the kernel code they were taken on (kernel_code_sha256)
-PAIR_TRAFFIC = {"kernel_sha256": "5f7d79dc7429a790ec22c8e0e453909c30557f7dd232a92a21ee88739e06e149",
-                "bytes": (16140 + 30718) * 1024}
+PAIR_TRAFFIC = {"kernel_sha256": "94a93e5a0cdbc0c6e4c769c6f204d863e223d4b26131e1f27f24b3c876c22745",
+                "bytes": (16008 + 30715) * 1024}
 
 
 def parse():
