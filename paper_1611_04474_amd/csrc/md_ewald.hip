@@ -11,8 +11,8 @@
 // two give equal terms), plus the self term -k alpha/sqrt(pi) sum q^2 and the neutralising
 // background -k pi Q^2 / (2 V alpha^2).
 //
-// This file holds the entry points and the direct sum, which smaller systems take; larger ones
-// take the same sum through a grid (md_ewald_mesh.hip).
+// This file holds the entry points and the direct sum, which systems of few atoms or few wave
+// numbers take; the others take the same sum through a grid (md_ewald_mesh.hip, ew_mesh_from).
 //
 // Phases are exact modulo one turn: each atom's fractional coordinate is held as a 32-bit
 // fixed-point fraction u, so m u (mod 2^32) is the phase of wave number m with no rounding,
@@ -27,8 +27,8 @@
 //                 one sine/cosine of the exact (mx, my) phase per atom and row;
 //   k_ew_final    the shares of an atom's force added; fixed-order sum of the row energies, self
 //                 and background, and the status word.
-// Systems that come here are small (larger ones take the grid), so launches and idle compute
-// units count: 3,000 atoms and 6,095 wave vectors took seven launches, 47 workgroups for the
+// Most systems that come here are small (larger ones with many wave numbers take the grid), so
+// launches and idle compute units count: 3,000 atoms and 6,095 wave vectors took seven launches, 47 workgroups for the
 // forces and 47 dependent loads per wave vector, 89 us; 41 this way, the same bits.
 // Every sum runs in a fixed order, so the results are the same bits on every run.
 #include <math.h>
