@@ -41,8 +41,8 @@ METRIC = "within-cutoff pair-interactions/s @92k atoms; p50/p99 latency mixed ba
 # HBM bytes per launch of the pair kernel at 92,224 atoms, from the FETCH_SIZE and
 # WRITE_SIZE counters scaled by a copy of known size (profiles/traffic_pair_fs_92k.md);
 # valid only for the kernel code they were taken on (kernel_code_sha256)
-PAIR_TRAFFIC = {"kernel_sha256": "94a93e5a0cdbc0c6e4c769c6f204d863e223d4b26131e1f27f24b3c876c22745",
-                "bytes": (16008 + 30715) * 1024}
+PAIR_TRAFFIC = {"kernel_sha256": "9a67ef996f7888365f2a0a6e14336fa1730cf6e169394ddede4d618068c29e87",
+                "bytes": (16024 + 30708) * 1024}
 
 
 def parse():

@@ -317,6 +317,9 @@ SysArgs<Real> make_args(const md_params* p, const Plan& pl, int64_t n, const Rea
   a.fs_xlong = fw.xlong;
   a.fs_xsplit = fw.xsplit;
   a.fs_split = fw.split;
+  a.own_nx = fw.nx;
+  a.own_xsplit = fw.xsplit;
+  a.own_split = fw.split;
   a.fs_slices = a.fs_su = fw.slices;
   a.fs_parts = fs_workgroups(a);
   return a;
@@ -365,9 +368,12 @@ static bool same_kind(const md_params* x, const md_params* y) {
 // the chip; in a batch the others fill it, and a split only repeats staging. Each system
 // keeps as many workgroups per cell as leave none of them longer than a 512th of the batch's
 // work (two per compute unit), at most its own choice; its slices (which fix the results'
-// bits) stay, taken in turn by fewer workgroups. A cell's cost is about its atoms squared plus
-// the staging and group overhead. Systems with the costliest workgroups come first, so that
-// short ones fill the tail.
+// bits) stay, taken in turn by fewer workgroups, and so do its parts, whole ones dealt to fewer
+// workgroups (fs_unit): a share of a neighbour's sum then has a bound that a system accepted alone
+// keeps (kAccRange). Against parts of a new split: 2 systems of 9,001 atoms 90.8 -> 88.1 us, 4
+// 139.3 -> 133.1, 4 of 3,000 105.4 -> 100.8, 6 of 6,000 134.0 -> 136.2, 16 of 2,000 to 200,000 1059.6 ->
+// 1061.8. A cell's cost is about its atoms squared plus the staging and group overhead. Systems with
+// the costliest workgroups come first, so that short ones fill the tail.
 static void batch_units(int n, SysArgs<float>* sys) {
   if (n == 1) return;
   double cost[kBatchMax], total = 0;
@@ -379,11 +385,14 @@ static void batch_units(int n, SysArgs<float>* sys) {
   for (int s = 0; s < n; ++s) {
     SysArgs<float>& a = sys[s];
     if (!(a.flags & MD_PAIR_SPLIT_MASK)) {   // a split that the caller forces stays
-      a.fs_nx = 0;
       const int units = (int)fmin(64.0, ceil(cost[s] * 512.0 / total));
       a.fs_su = units < a.fs_su ? units : a.fs_su;
-      const int split = (units + a.fs_su - 1) / a.fs_su;
-      a.fs_split = split < a.fs_split ? split : a.fs_split;
+      int split = (units + a.fs_su - 1) / a.fs_su;
+      split = split < a.own_split ? split : a.own_split;
+      // fewer parts where they are as long (of 6 own parts 3 pairs, not 2 pairs and 2 single ones)
+      const int most = (a.own_split + split - 1) / split;
+      a.fs_split = (a.own_split + most - 1) / most;
+      if (a.fs_split < a.own_split || split == 1) a.fs_nx = 0;   // otherwise its own choice as it is
     }
     cost[s] /= (double)(a.fs_su * a.fs_split);
   }

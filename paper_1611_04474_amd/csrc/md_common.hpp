@@ -180,6 +180,10 @@ struct SysArgs {
   int fs_slices;               // slices of its neighbour list, at least (FsWork)
   int fs_su;                   // slices spread over workgroups (fs_slices, or fewer in a batch
                                // that fills the chip: then a workgroup takes several in turn)
+  // fs_nx, fs_xsplit and fs_split of a call of its own: in a batch fs_split parts are made of
+  // these (see fs_unit)
+  int64_t own_nx;
+  int own_xsplit, own_split;
 };
 
 // Workgroups of the compacted kernel for one system.
@@ -189,7 +193,7 @@ __host__ __device__ inline int64_t fs_workgroups(const SysArgs<Real>& a) {
 }
 
 // Up to kBatchMax systems evaluated by one launch of each kernel of the path. Their
-// arguments (about 350 bytes each) stand in device memory, in each system's workspace, put
+// arguments (about 380 bytes each) stand in device memory, in each system's workspace, put
 // there by k_put_args; the kernels get the systems' block ranges and the arguments'
 // addresses. Block b of a batched launch belongs to the system s with cum[s] <= b < cum[s+1],
 // as its local block b - cum[s]. Handed over by value instead, ten systems fill the 4 KB of

@@ -79,10 +79,14 @@ constexpr float kBigU = 1.0e30f;    // squared distance given to lanes that must
 // Range of the per-atom 64-bit fixed-point sums of the float32 path: units of 2^-28
 // kcal/mol/A, magnitudes below 2^35. In the half shell an atom's sum gathers one
 // neighbour-side partial from each of the 14 images that stage it, in each of the n_split
-// workgroups of the staging cell (its home image and the 13 cells that have its cell
+// parts of the staging cell (its home image and the 13 cells that have its cell
 // ahead), each below 2^27 (kNbrPartialMax, also the bound of one pair's term), and one
 // home-side partial per LDS slice of its home cell's neighbour list, S of them, sharing
-// what is left: (2^35 - 14 n_split 2^27) / S each. In the full shell an atom's S home-side
+// what is left: (2^35 - 14 n_split 2^27) / S each. In a batch a workgroup takes several whole parts
+// of the system's own split, and its neighbour-side partials may reach as many times 2^27: a
+// batch accepts what a call of its own does. (Where some cells have a part more, the launch order
+// says which, so a share near the bound can be inside it in one call and outside in the next.) In
+// the full shell an atom's S home-side
 // partials are each below 2^35 / S. Every partial is checked, so a sum can never wrap.
 constexpr float kNbrPartialMax = 134217728.f;      // 2^27
 constexpr float kAccRange = 34359738368.f;         // 2^35
@@ -165,6 +169,9 @@ struct Hdr {
   int n_seg;
   int total;        // neighbour-list length
   int n_slice, len; // slices that it is staged in, and their length
+  // batches: own parts that this workgroup takes, and its k-th group: part + step k + skip (k / own)
+  int own, step, skip;
+  uint32_t inv;     // 2^32 / own
   int iters;        // binary-search steps that cover the longest segment
   int next;         // next group of home atoms to hand out
   int done;         // waves that have added their energy to esum
@@ -418,10 +425,11 @@ __device__ inline void lds_store_u16_lanes4(uint32_t a0, uint32_t a1, uint32_t a
 }
 
 // A workgroup's work: unit `unit` of the split x su of home cell `cell`; its energy goes to
-// partial `slot`.
+// partial `slot`. In a batch, part p of `split` is made of the parts p, p + split, ... of the `own`
+// that the cell has in a call of its own.
 struct FsUnit {
   int64_t cell, slot;
-  int unit, split, su;
+  int unit, split, su, own;
 };
 
 // Workgroup b: units 0 of the cells with the usual split in launch order, their units 1, ...,
@@ -442,6 +450,8 @@ __device__ inline FsUnit fs_unit(const SysArgs<Real>& a, int64_t b) {
   }
   f.cell = a.order[first + u % nt];
   f.unit = (int)(u / nt);
+  const uint32_t at = first + u % nt, ox = (uint32_t)a.own_nx;
+  f.own = (a.fs_xlong ? at < ox : at >= (uint32_t)a.n_cells - ox) ? a.own_xsplit : a.own_split;
   return f;
 }
 
@@ -489,7 +499,8 @@ struct Pre {
 // and e, and pairs beyond the cutoff need no test (the switch variable s clamps to 0).
 // kDiag: count filter passes, cutoff passes and filtered slots (MD_DIAG_COUNTERS).
 // kHalf: the half shell (64-bit fixed-point sums only). kDrain: force batches per drain.
-template <typename Real, bool kHalf, int kCoul, bool kClamp, bool kDiag, int kDrain>
+// kBatch: a system of a batched call (float32).
+template <typename Real, bool kHalf, int kCoul, bool kClamp, bool kDiag, int kDrain, bool kBatch>
 __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real>& a, int cap,
                                                               const FsUnit& fu) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
@@ -624,6 +635,14 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
       // slices: equal, at most cap (a multiple of 64) long
       const int ns = max(max(1, a.fs_slices), (tot + cap - 1) / cap);
       H.n_slice = ns;
+      if (kBatch) {
+        const int own = (fu.own - fu.unit % fu.split + fu.split - 1) / fu.split;
+        H.step = own == 1 ? fu.own : fu.split;
+        H.skip = own == 1 ? 0 : fu.own - own * fu.split;
+        H.inv = own == 1 ? 0 : 0xffffffffu / (uint32_t)own + 1;
+        // a whole cell: whichever split the launch order would give it
+        H.own = fu.split == 1 ? max(a.own_split, a.own_xsplit) : own;
+      }
       H.len = ((tot + ns - 1) / ns + 63) & ~63;
       H.done = 0;
       H.esum[0] = H.esum[1] = 0;
@@ -645,7 +664,7 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
   // workgroup takes slices unit / n_split, + su, ...
   const int n_slice = H.n_slice;
   // largest home-side partial of one slice (see kAccRange)
-  const float home_max = (kHalf ? kAccRange - 14.f * (float)max(a.fs_split, a.fs_xsplit) * kNbrPartialMax : kAccRange) /
+  const float home_max = (kHalf ? kAccRange - 14.f * (float)max(kBatch ? a.own_split : a.fs_split, kBatch ? a.own_xsplit : a.fs_xsplit) * kNbrPartialMax : kAccRange) /
                          (float)n_slice;
   const Real R = vsqrt(rc2) + Real(kWin);
   // energy: float32 in units of 2^-24 kcal/mol; float64 two-word (e_fix, e_lo): exact,
@@ -761,7 +780,11 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
     while (true) {
       int o = 0;
       if (lane == 0) o = atomicAdd(&H.next, 1);
-      o = part + n_split * __builtin_amdgcn_readfirstlane(__shfl(o, 0));
+      o = __builtin_amdgcn_readfirstlane(__shfl(o, 0));
+      if constexpr (kBatch)
+        o = part + __builtin_amdgcn_readfirstlane(H.step * o + H.skip * (int)__umulhi((uint32_t)o, H.inv));
+      else
+        o = part + n_split * o;
       if (o >= n_grp_q) break;
       const int ib = kQ * (down ? n_grp_q - 1 - o : o);
       const int nv = min(kQ, nA - ib);   // home atoms present in this group
@@ -1181,10 +1204,11 @@ __device__ __attribute__((always_inline)) inline bool pair_fs(const SysArgs<Real
           for (int c = 0; c < 3; ++c) {
             if constexpr (kF32) {
               // units of 2^-24 to the sums' 2^-28, each partial below 2^27 kcal/mol/A (2^51
-              // units, kNbrPartialMax)
+              // units, kNbrPartialMax) for each of the own parts
               const long long v = sJ[3 * (dst - P0) + c];
               constexpr long long kLim = (long long)kNbrPartialMax << 24;
-              if (v >= kLim || v < -kLim) st |= MD_STATUS_FIXED_OVERFLOW;
+              const long long lim = kBatch ? kLim * __builtin_amdgcn_readfirstlane(H.own) : kLim;
+              if (v >= lim || v < -lim) st |= MD_STATUS_FIXED_OVERFLOW;
               else if (v != 0)
                 global_add(&a.acc64[(int64_t)c * a.n + src],
                            (long long)((unsigned long long)v << 4));
@@ -1310,7 +1334,7 @@ void k_pair_fs(SysArgs<Real> a, int cap) {
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   const uint64_t c0 = __builtin_amdgcn_s_memtime();
   const FsUnit fu = fs_unit(a, blockIdx.x);
-  const bool last = pair_fs<Real, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, fu);
+  const bool last = pair_fs<Real, kHalf, kCoul, kClamp, kDiag, kDrain, false>(a, cap, fu);
   if (last && (threadIdx.x & 63) == 0) record_cost(a, fu, t0, c0, blockIdx.x == 0);
 }
 
@@ -1323,7 +1347,7 @@ void k_pair_fs_batch(Batch b, int cap) {
   int64_t blk;
   const SysArgs<float> a = batch_args(batch_pick(b, blockIdx.x, blk));
   const FsUnit fu = fs_unit(a, blk);
-  const bool last = pair_fs<float, kHalf, kCoul, kClamp, kDiag, kDrain>(a, cap, fu);
+  const bool last = pair_fs<float, kHalf, kCoul, kClamp, kDiag, kDrain, true>(a, cap, fu);
   if (last && (threadIdx.x & 63) == 0) record_cost(a, fu, t0, c0, blk == 0);
 }
 
